@@ -336,6 +336,8 @@ struct MatCtx {
   int64_t n_fix;             // stage-2 re-arrangement wavefronts: entries of dirty_list, else n_bunches
   int32_t *stale;            // bound plans: set (and never cleared) when stage 1 finds a dirty tile in a
                              // bunch outside dirty_list (row_ptr rewritten in place since plan time)
+  const int32_t *order;  // stage 1's wavefront slots: the bunch each takes, -1 = none (NULL: slot = bunch)
+  int64_t n_slots;       // entries of order
   int32_t *dbg_start;    // debug plans only
   int32_t *dbg_dirty;
   uint32_t *dbg_heads;
@@ -740,11 +742,21 @@ void sss_stage1(MatCtx a) {
   extern __shared__ uint32_t lds_words[];
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
-  const int64_t tb = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
-  if (tb >= a.n_bunches) return;
+  int64_t tb = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
+  if (a.order) {
+    if (tb >= a.n_slots) return;
+    tb = __builtin_amdgcn_readfirstlane(a.order[tb]);
+    if (tb < 0) return;
+  } else if (tb >= a.n_bunches) {
+    return;
+  }
   const int32_t brow = a.bunch_row ? a.bunch_row[tb] : -1;
   stage1_bunch<DT, W, DEBUG>(a, tb, lds_words + wid * stage1_lds_words(W, a.S), lane, brow);
 }
+
+// gfx950 (one partition) hands consecutive workgroups to its 8 XCDs in turn,
+// workgroup b to XCD b mod 8, and every XCD has its own L2.
+constexpr int kXcds = 8;
 
 // Plan time: the first row of every thread-bunch, the rightmost match of its
 // first nonzero (Section 3.2's tile boundary search), one thread per bunch.
@@ -775,6 +787,104 @@ __global__ void sss_mark_dirty_bunches(const int32_t *__restrict__ rp, int32_t m
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x) {
     const int32_t p = rp[r];
     if (p > 0 && p == rp[r + 1]) atomicOr(words + (p - 1) / SWT * stride, bit);
+  }
+}
+
+// Stage 1's column order.  A bunch inside a long row reads a narrow slice of
+// the columns (a row's columns ascend), so such bunches are sorted by their
+// place in their row and dealt to the XCDs in eight equal runs: each XCD's L2
+// then holds one moving slice of x instead of all of it.  The bunches of
+// short rows read all over x and follow in their own order, dealt in turn.
+// What bounds these gathers is how long a miss of L1 takes, and a hit in L2
+// takes less than half of a miss: 1M-row power law in FP64 (8 MB of x, W = 4,
+// S = 4) 221 -> 183 us per product, 4M-row Zipf 1.8 in FP32 (16 MB, W = 16,
+// S = 2) 1,103 -> 812 us, both with the same y bit for bit.
+//
+// A bunch counts as inside a long row when the row of its middle nonzero has
+// at least SWT of them.  SWT / 2 and SWT / 4 measured 2% faster on the first
+// matrix (179 us) and 2 to 5% slower on the second (848 us), whose bunches
+// are twice as long; 2 SWT and 4 SWT 2 to 10% slower on both.
+constexpr int kOrderBins = 256;  // places in a row; bin kOrderBins: short rows
+
+__global__ __launch_bounds__(256) void sss_order_keys(const int32_t *__restrict__ rp, int32_t m, int32_t nnz,
+                                                      int64_t SWT, int64_t n_bunches,
+                                                      const int32_t *__restrict__ bunch_row,
+                                                      uint32_t *__restrict__ keys, uint32_t *__restrict__ hist) {
+  __shared__ uint32_t count[kOrderBins + 1];
+  for (int i = threadIdx.x; i <= kOrderBins; i += blockDim.x) count[i] = 0u;
+  __syncthreads();
+  const int64_t tb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (tb < n_bunches) {
+    const int32_t mid = (int32_t)imin64(tb * SWT + SWT / 2, (int64_t)nnz - 1);
+    // the row of nonzero mid, between the first rows of this bunch and the next
+    int32_t lo = bunch_row[tb] & 0x7fffffff;
+    int32_t hi = tb + 1 < n_bunches ? bunch_row[tb + 1] & 0x7fffffff : m;
+    while (lo < hi) {
+      const int32_t c = lo + (hi - lo + 1) / 2;
+      if (rp[c] <= mid) lo = c;
+      else hi = c - 1;
+    }
+    const int32_t p = rp[lo];
+    const int64_t len = (lo < m ? (int64_t)rp[lo + 1] : (int64_t)nnz) - p;
+    const int64_t at = (int64_t)(mid - p);
+    const uint32_t key = len >= SWT && at >= 0 ? (uint32_t)imin64(at * kOrderBins / len, kOrderBins - 1)
+                                            : (uint32_t)kOrderBins;
+    keys[tb] = key;
+    atomicAdd(&count[key], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i <= kOrderBins; i += blockDim.x)
+    if (count[i]) atomicAdd(&hist[i], count[i]);
+}
+
+// The slot of the t-th wavefront of XCD k: workgroup b of B wavefronts runs
+// on XCD b mod kXcds.
+__device__ __forceinline__ int64_t xcd_slot(int64_t k, int64_t t, int B) { return (k + kXcds * (t / B)) * B + t % B; }
+
+// hist: the bunches per bin; cursor: zeros.  Within a bin the order is that
+// of the atomics, which decides only when a bunch runs.
+__global__ __launch_bounds__(256) void sss_order_scatter(const uint32_t *__restrict__ keys, int64_t n_bunches,
+                                                         int64_t n_slots, int B, const uint32_t *__restrict__ hist,
+                                                         uint32_t *__restrict__ cursor, int32_t *__restrict__ order) {
+  __shared__ uint32_t first[kOrderBins], count[kOrderBins + 1], base[kOrderBins + 1];
+  const int t = threadIdx.x;
+  static_assert(kOrderBins == 256, "one bin per thread");
+  first[t] = hist[t];
+  count[t] = 0u;
+  if (t == 0) count[kOrderBins] = 0u;
+  __syncthreads();
+  for (int d = 1; d < kOrderBins; d <<= 1) {  // inclusive scan of the long bins
+    const uint32_t v = t >= d ? first[t - d] : 0u;
+    __syncthreads();
+    first[t] += v;
+    __syncthreads();
+  }
+  const int64_t n_long = first[kOrderBins - 1];
+  const int64_t tb = (int64_t)blockIdx.x * blockDim.x + t;
+  uint32_t key = 0, mine = 0;
+  if (tb < n_bunches) {
+    key = keys[tb];
+    mine = atomicAdd(&count[key], 1u);
+  }
+  __syncthreads();
+  for (int i = t; i <= kOrderBins; i += blockDim.x) base[i] = count[i] ? atomicAdd(&cursor[i], count[i]) : 0u;
+  __syncthreads();
+  const int64_t each = n_long / kXcds, more = n_long % kXcds;  // the first `more` XCDs take one long bunch more
+  if (tb < n_bunches) {
+    int64_t i = (int64_t)base[key] + mine;
+    int64_t slot;
+    if (key < (uint32_t)kOrderBins) {
+      i += key > 0 ? first[key - 1] : 0u;
+      const int64_t head = more * (each + 1);
+      const int64_t k = i < head ? i / (each + 1) : more + (i - head) / each;
+      slot = xcd_slot(k, i < head ? i % (each + 1) : (i - head) % each, B);
+    } else {
+      i += n_long;
+      slot = xcd_slot(i % kXcds, i / kXcds, B);
+    }
+    order[slot] = (int32_t)tb;
+  } else if (tb < n_slots) {
+    order[xcd_slot(tb % kXcds, tb / kXcds, B)] = -1;
   }
 }
 
@@ -848,10 +958,6 @@ __global__ __launch_bounds__(256) void sss_floor(MatCtx a, typename VT<DT>::y_t 
 // within the matrix from the plan (found at plan time by the same
 // rightmost-match search the method uses for rows); stage 2 runs that search
 // over bunch_base itself.
-// gfx950 (one partition) hands consecutive workgroups to its 8 XCDs in turn,
-// workgroup b to XCD b mod 8, and every XCD has its own L2.
-constexpr int kXcds = 8;
-
 struct BatchArgs {
   const MatCtx *mats;
   const int64_t *bunch_base;  // [count+1]
@@ -1212,6 +1318,7 @@ constexpr size_t kFixupLdsBytes = 64 * 1024;  // LDS of one fixup workgroup
 // also holds the carry pass's staged entries
 static_assert(4 * kWave * 4 >= (kWave + kShortRun) * (sizeof(double) + sizeof(int)), "carry staging fits");
 constexpr int kMaxS = 16;
+constexpr int kMaxB = 4;
 
 bool dtype_ok(int dt) { return dt == SSS_F64 || dt == SSS_F32 || dt == SSS_BF16; }
 size_t y_size(int dt) { return dt == SSS_F64 ? 8 : 4; }
@@ -1287,6 +1394,9 @@ struct sss_plan_s {
   int32_t *dirty_list = nullptr; // bind_rows plans: the bunches with a dirty tile, found at plan time
   int64_t n_listed = 0;
   int32_t *stale = nullptr;      // bind_rows plans: one word, see MatCtx::stale
+  int32_t *order = nullptr;      // bind_rows plans that gain from it: see sss_order_scatter
+  uint32_t *order_hist = nullptr;
+  int64_t n_slots = 0;
   int32_t *dbg_start = nullptr;
   int32_t *dbg_dirty = nullptr;
   uint32_t *dbg_heads = nullptr;
@@ -1310,8 +1420,8 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // entry per tile), every array 256-byte aligned.
 struct AuxLayout {
   int64_t n_tiles = 0, n_bunches = 0;
-  size_t dmask = 0, spec = 0, sidx = 0, sval = 0, tail = 0, brow = 0, dlist = 0, stale = 0, dstart = 0, ddirty = 0,
-         dheads = 0;
+  size_t dmask = 0, spec = 0, sidx = 0, sval = 0, tail = 0, brow = 0, dlist = 0, stale = 0, order = 0, ohist = 0,
+         dstart = 0, ddirty = 0, dheads = 0;
   size_t total = 0;
 };
 
@@ -1332,6 +1442,8 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug) {
     L.brow = off; off = align256(off + sizeof(int32_t) * (nb + 1));
     L.dlist = off; off = align256(off + sizeof(int32_t) * (nb + 1));
     L.stale = off; off = align256(off + sizeof(int32_t));
+    L.order = off; off = align256(off + sizeof(int32_t) * (nb + kXcds * kMaxB));
+    L.ohist = off; off = align256(off + sizeof(uint32_t) * 2 * (kOrderBins + 1));
   }
   if (debug) {
     L.dstart = off; off = align256(off + sizeof(int32_t) * (nt + 1));
@@ -1356,6 +1468,8 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
   p->bunch_row = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
   p->dirty_list = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.dlist) : nullptr;
   p->stale = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.stale) : nullptr;
+  p->order = nullptr;  // set by plan_order
+  p->order_hist = p->bind_rows ? reinterpret_cast<uint32_t *>(base + L.ohist) : nullptr;
   p->dbg_start = p->debug ? reinterpret_cast<int32_t *>(base + L.dstart) : nullptr;
   p->dbg_dirty = p->debug ? reinterpret_cast<int32_t *>(base + L.ddirty) : nullptr;
   p->dbg_heads = p->debug ? reinterpret_cast<uint32_t *>(base + L.dheads) : nullptr;
@@ -1410,6 +1524,8 @@ MatCtx plan_ctx(sss_plan p, const int32_t *row_ptr, const int32_t *col, const vo
   a.dirty_list = p->dirty_list;
   a.n_fix = p->dirty_list ? p->n_listed : p->n_bunches;
   a.stale = p->stale;
+  a.order = p->order;
+  a.n_slots = p->n_slots;
   a.dbg_start = p->dbg_start; a.dbg_dirty = p->dbg_dirty; a.dbg_heads = p->dbg_heads;
   return a;
 }
@@ -1430,7 +1546,7 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
   Stage1Fn k1 = pick_stage1(p->dt, p->W, p->debug != 0);
   if (!k1) return SSS_ERR_UNSUPPORTED;
   const MatCtx a1 = plan_ctx(p, row_ptr, col, val, x, y);
-  const int64_t blocks1 = (p->n_bunches + p->B - 1) / p->B;
+  const int64_t blocks1 = ((p->order ? p->n_slots : p->n_bunches) + p->B - 1) / p->B;
   const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
   hipLaunchKernelGGL(k1, dim3((unsigned)blocks1), dim3(p->B * kWave), lds1, stream, a1);
   SSS_HIP(hipGetLastError());
@@ -1636,6 +1752,37 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
 
 namespace {
 
+// Bound plans: stage 1's column order (see sss_order_keys), where it can
+// gain: x must be larger than what stays in an XCD's 4 MB L2 beside the
+// streamed matrix (power law, Zipf and dense rows: 2.16 MB of x 1% slower to
+// 1% faster, 2.8 MB 1 to 3%, 3.2 MB 2 to 4%, 4 MB 6 to 9%, 8 MB 9 to 22%
+// faster), and enough bunches must lie in long rows.  The order is made on
+// the device; the host reads back only how many bunches are short.  The
+// speculator's space holds the keys (stage 1 writes every entry that stage 2
+// reads).
+constexpr int64_t kOrderMinX = int64_t(5) << 19;
+constexpr int64_t kOrderMinBunches = 2048;
+
+int plan_order(sss_plan p, const int32_t *row_ptr, int32_t *order, int64_t SWT, hipStream_t s) {
+  const int64_t nb = p->n_bunches, x_bytes = p->n * (int64_t)y_size(p->dt);
+  if (x_bytes < kOrderMinX || nb < kOrderMinBunches) return SSS_OK;
+  const int64_t group = (int64_t)kXcds * p->B, n_slots = (nb + group - 1) / group * group;
+  uint32_t *keys = reinterpret_cast<uint32_t *>(p->speculator), *hist = p->order_hist;
+  hipLaunchKernelGGL(sss_order_keys, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, row_ptr, (int32_t)p->m,
+                     (int32_t)p->nnz, SWT, nb, p->bunch_row, keys, hist);
+  SSS_HIP(hipGetLastError());
+  hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, keys, nb, n_slots,
+                     p->B, hist, hist + kOrderBins + 1, order);
+  SSS_HIP(hipGetLastError());
+  uint32_t n_short = 0;
+  SSS_HIP(hipMemcpyAsync(&n_short, hist + kOrderBins, sizeof(n_short), hipMemcpyDeviceToHost, s));
+  SSS_HIP(hipStreamSynchronize(s));
+  if ((nb - (int64_t)n_short) * 16 < nb) return SSS_OK;
+  p->order = order;
+  p->n_slots = n_slots;
+  return SSS_OK;
+}
+
 // Bound plans: mark every bunch with a dirty tile on the device, then list
 // them on the host (bunch order) and copy the list to the plan; synchronises
 // `s`.
@@ -1690,7 +1837,7 @@ int sss_csr_spmv_plan_create(int64_t m, int64_t n, int64_t nnz, const int32_t *r
     }
   }
   if (!(W == 4 || W == 8 || W == 16)) return SSS_ERR_UNSUPPORTED;
-  if (S < 1 || S > kMaxS || B < 1 || B > 4) return SSS_ERR_INVALID_VALUE;
+  if (S < 1 || S > kMaxS || B < 1 || B > kMaxB) return SSS_ERR_INVALID_VALUE;
   if (o.bind_rows && m > 0 && nnz > 0 && !row_ptr) return SSS_ERR_INVALID_VALUE;
   if (!o.workspace && o.workspace_bytes) return SSS_ERR_INVALID_VALUE;
   sss_plan p = new sss_plan_s();
@@ -1713,6 +1860,10 @@ int sss_csr_spmv_plan_create(int64_t m, int64_t n, int64_t nnz, const int32_t *r
     // the bunches with a dirty tile (marked in bunch_row's top bit), listed
     // in order so that stage 2 gives only them a wavefront
     if (rc == SSS_OK) rc = plan_list_dirty(p, row_ptr, SWT, s);
+    if (rc == SSS_OK) {
+      const AuxLayout L = aux_layout(nnz, p->W, p->S, true, p->debug != 0);
+      rc = plan_order(p, row_ptr, reinterpret_cast<int32_t *>(static_cast<char *>(p->aux) + L.order), SWT, s);
+    }
   }
   if (rc == SSS_OK) {
     e = hipStreamSynchronize(s);
@@ -1904,7 +2055,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   const int S = o.S ? o.S : default_S(dt);
   const int B = o.B ? o.B : kDefaultB;
   if (!(W == 4 || W == 8 || W == 16)) return SSS_ERR_UNSUPPORTED;
-  if (S < 1 || S > kMaxS || B < 1 || B > 4 || o.debug) return SSS_ERR_INVALID_VALUE;
+  if (S < 1 || S > kMaxS || B < 1 || B > kMaxB || o.debug) return SSS_ERR_INVALID_VALUE;
   // SELECTOR mode: every matrix's S from its class scores, W shared
   std::vector<int> sel_S;
   if (o.mode == SSS_MODE_SELECTOR && count > 0 && sss_selector_loaded()) {
