@@ -144,7 +144,11 @@ int sss_csr_spmv_plan_create(int64_t m, int64_t n, int64_t nnz, const int32_t *r
 int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtype dt,
                                      const sss_plan_opts *opts, size_t *bytes);
 
-/* y = A x with a plan (both stages of Section 3.2, enqueued on `stream`).
+/* y = A x with a plan (both stages of Section 3.2, enqueued on `stream` as one
+ * launch that does both stages' work per thread-bunch, and a second, short
+ * one for rows that cross into a thread-bunch by more than 64 entries; a
+ * bind_rows plan that has no such row leaves the second out.  Debug plans run
+ * the two stages as separate launches; y is the same bit for bit).
  * The sizes are the plan's; val/x/y types follow the plan's dtype.  m = 0 is a
  * no-op; nnz = 0 zeroes y.  SSS_ERR_INVALID_VALUE for a NULL plan, a NULL
  * pointer whose array is non-empty, or misaligned col/val.  SSS_ERR_PLAN_MISMATCH
@@ -154,9 +158,10 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
  * (rp[r] <= b < rp[r + 1]) and searches again where it no longer holds, so
  * rewriting that array in place (same m and nnz) gives a correct y, at the
  * search's cost; a dirty tile in a bunch the plan did not list then marks
- * the plan stale, and from that call on stage 2 also re-arranges the
- * unlisted dirty bunches (one after another per 64 bunches: correct, slower;
- * make a new plan for the new structure). */
+ * the plan stale, and from that call on stage 2 (debug plans and
+ * sss_csr_spmv_stage2) also re-arranges the unlisted dirty bunches (one after
+ * another per 64 bunches: correct, slower; make a new plan for the new
+ * structure). */
 int sss_csr_spmv_execute(sss_plan p, const int32_t *row_ptr, const int32_t *col,
                          const void *val, const void *x, void *y, void *stream);
 
@@ -276,11 +281,13 @@ int sss_batch_plan_create_grid(int count, const sss_csr_desc *mats, sss_dtype dt
  * NULL. */
 int sss_batch_plan_schedule(sss_plan p, int count, int *W, int *S);
 
-/* Run a batch plan on `stream`: two launches (stage 1, stage 2), no
- * allocation, no host synchronisation. */
+/* Run a batch plan on `stream`: one launch that does both stages' work, and a
+ * second, short one where some row crosses into a thread-bunch by more than
+ * 64 entries or some matrix has no nonzero; no allocation, no host
+ * synchronisation. */
 int sss_batch_execute(sss_plan p, void *stream);
 
-/* The same two launches captured once into a HIP graph (on the first call,
+/* The same launches captured once into a HIP graph (on the first call,
  * on a private stream) and replayed on `stream` by every call. */
 int sss_batch_graph_launch(sss_plan p, void *stream);
 

@@ -24,6 +24,10 @@
 //     ends inside row `stop` hands its last partial to the next tile through
 //     the transmitter.  Dirty tiles are recorded, as <start, stop, tile>, in
 //     the bunch's own speculator slots, with a per-bunch dirty mask.
+// sss_csr_spmv_execute and batches run the fused kernel (sss_fused), which
+// does both stages' work in one launch; the split kernels below it serve
+// sss_csr_spmv_stage1 / stage2 and debug plans, which record the paper's
+// intermediate state.
 // Stage 2 (Section 3.2, checking prediction; the paper runs it on a CPU core)
 // is one device kernel with three independent parts: the synchronizer carries
 // (one thread per run of bunches sharing a first row; the wavefront for long
@@ -60,6 +64,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 #include <vector>
 
 #include "sss.h"
@@ -91,9 +96,6 @@ typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 #endif
 #ifndef SSS_NT_STORES
 #define SSS_NT_STORES 0
-#endif
-#ifndef SSS_WAVES_PER_EU
-#define SSS_WAVES_PER_EU 0
 #endif
 
 // streaming loads of the matrix arrays (plain loads stream faster than
@@ -218,6 +220,9 @@ __device__ __forceinline__ int wave_next(int v, int last) {
 __device__ __forceinline__ int wave_prev(int v, int first) {
   return __builtin_amdgcn_update_dpp(first, v, kWaveShr1, 0xf, 0xf, false);
 }
+// this wavefront's index in its workgroup, in a scalar register (what hangs
+// on it -- the bunch, its bounds and addresses -- then stays scalar too)
+__device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
 // v of lane `l`, for a lane index the same in every lane
 __device__ __forceinline__ int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 // a 64-bit value the same in every lane, in scalar registers
@@ -299,6 +304,14 @@ __device__ __forceinline__ int wave_iscan(int x) {
   return x;
 }
 
+// the last lane's value, in scalar registers
+__device__ __forceinline__ double last_lane(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, kWave - 1);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), kWave - 1);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // sum over the 64 lanes in a fixed tree (pairs 1 apart, 2 apart, ... 32
 // apart); every lane returns the total
 __device__ __forceinline__ double wave_sum_tree(double v) {
@@ -308,6 +321,18 @@ __device__ __forceinline__ double wave_sum_tree(double v) {
 }
 
 // ---------------------------------------------------------------- stage 1
+
+// What a bunch leaves for stage 2.  One record, stored by one instruction:
+// four arrays cost a bunch four partly written cache lines, which on a 160^3
+// 27-point stencil took 3 us of 266.
+struct BunchState {
+  double sync_val;
+  double tail_val;      // its last partial, when the bunch ends inside a row that is not its first row and
+                        // continues into the next bunch
+  int32_t sync_idx;
+  uint32_t dirty_mask;  // bit t: tile t is dirty
+};
+static_assert(sizeof(BunchState) == 24, "six words");
 
 // One matrix as the kernels see it: the caller's arrays, sizes, and the
 // plan's auxiliary arrays for this matrix (already offset to it).
@@ -323,12 +348,8 @@ struct MatCtx {
   int32_t W;
   int64_t n_bunches;
   int64_t n_tiles;
-  uint32_t *dirty_mask;  // per bunch: bit t set when its tile t is dirty
+  BunchState *state;     // per bunch
   int4 *speculator;      // per bunch, S slots: <start, stop, tile, 0> of its dirty tiles, packed
-  int32_t *sync_idx;
-  double *sync_val;
-  double *tail_val;      // per bunch: its last partial, when the bunch ends inside a row that is not
-                         // its first row and continues into the next bunch (written only then)
   const int32_t *bunch_row;  // per bunch: its first row, found at plan time (NULL: search); the top
                              // bit is set on the bunches listed in dirty_list
   const int32_t *dirty_list; // bound plans: the bunches whose tiles the plan found dirty (NULL: every
@@ -336,8 +357,10 @@ struct MatCtx {
   int64_t n_fix;             // stage-2 re-arrangement wavefronts: entries of dirty_list, else n_bunches
   int32_t *stale;            // bound plans: set (and never cleared) when stage 1 finds a dirty tile in a
                              // bunch outside dirty_list (row_ptr rewritten in place since plan time)
-  const int32_t *order;  // stage 1's wavefront slots: the bunch each takes, -1 = none (NULL: slot = bunch)
-  int64_t n_slots;       // entries of order
+  int32_t carries;       // fused kernel: a sss_carries launch follows and completes the long crossing rows
+  const int4 *slots;     // bound plans, per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
+                         // dirty_list), slot_need, 0>; NULL: slot = bunch
+  int64_t n_slots;
   int32_t *dbg_start;    // debug plans only
   int32_t *dbg_dirty;
   uint32_t *dbg_heads;
@@ -704,7 +727,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     const double plast = cnt == 1 ? p0 : part[cnt - 1];
     if (start == r0) sync_v = p0;
     transmitter = ends_mid ? plast : 0.0;
-    if (!has_next && ends_mid && !(cnt == 1 && start == r0) && lane == 0) a.tail_val[tb] = plast;
+    if (!has_next && ends_mid && !(cnt == 1 && start == r0) && lane == 0) a.state[tb].tail_val = plast;
     __builtin_amdgcn_wave_barrier();
 
     // ---- dirty tile: label it for the re-arrangement, in this bunch's own
@@ -715,9 +738,9 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     }
   }
   if (lane == 0) {
-    a.sync_idx[tb] = r0;
-    a.sync_val[tb] = sync_v;
-    a.dirty_mask[tb] = dirty_bits;
+    a.state[tb].sync_idx = r0;
+    a.state[tb].sync_val = sync_v;
+    a.state[tb].dirty_mask = dirty_bits;
     // a bound plan re-arranges only the bunches it listed; a dirty tile
     // anywhere else sends stage 2 to its fallback for every later call
     if (dirty_bits && !listed && a.stale) *a.stale = 1;
@@ -725,33 +748,527 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
 }
 
 
-// Occupancy asked of the register allocator per instance: none; every
-// instance already runs at its spill-free maximum (a higher target makes the
-// FP64 W = 4 instance spill).
-template <int DT, int W>
-constexpr int stage1_waves_per_eu() { return 1; }
-
 template <int DT, int W, bool DEBUG>
-__global__ __launch_bounds__(256)
-#if SSS_WAVES_PER_EU
-__attribute__((amdgpu_waves_per_eu(SSS_WAVES_PER_EU, 8)))
-#else
-__attribute__((amdgpu_waves_per_eu(stage1_waves_per_eu<DT, W>(), 8)))
-#endif
-void sss_stage1(MatCtx a) {
+__global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
   extern __shared__ uint32_t lds_words[];
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
   int64_t tb = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
-  if (a.order) {
+  if (a.slots) {
     if (tb >= a.n_slots) return;
-    tb = __builtin_amdgcn_readfirstlane(a.order[tb]);
+    tb = __builtin_amdgcn_readfirstlane(a.slots[tb].x);
     if (tb < 0) return;
   } else if (tb >= a.n_bunches) {
     return;
   }
   const int32_t brow = a.bunch_row ? a.bunch_row[tb] : -1;
   stage1_bunch<DT, W, DEBUG>(a, tb, lds_words + wid * stage1_lds_words(W, a.S), lane, brow);
+}
+
+// ---------------------------------------------------------------- fused kernel
+
+// Execute's kernel: stage 1 and, for its own bunch, the work of stage 2, so
+// that y needs no second launch.
+//  * A dirty tile stores its partials straight to its non-empty rows and
+//    zeroes the empty ones, from row_ptr and the partials in LDS, instead of
+//    storing them side by side for a re-arrangement to read back.
+//  * The bunch in which a row ends completes a row that began at most kBack
+//    nonzeros before the bunch: it loads and sums those itself (back_sum),
+//    and the bunch before drops its tail.  No bunch waits for another.  Rows
+//    that began further back (long crossing rows) are left to sss_carries,
+//    which adds the synchronizer entries in double as stage 2 does; where the
+//    plan saw no such row at plan time (MatCtx::carries = 0) that launch is
+//    left out, and a row_ptr rewritten in place since is served by the same
+//    loads, a wavefront's worth at a time.
+//  * The leading empty rows are shared out over the bunches.
+//
+// What bounds it is the latency of the loads a wavefront waits for one after
+// the other, so every load goes out as early as its address is known: the
+// first two tiles' columns and values, the row pointers and the entries
+// before the bunch at once, tile 0's gathers behind them; in the tile loop
+// the gathers of tile t + 1 (whose columns came in while tile t - 1 was
+// summed) and the columns and values of tile t + 2 go out before tile t is
+// summed.  The loads are buffer loads whose range ends with the bunch: past
+// it they return 0 without touching memory, so nothing in the loop branches
+// on what is left (a branch around a load makes the compiler wait for every
+// load in flight where the paths meet), and one 32-bit offset replaces a
+// 64-bit address per load.
+//
+// Per product, the two launches before / this kernel (and sss_carries where
+// needed): 160^3 27-point stencil FP64 276 / 262 us (1.39 GB: 5.0 / 5.3
+// TB/s), 1414^2 5-point stencil FP64 39.9 / 32.1 us (160 MB: 4.0 / 5.0 TB/s),
+// FEM band 778K x 50 FP32 74.2 / 64.2 us (320 MB: 4.3 / 5.0 TB/s), 1M-row
+// power law FP64 182.9 / 171.9 us and BF16 117.8 / 110.8 us (both in column
+// order), 30K-row web-like FP32 12.3 / 10.6 us (the host's share is most of
+// that).
+constexpr int kBack = kWave;
+
+// Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
+// a long crossing row (left to sss_carries)?
+__device__ __forceinline__ bool long_crossing(int64_t rs, int64_t re, int64_t b0, int64_t SWT) {
+  return re > b0 + SWT ? true : rs < b0 - kBack;
+}
+// the entries of that row before the bunch that the bunch sums itself
+__device__ __forceinline__ int back_entries(int64_t rs, int64_t re, int64_t b0, int64_t SWT) {
+  return long_crossing(rs, re, b0, SWT) ? 0 : (int)(b0 - rs);
+}
+
+// How the loads go out.
+//  kCached: plain loads.
+//  kStreamed: the columns and values as non-temporal loads, which leave L2 to
+//    x.  Faster where the matrix comes from memory anyway, slower where much
+//    of it was still cached (see form_of).
+//  kWide: streamed, and x is 4 GB or more, past a buffer load's 32-bit offset.
+enum Form { kCached, kStreamed, kWide };
+
+// What a plan tells a bunch of its first row, rp[r0] <= b0 < rp[r0 + 1]: its
+// back_entries (7 bits), and above them how many entries of row_ptr after
+// rp[r0] the bunch needs, up to the first that is past its end (kSpanMax:
+// more than the two that each lane loads ahead).
+constexpr int kSpanMax = 2 * kWave;
+__device__ __forceinline__ int slot_need(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb, int32_t r,
+                                         int32_t r_next) {
+  const int back = r < m ? back_entries(rp[r], rp[r + 1], tb * SWT, SWT) : 0;
+  // r_next: the next bunch's first row, m after the last bunch
+  const int64_t span = imin64((int64_t)(r_next < m ? r_next + 1 : m) - r, kSpanMax);
+  return back | (int)span << 8;
+}
+
+// Buffer loads: the descriptor's range is in bytes, checked per 32-bit word.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format
+__device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRsrcWord3);
+}
+template <typename T, bool NT = false>
+__device__ __forceinline__ T buffer_load(rsrc_t r, int voffset, int soffset) {
+  constexpr int kAux = NT ? 2 : 0;
+  static_assert(sizeof(T) == 2 || sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one load");
+  T v;
+  if constexpr (sizeof(T) == 2) {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b16(r, voffset, soffset, kAux);
+    __builtin_memcpy(&v, &w, 2);
+  } else if constexpr (sizeof(T) == 4) {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b32(r, voffset, soffset, kAux);
+    __builtin_memcpy(&v, &w, 4);
+  } else if constexpr (sizeof(T) == 8) {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, voffset, soffset, kAux);
+    __builtin_memcpy(&v, &w, 8);
+  } else {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b128(r, voffset, soffset, kAux);
+    __builtin_memcpy(&v, &w, 16);
+  }
+  return v;
+}
+
+// One tile's columns and stored values in the grouped order, as loaded: one
+// 16-byte load of values per row (8 bytes where G is 4 BF16 values).
+template <int DT, int W>
+struct Tile {
+  static constexpr int G = group_w<DT, W>(), R = W / G;
+  static constexpr int VB = (int)sizeof(typename VT<DT>::val_t);
+  static constexpr int CI = G >= 4 ? G / 4 : 1;  // column loads per row
+  using col_t = std::conditional_t<G == 2, v2u, v4u>;
+  using raw_t = std::conditional_t<G * VB == 16, v4u, v2u>;
+  col_t c[R * CI];
+  raw_t v[R];
+
+  template <bool NT>
+  __device__ __forceinline__ void load(rsrc_t rc, rsrc_t rv, int t, int lane) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int i = 0; i < CI; ++i)
+        c[r * CI + i] = buffer_load<col_t, NT>(rc, lane * G * 4 + r * kWave * G * 4 + i * 16, t * W * kWave * 4);
+      v[r] = buffer_load<raw_t, NT>(rv, lane * G * VB + r * kWave * G * VB, t * W * kWave * VB);
+    }
+  }
+  __device__ __forceinline__ uint32_t column(int i) const {
+    if constexpr (G == 2) return c[i / 2][i % 2];
+    else return c[i / 4][i % 4];
+  }
+  __device__ __forceinline__ typename VT<DT>::prod_t value(int i) const {
+    const int r = i / G, g = i % G;
+    if constexpr (DT == SSS_F64) {
+      const uint64_t b = (uint64_t)v[r][2 * g] | ((uint64_t)v[r][2 * g + 1] << 32);
+      return __longlong_as_double((long long)b);
+    } else if constexpr (DT == SSS_F32) {
+      return __uint_as_float(v[r][g]);
+    } else {
+      const uint32_t w = v[r][g / 2];
+      return __uint_as_float(g % 2 ? w & 0xffff0000u : w << 16);
+    }
+  }
+  // the values of entries at or past `left` (in the tile) become 0
+  __device__ __forceinline__ static int offset(int i, int lane) { return (i / G) * kWave * G + lane * G + i % G; }
+};
+
+// The sum of row entries rs .. b0-1, the part of a row before the bunch that
+// begins at b0; lane l holds the product of entry b0 - kBack + l.  Up to
+// kBack of them are summed as the bunch before sums its tail (its last lanes,
+// W entries each, then the wave scan), so y is the same bit for bit wherever
+// the row's parts are added.
+template <int DT, int W, typename prod_t>
+__device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, double *lds, int lane) {
+  prod_t *buf = reinterpret_cast<prod_t *>(lds);
+  buf[lane] = product;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  constexpr int kFirst = kWave - kBack / W;  // the first lane whose entries are among the last kBack
+  Acc<DT> acc;
+  acc.zero();
+  if (lane >= kFirst) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) acc.add(buf[(lane - kFirst) * W + i]);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int head = kFirst + (rs - (b0 - kBack)) / W;
+  Acc<DT> inc = acc;
+  int f = lane == head ? 1 : 0;
+  wave_seg_scan(inc, f);
+  const Acc<DT> carry = dpp_acc<kWaveShr1, 0xf>(inc);
+  Acc<DT> c = acc;
+  if (head != kWave - 1) c.prepend(carry);
+  return last_lane(c.value());
+}
+
+// What the tiles of a bunch share.
+template <int DT, int W>
+struct Bunch {
+  using y_t = typename VT<DT>::y_t;
+  using prod_t = typename VT<DT>::prod_t;
+  const int32_t *__restrict__ rp;
+  y_t *__restrict__ y;
+  int4 *speculator;      // this bunch's slots, or NULL
+  uint32_t *mask;        // LDS: descriptor bits
+  double *part;          // LDS: products, then partials, of one tile
+  int m, lane, r0, first_tile;
+  uint32_t dirty_bits;
+  int my_start, my_rp;   // lane t: tile t's start row and its row_ptr
+  uint64_t filled_rows;  // lane c: which of the rows r0 + 64 c + 0 .. 63 hold entries
+  double transmitter, sync_v;
+
+  // The segmented sum of tile t, entries b .. e-1 of the matrix, whose
+  // products lie in `part` in the layout of products_out; as in stage1_bunch.
+  // `pr` holds them already where that layout is the lane order.
+  __device__ __forceinline__ double sum_tile(int t, int e, prod_t (&pr)[W]) {
+    constexpr int WT = W * kWave;
+    constexpr int WPT = WT / 32;
+    constexpr uint32_t LOW = (W >= 32) ? 0xffffffffu : ((1u << W) - 1u);
+    const int start = lane_value(my_start, t);
+    const int stop = lane_value(my_start, t + 1);
+    const bool ends_mid = (stop < m) && (lane_value(my_rp, t + 1) < e);
+    const bool dirty = (dirty_bits >> t) & 1u;
+
+    uint32_t hb = (mask[t * WPT + ((lane * W) >> 5)] >> ((lane * W) & 31)) & LOW;
+    const bool bit0 = __builtin_amdgcn_readlane((int)hb, 0) & 1;
+    if (lane == 0) hb |= 1u;
+    const double tx = bit0 ? 0.0 : transmitter;
+
+    const int c_heads = __popc(hb);
+    const int incl = wave_iscan(c_heads);
+    const int cnt = __builtin_amdgcn_readlane(incl, kWave - 1);
+    const int rank0 = incl - c_heads;
+
+    products_in<DT, W>(reinterpret_cast<const prod_t *>(part), lane, pr);
+    Acc<DT> acc, pre;
+    acc.zero();
+    pre.zero();
+    bool seen = false;
+    int q = rank0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      if ((hb >> i) & 1u) {
+        part[q > 0 ? q - 1 : 0] = acc.value();
+        if (!seen) pre = acc;
+        seen = true;
+        ++q;
+        acc.zero();
+      }
+      acc.add(pr[i]);
+    }
+    if (!seen) pre = acc;
+    Acc<DT> inc = acc;
+    int f = seen ? 1 : 0;
+    wave_seg_scan(inc, f);
+    const Acc<DT> carry = dpp_acc<kWaveShr1, 0xf>(inc);
+    if (seen && rank0 > 0) {
+      Acc<DT> c = pre;
+      c.prepend(carry);
+      part[rank0 - 1] = c.value();
+    }
+    if (lane == kWave - 1) {
+      Acc<DT> c = pre;
+      c.prepend(carry);
+      part[cnt - 1] = seen ? acc.value() : c.value();
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    if (dirty) {
+      // rows start + 1 .. stop - 1: the k-th non-empty one takes partial k
+      // (k >= 1), the empty ones 0.  Which are empty the row pass has kept for
+      // its first 64 chunks (row_ptr read again here would make the tile wait
+      // for every load in flight).
+      if (lane == 0 && start != r0 && !(cnt == 1 && ends_mid)) y_store((y_t)(part[0] + tx), &y[start]);
+      int k = 0;
+      for (int c = (start + 1 - r0) / kWave; r0 + c * kWave < stop; ++c) {
+        const int r = r0 + c * kWave + lane;
+        const bool in = r > start && r < stop;
+        uint64_t filled;
+        if (c < kWave) {
+          filled = ((uint64_t)(uint32_t)lane_value((int)(filled_rows >> 32), c) << 32) |
+                   (uint32_t)lane_value((int)(uint32_t)filled_rows, c);
+          filled &= __ballot(in);
+        } else {
+          filled = __ballot(in && rp[r] != rp[r + 1]);
+        }
+        const int rank = k + 1 + __popcll(filled & ((1ull << lane) - 1ull));
+        if (in) y_store((filled >> lane) & 1ull ? (y_t)part[min(rank, WT - 1)] : (y_t)0, &y[r]);
+        k += __popcll(filled);
+      }
+      if (lane == 0 && speculator)
+        speculator[__popc(dirty_bits & ((1u << t) - 1u))] = make_int4(start, stop, first_tile + t, 0);
+    } else {
+      for (int q = lane; q < cnt; q += kWave) {
+        const bool last = (q == cnt - 1);
+        const int idx = start + q;
+        if (!(q == 0 && start == r0) && !(last && ends_mid) && (unsigned)idx < (unsigned)m) {
+          double v = part[q];
+          if (q == 0) v += tx;
+          y_store((y_t)v, &y[idx]);
+        }
+      }
+    }
+    const double p0 = part[0] + tx;
+    const double plast = cnt == 1 ? p0 : part[cnt - 1];
+    if (start == r0) sync_v = p0;
+    transmitter = ends_mid ? plast : 0.0;
+    __builtin_amdgcn_wave_barrier();
+    // the tail, where this is the bunch's last tile: what its last row holds
+    // of it, unless that row is the bunch's first (then the synchronizer's)
+    return ends_mid && !(cnt == 1 && start == r0) ? plast : 0.0;
+  }
+};
+
+// tb, the bunch; brow, its first row at plan time or -1; need, its slot_need
+// (0 without a plan): the same in every lane.
+template <int DT, int W, Form FORM>
+__device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const int brow, const int need,
+                                            uint32_t *lds_wave, const int lane) {
+  using val_t = typename VT<DT>::val_t;
+  using x_t = typename VT<DT>::x_t;
+  using y_t = typename VT<DT>::y_t;
+  using prod_t = typename VT<DT>::prod_t;
+  constexpr int WT = W * kWave;
+  constexpr int WPT = WT / 32;
+  const int S = a.S, m = a.m;
+  const int SWT = S * WT;
+  const int b0 = tb * SWT;  // < nnz
+  const int left = min(a.nnz - b0, SWT);
+  const int bS = b0 + left;
+  const int tiles = (left + WT - 1) / WT;
+  const bool known = brow != -1;
+  const int back_n = need & 0xff;
+  uint32_t *mask = lds_wave;
+  uint32_t *dflag = mask + S * WPT;
+
+  // ---- the loads that need nothing
+  const rsrc_t rc = make_rsrc(a.col + b0, (uint32_t)left * 4u);
+  // (whole words: an odd number of BF16 values ends inside one)
+  const rsrc_t rv = make_rsrc(static_cast<const val_t *>(a.val) + b0, ((uint32_t)left * sizeof(val_t) + 3u) & ~3u);
+  const rsrc_t rx = make_rsrc(a.x, 0xffffffffu);
+  auto gather = [&](uint32_t c) {
+    if constexpr (FORM == kWide) return static_cast<const x_t *>(a.x)[c];
+    else return buffer_load<x_t>(rx, (int)(c * (uint32_t)sizeof(x_t)), 0);
+  };
+  constexpr bool NT = FORM != kCached;
+  Tile<DT, W> cur, next;
+  cur.template load<NT>(rc, rv, 0, lane);
+  const int back_off = lane - (kBack - back_n);  // lanes below 0: outside
+  const uint32_t back_c =
+      buffer_load<uint32_t>(make_rsrc(a.col + (b0 - back_n), (uint32_t)back_n * 4u), back_off * 4, 0);
+  const val_t back_v = buffer_load<val_t>(
+      make_rsrc(static_cast<const val_t *>(a.val) + (b0 - back_n), (uint32_t)back_n * sizeof(val_t)),
+      back_off * (int)sizeof(val_t), 0);
+  int r0 = known ? brow & 0x7fffffff : 0;
+  const int span = need >> 8;
+  const bool ahead = known && span < kSpanMax;
+  const rsrc_t rr = make_rsrc(a.row_ptr + r0, ahead ? (uint32_t)(span + 1) * 4u : 0u);
+  const int rows0 = buffer_load<int>(rr, lane * 4, 0);
+  const int rows1 = buffer_load<int>(rr, lane * 4 + kWave * 4, 0);
+  const int second_row = a.row_ptr[1];
+  if (S > 1) next.template load<NT>(rc, rv, 1, lane);
+
+  // ---- the gathers of tile 0
+  x_t xv[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) xv[i] = gather(cur.column(i));
+  const x_t back_x = gather(back_c);  // (column 0 in the lanes that hold none)
+
+  // ---- descriptor, tile start rows, dirty tiles: one pass over the rows
+  for (int i = lane; i < S * WPT; i += kWave) mask[i] = 0u;
+  if (lane == 0) *dflag = 0u;
+  __builtin_amdgcn_wave_barrier();
+
+  const int32_t *__restrict__ rp = a.row_ptr;
+  const int my_b = b0 + min(min(lane, S) * WT, left);
+  int my_count = 0, my_rp = 0;  // lane t <= S: as in stage1_bunch
+  int first_rs = 0, first_re = 0;
+  uint64_t filled_rows = 0;
+  // the plan's rows hold where rp[r0] <= b0 < rp[r0 + 1] and the entry after
+  // the span is past bS (or the last): row_ptr ascends, so every row between
+  // is the bunch's.  Else (no plan, a long span, or row_ptr rewritten in place
+  // since) the pass loads its rows itself, from the row that it searches for.
+  bool loaded = false;
+  if (ahead) {
+    const int p0 = lane_value(rows0, 0), q0 = lane_value(rows0, 1);
+    const int end = span < kWave ? lane_value(rows0, span) : lane_value(rows1, span - kWave);
+    loaded = p0 <= b0 && b0 < q0 && (r0 + span >= m || end > bS);
+  }
+  if (!loaded) {
+    bool found = false;
+    if (known) found = rp[r0] <= b0 && b0 < rp[r0 + 1];
+    if (!found) r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(rp, m, b0, lane));
+  }
+  // one chunk of 64 rows: p = rp[r], after = the entry past the chunk (a value
+  // past bS beyond the last entry, or beyond the span); true when more follow
+  auto row_chunk = [&](int rbase, int p, int after) {
+    const int r = rbase + lane;
+    const int q = wave_next(p, after);  // rp[r + 1]
+    if (rbase == r0) {
+      first_rs = lane_value(p, 0);
+      first_re = lane_value(q, 0);
+    }
+    if (r < m && q > p && p >= b0 && p < bS) {
+      const int off = p - b0;
+      atomicOr(&mask[off >> 5], 1u << (off & 31));
+    }
+    if (r < m && q == p && p > b0 && p <= bS) atomicOr(dflag, 1u << ((p - b0 - 1) / WT));
+    const uint64_t filled = __ballot(q != p);
+    if (lane == (rbase - r0) / kWave) filled_rows = filled;
+    for (int t = 0; t <= S; ++t) {
+      const int c = __popcll(__ballot(p <= lane_value(my_b, t)));
+      const int p_last_in = lane_value(p, c > 0 ? c - 1 : 0);
+      if (lane == t) {
+        my_count += c;
+        if (c > 0) my_rp = p_last_in;
+      }
+    }
+    return lane_value(p, kWave - 1) <= bS && rbase + (kWave - 1) < m;
+  };
+  if (loaded) {  // (apart from the loop below, whose loads would make this wait for tile 0's gathers)
+    for (int chunk = 0; chunk < 2; ++chunk) {
+      const int p = chunk * kWave + lane <= span ? (chunk == 0 ? rows0 : rows1) : INT_MAX;
+      const int after = chunk == 0 && span >= kWave ? lane_value(rows1, 0) : INT_MAX;
+      if (!row_chunk(r0 + chunk * kWave, p, after)) break;
+    }
+  } else {
+    for (int rbase = r0;; rbase += kWave) {
+      const int p = rbase + lane <= m ? rp[rbase + lane] : INT_MAX;
+      if (!row_chunk(rbase, p, rbase + kWave <= m ? rp[rbase + kWave] : INT_MAX)) break;
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+
+  Bunch<DT, W> u;
+  u.rp = rp;
+  u.y = static_cast<y_t *>(a.y);
+  u.speculator = a.speculator ? a.speculator + (int64_t)tb * S : nullptr;
+  u.mask = mask;
+  u.part = reinterpret_cast<double *>(mask + S * WPT + 2);
+  u.m = m;
+  u.lane = lane;
+  u.r0 = r0;
+  u.first_tile = tb * S;
+  u.dirty_bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)*dflag);
+  u.my_start = lane <= S ? r0 + my_count - 1 : 0;
+  u.my_rp = my_rp;
+  u.filled_rows = filled_rows;
+  u.transmitter = 0.0;
+  u.sync_v = 0.0;
+
+  // ---- does this bunch write y[r0]: it does when the row ends here and is
+  // no long crossing row; the row's entries before the bunch are summed here
+  const bool own_first = r0 < m && (int64_t)first_re <= (int64_t)b0 + SWT && (!a.carries || first_rs >= b0 - kBack);
+  double before = 0.0;
+  if (own_first && first_rs < b0) {
+    const val_t *__restrict__ val = static_cast<const val_t *>(a.val);
+    const x_t *__restrict__ x = static_cast<const x_t *>(a.x);
+    if (first_rs < b0 - kBack) {  // a row further back than the plan knew of
+      double v = 0.0;
+      for (int k = first_rs + lane; k < b0; k += kWave) v += (double)scalar_val(val, k) * (double)x[a.col[k]];
+      before = last_lane(wave_sum_tree(v));
+    } else {
+      prod_t product = back_off >= 0 ? (prod_t)scalar_val(&back_v, 0) * (prod_t)back_x : (prod_t)0;
+      if (b0 - first_rs != back_n) {  // not found at plan time, or row_ptr rewritten since
+        const int k = b0 - kBack + lane;
+        product = k >= first_rs ? (prod_t)scalar_val(val, k) * (prod_t)x[a.col[k]] : (prod_t)0;
+      }
+      before = back_sum<DT, W>(product, first_rs, b0, u.part, lane);
+    }
+  }
+
+  // ---- the tiles
+  prod_t pr[W];
+  auto products = [&](int t) {
+    prod_t av[W], bv[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      av[i] = cur.value(i);
+      bv[i] = (prod_t)xv[i];
+    }
+    if (left - t * WT < WT) {  // the matrix's last tile: entries past its end add 0
+#pragma unroll
+      for (int i = 0; i < W; ++i)
+        if (Tile<DT, W>::offset(i, lane) >= left - t * WT) av[i] = bv[i] = (prod_t)0;
+    }
+    products_out<DT, W>(av, bv, reinterpret_cast<prod_t *>(u.part), lane, pr);
+  };
+  double tail = 0.0;
+  for (int t = 0; t + 1 < tiles; ++t) {
+    products(t);
+    cur = next;
+#pragma unroll
+    for (int i = 0; i < W; ++i) xv[i] = gather(cur.column(i));
+    if (t + 2 < tiles) next.template load<NT>(rc, rv, t + 2, lane);
+    (void)u.sum_tile(t, b0 + (t + 1) * WT, pr);
+  }
+  products(tiles - 1);
+  tail = u.sum_tile(tiles - 1, bS, pr);
+
+  if (own_first && lane == 0) y_store((y_t)(before + u.sync_v), &u.y[r0]);
+  // rows before the first non-empty one: those of this bunch's share of y
+  if (second_row == 0) {
+    const int64_t hi = (int64_t)m * (tb + 1) / a.n_bunches;
+    for (int64_t r = (int64_t)m * tb / a.n_bunches + lane; r < hi && rp[r + 1] == 0; r += kWave) u.y[r] = (y_t)0;
+  }
+  if (a.state) {  // (a batch that needs no carries keeps none)
+    const uint64_t sv = (uint64_t)__double_as_longlong(u.sync_v), tv = (uint64_t)__double_as_longlong(tail);
+    const uint32_t words[6] = {(uint32_t)sv, (uint32_t)(sv >> 32), (uint32_t)tv, (uint32_t)(tv >> 32), (uint32_t)r0,
+                               u.dirty_bits};
+    uint32_t w = words[0];
+#pragma unroll
+    for (int i = 1; i < 6; ++i) w = lane == i ? words[i] : w;
+    if (lane < 6) reinterpret_cast<uint32_t *>(a.state + tb)[lane] = w;
+  }
+}
+
+template <int DT, int W, Form FORM>
+__global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
+  extern __shared__ uint32_t lds_words[];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = wave_in_block();
+  const int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
+  int4 slot = make_int4((int)g, -1, 0, 0);
+  if (a.slots) {
+    if (g >= a.n_slots) return;
+    slot = uniform_load(a.slots + g);
+    if (slot.x < 0) return;
+  } else if (g >= a.n_bunches) {
+    return;
+  }
+  fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, lds_words + wid * stage1_lds_words(W, a.S), lane);
 }
 
 // gfx950 (one partition) hands consecutive workgroups to its 8 XCDs in turn,
@@ -770,23 +1287,26 @@ __device__ __forceinline__ int32_t rightmost_row(const int32_t *__restrict__ rp,
   return lo;
 }
 
+// *any_long is set when some bunch's first row is a long crossing row.
 __global__ void sss_bunch_rows(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t n_bunches,
-                               int32_t *__restrict__ out) {
+                               int32_t *__restrict__ out, int32_t *__restrict__ any_long) {
   for (int64_t tb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; tb < n_bunches;
-       tb += (int64_t)gridDim.x * blockDim.x)
-    out[tb] = rightmost_row(rp, m, tb * SWT);
+       tb += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t r = rightmost_row(rp, m, tb * SWT);
+    out[tb] = r;
+    if (r < m && long_crossing(rp[r], rp[r + 1], tb * SWT, SWT)) *any_long = 1;
+  }
 }
 
 // Plan time: mark every bunch with a dirty tile by OR-ing `bit` into
-// words[bunch * stride].  A tile is dirty exactly when an empty row r with
+// words[bunch].  A tile is dirty exactly when an empty row r with
 // row_ptr[r] = p > 0 lies in it (tile (p - 1) / WT, Section 3.2's dirty
-// condition), so its bunch is (p - 1) / SWT.  Single plans mark the top bit
-// of bunch_row, batch plans the last word of each bunch's bunch_info entry.
+// condition), so its bunch is (p - 1) / SWT.
 __global__ void sss_mark_dirty_bunches(const int32_t *__restrict__ rp, int32_t m, int64_t SWT,
-                                       uint32_t *__restrict__ words, int stride, uint32_t bit) {
+                                       uint32_t *__restrict__ words, uint32_t bit) {
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x) {
     const int32_t p = rp[r];
-    if (p > 0 && p == rp[r + 1]) atomicOr(words + (p - 1) / SWT * stride, bit);
+    if (p > 0 && p == rp[r + 1]) atomicOr(words + (p - 1) / SWT, bit);
   }
 }
 
@@ -841,11 +1361,29 @@ __global__ __launch_bounds__(256) void sss_order_keys(const int32_t *__restrict_
 // on XCD b mod kXcds.
 __device__ __forceinline__ int64_t xcd_slot(int64_t k, int64_t t, int B) { return (k + kXcds * (t / B)) * B + t % B; }
 
-// hist: the bunches per bin; cursor: zeros.  Within a bin the order is that
+// A slot's entry for bunch tb (bunch_row: first rows, with the top bit).
+__device__ __forceinline__ int4 slot_entry(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb,
+                                           int64_t n_bunches, const int32_t *__restrict__ bunch_row) {
+  const int32_t row = bunch_row[tb];
+  const int32_t next = tb + 1 < n_bunches ? bunch_row[tb + 1] & 0x7fffffff : m;
+  return make_int4((int)tb, row, slot_need(rp, m, SWT, tb, row & 0x7fffffff, next), 0);
+}
+
+// Slots in bunch order.
+__global__ __launch_bounds__(256) void sss_slots(const int32_t *__restrict__ rp, int32_t m, int64_t SWT,
+                                                 int64_t n_bunches, const int32_t *__restrict__ bunch_row,
+                                                 int4 *__restrict__ slots) {
+  const int64_t tb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (tb < n_bunches) slots[tb] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row);
+}
+
+// Slots in column order.  hist: the bunches per bin; cursor: zeros.  Within a bin the order is that
 // of the atomics, which decides only when a bunch runs.
-__global__ __launch_bounds__(256) void sss_order_scatter(const uint32_t *__restrict__ keys, int64_t n_bunches,
-                                                         int64_t n_slots, int B, const uint32_t *__restrict__ hist,
-                                                         uint32_t *__restrict__ cursor, int32_t *__restrict__ order) {
+__global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restrict__ rp, int32_t m, int64_t SWT,
+                                                         int64_t n_bunches, const int32_t *__restrict__ bunch_row,
+                                                         const uint32_t *__restrict__ keys, int64_t n_slots, int B,
+                                                         const uint32_t *__restrict__ hist,
+                                                         uint32_t *__restrict__ cursor, int4 *__restrict__ slots) {
   __shared__ uint32_t first[kOrderBins], count[kOrderBins + 1], base[kOrderBins + 1];
   const int t = threadIdx.x;
   static_assert(kOrderBins == 256, "one bin per thread");
@@ -882,16 +1420,18 @@ __global__ __launch_bounds__(256) void sss_order_scatter(const uint32_t *__restr
       i += n_long;
       slot = xcd_slot(i % kXcds, i / kXcds, B);
     }
-    order[slot] = (int32_t)tb;
+    slots[slot] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row);
   } else if (tb < n_slots) {
-    order[xcd_slot(tb % kXcds, tb / kXcds, B)] = -1;
+    slots[xcd_slot(tb % kXcds, tb / kXcds, B)] = make_int4(-1, 0, 0, 0);
   }
 }
 
 // Plan time, batches: for global bunch g its matrix (the rightmost i with
-// bunch_base[i] <= g), its first row and its index within the matrix.
+// bunch_base[i] <= g), its first row and its index within the matrix;
+// *any_long as in sss_bunch_rows.
 __global__ void sss_batch_bunch_info(const MatCtx *__restrict__ mats, const int64_t *__restrict__ bunch_base,
-                                     int32_t count, int64_t total, int4 *__restrict__ out) {
+                                     int32_t count, int64_t total, int4 *__restrict__ out,
+                                     int32_t *__restrict__ any_long) {
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
     int32_t lo = 0, hi = count;
     while (lo < hi) {
@@ -900,8 +1440,11 @@ __global__ void sss_batch_bunch_info(const MatCtx *__restrict__ mats, const int6
       else hi = mid - 1;
     }
     const MatCtx &a = mats[lo];
-    const int64_t tb = g - bunch_base[lo];
-    out[g] = make_int4(lo, rightmost_row(a.row_ptr, a.m, tb * (int64_t)a.S * a.W * kWave), (int)tb, 0);
+    const int64_t tb = g - bunch_base[lo], SWT = (int64_t)a.S * a.W * kWave;
+    const int32_t r = rightmost_row(a.row_ptr, a.m, tb * SWT);
+    if (r < a.m && long_crossing(a.row_ptr[r], a.row_ptr[r + 1], tb * SWT, SWT)) *any_long = 1;
+    const int32_t next = tb + 1 < a.n_bunches ? rightmost_row(a.row_ptr, a.m, (tb + 1) * SWT) : a.m;
+    out[g] = make_int4(lo, r, (int)tb, slot_need(a.row_ptr, a.m, SWT, tb, r, next));
   }
 }
 
@@ -966,11 +1509,10 @@ struct BatchArgs {
   int32_t S_max;
   int64_t total_bunches;
   int64_t total_chunks;
-  int64_t total_waves;        // stage-2 work items: total_chunks + n_fix + count
-  int64_t n_fix;              // stage-2 re-arrangement items: the listed bunches
-  const int32_t *dirty_list;  // the global bunches found at plan time to hold a dirty tile
-  int32_t *stale;             // set when stage 1 finds a dirty tile in an unlisted bunch
-  const int4 *bunch_info;     // per global bunch: <matrix, first row, bunch within the matrix, listed>
+  int64_t total_waves;        // second-launch work items: the carry chunks (0 without long crossing
+                              // rows), then one per matrix where some matrix has no nonzero
+  int32_t carries;            // MatCtx::carries of every matrix of the batch
+  const int4 *bunch_info;     // per global bunch: <matrix, first row, bunch within the matrix, slot_need>
   // stage 1's XCD windows: the workgroups b with b mod n_windows = k take the
   // global bunches window[k] .. window[k+1]-1, in order.  n_windows is kXcds
   // (one contiguous window per XCD, holding an equal share of the nonzeros)
@@ -980,18 +1522,13 @@ struct BatchArgs {
 };
 
 // A global bunch's plan entry and its matrix's context, read once per
-// wavefront: through the scalar unit into scalar registers, except for W = 16,
-// whose register budget the scalar copy of the context pushes past the next
-// occupancy step (g < 2^31: the grid is limited to that many wavefronts).
-template <int W>
+// wavefront through the scalar unit into scalar registers (g < 2^31: the grid
+// is limited to that many wavefronts).
 __device__ __forceinline__ void batch_entry(const BatchArgs &b, int64_t g, int4 &bi, MatCtx &a) {
-  if constexpr (W == 16) {
-    bi = b.bunch_info[g];
-    a = b.mats[bi.x];
-  } else {
-    bi = uniform_load(b.bunch_info + uniform_i64(g));
-    a = uniform_load(b.mats + bi.x);
-  }
+  bi = uniform_load(b.bunch_info + g);
+  a = uniform_load(b.mats + bi.x);
+  a.carries = b.carries;
+  if (!b.carries) a.state = nullptr;
 }
 
 
@@ -1004,11 +1541,11 @@ __device__ __forceinline__ int64_t window_bunch(const BatchArgs &b, int wid) {
   return g < b.window[k + 1] ? g : -1;
 }
 
-template <int DT, int W>
-__global__ __launch_bounds__(256) void sss_stage1_batch(BatchArgs b) {
+template <int DT, int W, Form FORM>
+__global__ __launch_bounds__(256) void sss_fused_batch(BatchArgs b) {
   extern __shared__ uint32_t lds_words[];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wid = threadIdx.x / kWave;
+  const int wid = wave_in_block();
   uint32_t *lds_wave = lds_words + wid * stage1_lds_words(W, b.S_max);
   // One wavefront per thread-bunch, XCD-aware: workgroup blockIdx.x, which
   // runs on XCD blockIdx.x mod kXcds, takes the (blockIdx.x / kXcds)-th
@@ -1023,19 +1560,19 @@ __global__ __launch_bounds__(256) void sss_stage1_batch(BatchArgs b) {
   if (g < 0) return;
   int4 bi;
   MatCtx a;
-  batch_entry<W>(b, g, bi, a);
-  stage1_bunch<DT, W, false>(a, bi.z, lds_wave, lane, bi.w ? (int32_t)((uint32_t)bi.y | 0x80000000u) : bi.y);
+  batch_entry(b, g, bi, a);
+  fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, lds_wave, lane);
 }
 
 // The same work as a persistent grid (batch_persistent plans): as many
 // workgroups as stay resident, a multiple of kXcds; the workgroups with
 // blockIdx.x mod kXcds = k stride over window k, one bunch per wavefront per
 // step.
-template <int DT, int W>
-__global__ __launch_bounds__(256) void sss_stage1_batch_persistent(BatchArgs b) {
+template <int DT, int W, Form FORM>
+__global__ __launch_bounds__(256) void sss_fused_batch_persistent(BatchArgs b) {
   extern __shared__ uint32_t lds_words[];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wid = threadIdx.x / kWave;
+  const int wid = wave_in_block();
   uint32_t *lds_wave = lds_words + wid * stage1_lds_words(W, b.S_max);
   const int G = b.n_windows;
   const int k = (int)(blockIdx.x % G);
@@ -1045,8 +1582,8 @@ __global__ __launch_bounds__(256) void sss_stage1_batch_persistent(BatchArgs b) 
   for (int64_t g = b.window[k] + (int64_t)(blockIdx.x / G) * wpb + wid; g < hi; g += stride) {
     int4 bi;
     MatCtx a;
-    batch_entry<W>(b, g, bi, a);
-    stage1_bunch<DT, W, false>(a, bi.z, lds_wave, lane, bi.w ? (int32_t)((uint32_t)bi.y | 0x80000000u) : bi.y);
+    batch_entry(b, g, bi, a);
+    fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, lds_wave, lane);
   }
 }
 
@@ -1057,16 +1594,21 @@ __global__ __launch_bounds__(256) void sss_stage1_batch_persistent(BatchArgs b) 
 template <int DT, int W, bool GATHER>
 __global__ __launch_bounds__(256) void sss_floor_batch(BatchArgs b, typename VT<DT>::y_t *__restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wid = threadIdx.x / kWave;
+  const int wid = wave_in_block();
   const int64_t g = window_bunch(b, wid);
   if (g < 0) return;
   int4 bi;
   MatCtx a;
-  batch_entry<W>(b, g, bi, a);
+  batch_entry(b, g, bi, a);
   out[g * kWave + lane] = (typename VT<DT>::y_t)floor_bunch<DT, W, GATHER>(a, bi.z, lane);
 }
 
 // ---------------------------------------------------------------- stage 2
+
+// the carry kernels' workgroup, and a wavefront's staging in doubles: the
+// values and (half as wide) the row indices of its chunk and kShortRun more
+constexpr int kCarryThreads = 128;
+constexpr int kCarryLds = (kWave + kShortRun) * 3 / 2;
 
 // (1) re-arrange the dirty tiles of thread-bunch tb: a dirty tile's partials
 // 1.. sit at y[start+1..]; the k-th non-empty row strictly between start and
@@ -1077,7 +1619,7 @@ __device__ __forceinline__ void fixup_dirty(const MatCtx &a, const int64_t tb, Y
   const int32_t *__restrict__ rp = a.row_ptr;
   YT *y = static_cast<YT *>(a.y);
   const int WT = a.W * kWave;
-  const uint32_t dm = a.dirty_mask[tb];
+  const uint32_t dm = a.state[tb].dirty_mask;
   const int n_dirty = __popc(dm);
   if (n_dirty == 0) return;
   // all of the bunch's speculator entries in one load: lane e holds entry e
@@ -1135,7 +1677,8 @@ __device__ __forceinline__ void fixup_dirty(const MatCtx &a, const int64_t tb, Y
 // the kernel's occupancy); longer runs (rows longer than kShortRun bunches)
 // by the whole wavefront: coalesced loads, per-lane partial sums, then a
 // fixed-shape tree over the lanes, so the rounding does not depend on timing.
-template <typename YT>
+// LONG_ONLY: only the long crossing rows, the others are complete.
+template <typename YT, bool LONG_ONLY>
 __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chunk0, const int lane, void *lds) {
   const int32_t *__restrict__ rp = a.row_ptr;
   YT *y = static_cast<YT *>(a.y);
@@ -1146,13 +1689,13 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
   // one round of loads: this chunk's entries, the kShortRun entries after it
   // (lanes 0..kShortRun-1) and the one before it.  Entries past the last
   // bunch read as index -1, value 0.
-  const int idx = valid ? a.sync_idx[tb] : -1;
-  const double own_v = valid ? a.sync_val[tb] : 0.0;
+  const int idx = valid ? a.state[tb].sync_idx : -1;
+  const double own_v = valid ? a.state[tb].sync_val : 0.0;
   const int64_t tt = chunk0 + kWave + lane;
   const bool tail_in = lane < kShortRun && tt < nb;
-  const int tail_i = tail_in ? a.sync_idx[tt] : -1;
-  const double tail_v = tail_in ? a.sync_val[tt] : 0.0;
-  const int before_chunk = chunk0 > 0 ? a.sync_idx[chunk0 - 1] : -1;
+  const int tail_i = tail_in ? a.state[tt].sync_idx : -1;
+  const double tail_v = tail_in ? a.state[tt].sync_val : 0.0;
+  const int before_chunk = chunk0 > 0 ? a.state[chunk0 - 1].sync_idx : -1;
   double *s_val = static_cast<double *>(lds);
   int *s_idx = reinterpret_cast<int *>(s_val + kWave + kShortRun);
   s_idx[lane] = idx;
@@ -1168,15 +1711,19 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
   const bool head = valid && (tb == 0 || prev != idx);
   const bool is_long = head && (tb + kShortRun < nb) && (s_idx[lane + kShortRun] == idx);
   if (head && !is_long) {
-    // sync_idx is non-decreasing (entries past the end read -1): the run is
-    // the prefix of the next kShortRun entries equal to idx
-    double sum = 0.0;
-    for (int j = 0; j < kShortRun; ++j) {
-      if (s_idx[lane + j] != idx) break;
-      sum += s_val[lane + j];
+    const int rs = rp[idx];
+    // (a run of more than one bunch holds a long crossing row)
+    if (!LONG_ONLY || long_crossing(rs, rp[idx + 1], tb * SWT, SWT)) {
+      // sync_idx is non-decreasing (entries past the end read -1): the run is
+      // the prefix of the next kShortRun entries equal to idx
+      double sum = 0.0;
+      for (int j = 0; j < kShortRun; ++j) {
+        if (s_idx[lane + j] != idx) break;
+        sum += s_val[lane + j];
+      }
+      const bool fresh = (int64_t)rs == tb * SWT;
+      y[idx] = (YT)(fresh ? sum : a.state[tb - 1].tail_val + sum);
     }
-    const bool fresh = (int64_t)rp[idx] == tb * SWT;
-    y[idx] = (YT)(fresh ? sum : a.tail_val[tb - 1] + sum);
   }
   uint64_t longs = __ballot(is_long);
   while (longs) {
@@ -1187,14 +1734,14 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
     double acc = 0.0;
     for (int64_t off = 0;; off += kWave) {
       const int64_t j = t0 + off + lane;
-      const bool in = j < nb && a.sync_idx[j] == ridx;
-      if (in) acc += a.sync_val[j];
+      const bool in = j < nb && a.state[j].sync_idx == ridx;
+      if (in) acc += a.state[j].sync_val;
       if (__ballot(in) != ~0ull) break;
     }
     const double total = wave_sum_tree(acc);
     if (lane == l) {
       const bool fresh = (int64_t)rp[ridx] == t0 * SWT;
-      y[ridx] = (YT)(fresh ? total : a.tail_val[t0 - 1] + total);
+      y[ridx] = (YT)(fresh ? total : a.state[t0 - 1].tail_val + total);
     }
   }
   // the staged entries are read before the wavefront's next use of `lds`
@@ -1206,13 +1753,10 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
 // of chunk0 .. chunk0+63 that its list lacks, one after another (the listed
 // ones have their own wavefronts).
 template <typename YT>
-__device__ __forceinline__ void fixup_unlisted(const MatCtx &a, const int64_t chunk0, YT *slots, const int lane,
-                                               const int4 *binfo = nullptr) {
-  // listed: the top bit of bunch_row (single plans), or the last word of the
-  // bunch's entry in binfo (a batch's entries of this matrix)
+__device__ __forceinline__ void fixup_unlisted(const MatCtx &a, const int64_t chunk0, YT *slots, const int lane) {
+  // listed: the top bit of bunch_row
   const int64_t tb = chunk0 + lane;
-  bool todo = false;
-  if (tb < a.n_bunches && a.dirty_mask[tb] != 0) todo = binfo ? binfo[tb].w == 0 : a.bunch_row[tb] >= 0;
+  const bool todo = tb < a.n_bunches && a.state[tb].dirty_mask != 0 && a.bunch_row[tb] >= 0;
   uint64_t todo_bits = __ballot(todo);
   while (todo_bits) {
     const int l = __ffsll((unsigned long long)todo_bits) - 1;
@@ -1226,7 +1770,7 @@ __device__ __forceinline__ void fixup_unlisted(const MatCtx &a, const int64_t ch
 template <typename YT>
 __device__ __forceinline__ void fixup_leading(const MatCtx &a, const int64_t first, const int64_t stride) {
   YT *y = static_cast<YT *>(a.y);
-  const int64_t r_first = a.n_bunches > 0 ? a.sync_idx[0] : a.m;
+  const int64_t r_first = a.n_bunches > 0 ? a.state[0].sync_idx : a.m;
   for (int64_t r = first; r < r_first; r += stride) y[r] = (YT)0;
 }
 
@@ -1246,7 +1790,7 @@ __global__ __launch_bounds__(1024) void sss_fixup(MatCtx a) {
   const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
   const int64_t n_chunks = (a.n_bunches + kWave - 1) / kWave;
   if (wave < n_chunks) {
-    fixup_carries<YT>(a, wave * kWave, lane, slots);
+    fixup_carries<YT, false>(a, wave * kWave, lane, slots);
     if (a.dirty_list && *a.stale) fixup_unlisted<YT>(a, wave * kWave, slots, lane);
   } else if (wave < n_chunks + a.n_fix) {
     fixup_dirty<YT>(a, a.dirty_list ? (int64_t)a.dirty_list[wave - n_chunks] : wave - n_chunks, slots, lane);
@@ -1254,13 +1798,25 @@ __global__ __launch_bounds__(1024) void sss_fixup(MatCtx a) {
   fixup_leading<YT>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
-// Stage 2 of a batch, persistent: work items 0..total_chunks-1 settle one carry
-// chunk (64 bunches of one matrix) each, the next total_bunches re-arrange one
-// global bunch's dirty tiles each, the last count zero one matrix's leading
-// rows each.
+// After the fused kernel: the carries of the long crossing rows, one
+// wavefront per 64 bunches.  What it costs is a launch that depends on the
+// one before it (4 to 5 us behind a running kernel) and one chain of loads,
+// so a plan that knows it has no such row leaves it out.
 template <typename YT>
-__global__ __launch_bounds__(1024) void sss_fixup_batch(BatchArgs b) {
-  extern __shared__ unsigned char lds_raw[];
+__global__ __launch_bounds__(kCarryThreads) void sss_carries(MatCtx a) {
+  __shared__ double lds[kCarryThreads / kWave][kCarryLds];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = threadIdx.x / kWave;
+  const int64_t chunk0 = ((int64_t)blockIdx.x * (kCarryThreads / kWave) + wid) * kWave;
+  if (chunk0 < a.n_bunches) fixup_carries<YT, true>(a, chunk0, lane, lds[wid]);
+}
+
+// The same for a batch, persistent: work items 0..total_chunks-1 settle one
+// carry chunk (64 bunches of one matrix) each (none when no matrix has a long
+// crossing row), the last count zero the y of the matrices without a nonzero.
+template <typename YT>
+__global__ __launch_bounds__(kCarryThreads) void sss_carries_batch(BatchArgs b) {
+  __shared__ double lds[kCarryThreads / kWave][kCarryLds];
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
   const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / kWave);
@@ -1268,19 +1824,10 @@ __global__ __launch_bounds__(1024) void sss_fixup_batch(BatchArgs b) {
     if (w < b.total_chunks) {
       const int i = __builtin_amdgcn_readfirstlane((int)wave_rightmost(b.chunk_base, (int64_t)b.count, w, lane));
       const MatCtx a = uniform_load(b.mats + i);
-      YT *slots = reinterpret_cast<YT *>(lds_raw) + (size_t)wid * a.W * kWave;
-      const int64_t chunk0 = (w - uniform_load(b.chunk_base + i)) * kWave;
-      fixup_carries<YT>(a, chunk0, lane, slots);
-      if (*b.stale) fixup_unlisted<YT>(a, chunk0, slots, lane, b.bunch_info + uniform_load(b.bunch_base + i));
-    } else if (w < b.total_chunks + b.n_fix) {
-      const int64_t g = b.dirty_list[w - b.total_chunks];
-      const int i = __builtin_amdgcn_readfirstlane((int)wave_rightmost(b.bunch_base, (int64_t)b.count, g, lane));
-      const MatCtx a = uniform_load(b.mats + i);
-      YT *slots = reinterpret_cast<YT *>(lds_raw) + (size_t)wid * a.W * kWave;
-      fixup_dirty<YT>(a, g - uniform_load(b.bunch_base + i), slots, lane);
+      fixup_carries<YT, true>(a, (w - uniform_load(b.chunk_base + i)) * kWave, lane, lds[wid]);
     } else {
-      const MatCtx a = uniform_load(b.mats + __builtin_amdgcn_readfirstlane((int)(w - b.total_chunks - b.n_fix)));
-      fixup_leading<YT>(a, lane, kWave);
+      const MatCtx a = uniform_load(b.mats + __builtin_amdgcn_readfirstlane((int)(w - b.total_chunks)));
+      if (a.n_bunches == 0) fixup_leading<YT>(a, lane, kWave);
     }
   }
 }
@@ -1332,45 +1879,33 @@ using Stage1Fn = void (*)(MatCtx);
 using BatchFn = void (*)(BatchArgs);
 
 template <int DT, int W>
-Stage1Fn pick_dbg(bool dbg) { return dbg ? sss_stage1<DT, W, true> : sss_stage1<DT, W, false>; }
+Stage1Fn pick_stage1(bool debug) { return debug ? sss_stage1<DT, W, true> : sss_stage1<DT, W, false>; }
 
-template <int DT>
-Stage1Fn pick_w(int W, bool dbg) {
-  switch (W) {
-    case 4: return pick_dbg<DT, 4>(dbg);
-    case 8: return pick_dbg<DT, 8>(dbg);
-    case 16: return pick_dbg<DT, 16>(dbg);
-    default: return nullptr;
-  }
+template <int DT, int W>
+Stage1Fn pick_fused(Form form) {
+  return form == kCached ? sss_fused<DT, W, kCached>
+                         : (form == kStreamed ? sss_fused<DT, W, kStreamed> : sss_fused<DT, W, kWide>);
 }
 
-Stage1Fn pick_stage1(int dt, int W, bool dbg) {
-  switch (dt) {
-    case SSS_F64: return pick_w<SSS_F64>(W, dbg);
-    case SSS_F32: return pick_w<SSS_F32>(W, dbg);
-    case SSS_BF16: return pick_w<SSS_BF16>(W, dbg);
-    default: return nullptr;
-  }
+template <int DT, int W, Form FORM>
+BatchFn pick_batch_form(bool persistent) {
+  return persistent ? sss_fused_batch_persistent<DT, W, FORM> : sss_fused_batch<DT, W, FORM>;
 }
 
-template <int DT>
-BatchFn pick_batch_w(int W, bool persistent) {
-  switch (W) {
-    case 4: return persistent ? sss_stage1_batch_persistent<DT, 4> : sss_stage1_batch<DT, 4>;
-    case 8: return persistent ? sss_stage1_batch_persistent<DT, 8> : sss_stage1_batch<DT, 8>;
-    case 16: return persistent ? sss_stage1_batch_persistent<DT, 16> : sss_stage1_batch<DT, 16>;
-    default: return nullptr;
-  }
+template <int DT, int W>
+BatchFn pick_batch(Form form, bool persistent) {
+  return form == kCached ? pick_batch_form<DT, W, kCached>(persistent)
+                         : (form == kStreamed ? pick_batch_form<DT, W, kStreamed>(persistent)
+                                              : pick_batch_form<DT, W, kWide>(persistent));
 }
 
-BatchFn pick_stage1_batch(int dt, int W, bool persistent) {
-  switch (dt) {
-    case SSS_F64: return pick_batch_w<SSS_F64>(W, persistent);
-    case SSS_F32: return pick_batch_w<SSS_F32>(W, persistent);
-    case SSS_BF16: return pick_batch_w<SSS_BF16>(W, persistent);
-    default: return nullptr;
-  }
-}
+// the instance of a value type and W: PICK<DT, W>(args)
+#define SSS_PICK_W(PICK, DT, W, ...) \
+  (W == 4 ? PICK<DT, 4>(__VA_ARGS__) : (W == 8 ? PICK<DT, 8>(__VA_ARGS__) : (W == 16 ? PICK<DT, 16>(__VA_ARGS__) : nullptr)))
+#define SSS_PICK(PICK, dt, W, ...)                                            \
+  ((dt) == SSS_F64 ? SSS_PICK_W(PICK, SSS_F64, W, __VA_ARGS__)                \
+                   : ((dt) == SSS_F32 ? SSS_PICK_W(PICK, SSS_F32, W, __VA_ARGS__) \
+                                      : SSS_PICK_W(PICK, SSS_BF16, W, __VA_ARGS__)))
 
 }  // namespace
 
@@ -1385,16 +1920,14 @@ struct sss_plan_s {
   int64_t n_tiles = 0, n_bunches = 0;
   void *aux = nullptr;
   bool owns_aux = false;  // false: caller-provided workspace, or the static scratch
-  uint32_t *dirty_mask = nullptr;
+  BunchState *state = nullptr;
   int4 *speculator = nullptr;
-  int32_t *sync_idx = nullptr;
-  double *sync_val = nullptr;
-  double *tail_val = nullptr;
   int32_t *bunch_row = nullptr;  // plans made with bind_rows only
   int32_t *dirty_list = nullptr; // bind_rows plans: the bunches with a dirty tile, found at plan time
   int64_t n_listed = 0;
-  int32_t *stale = nullptr;      // bind_rows plans: one word, see MatCtx::stale
-  int32_t *order = nullptr;      // bind_rows plans that gain from it: see sss_order_scatter
+  int32_t *stale = nullptr;      // bind_rows plans: see MatCtx::stale; the word after it: any long crossing row
+  int32_t carries = 1;           // 0: no long crossing row at plan time (see sss_fused), so no second launch
+  int4 *slots = nullptr;         // bind_rows plans: see MatCtx::slots
   uint32_t *order_hist = nullptr;
   int64_t n_slots = 0;
   int32_t *dbg_start = nullptr;
@@ -1403,9 +1936,10 @@ struct sss_plan_s {
   // batch plans only
   bool batch = false;
   bool batch_persistent = false;
+  Form batch_form = kCached;
   BatchArgs bargs{};
   std::vector<int> mat_S;  // each matrix's tiles per thread-bunch
-  int blocks1 = 0, blocks2 = 0, wpb2 = 1;
+  int blocks1 = 0, blocks2 = 0;
   hipStream_t capture_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
@@ -1420,7 +1954,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // entry per tile), every array 256-byte aligned.
 struct AuxLayout {
   int64_t n_tiles = 0, n_bunches = 0;
-  size_t dmask = 0, spec = 0, sidx = 0, sval = 0, tail = 0, brow = 0, dlist = 0, stale = 0, order = 0, ohist = 0,
+  size_t state = 0, spec = 0, brow = 0, dlist = 0, stale = 0, slots = 0, ohist = 0,
          dstart = 0, ddirty = 0, dheads = 0;
   size_t total = 0;
 };
@@ -1433,16 +1967,15 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug) {
   L.n_bunches = nnz > 0 ? (nnz + SWT - 1) / SWT : 0;
   const size_t nt = (size_t)L.n_tiles, nb = (size_t)L.n_bunches;
   size_t off = 0;
-  L.dmask = off; off = align256(off + sizeof(uint32_t) * (nb + 1));
+  // (the size of two 4-byte and two 8-byte arrays, which the largest nnz of
+  // sss_csr_spmv_noalloc is stated for)
+  L.state = off; off += 2 * align256(sizeof(int32_t) * (nb + 1)) + 2 * align256(sizeof(double) * (nb + 1));
   L.spec = off; off = align256(off + sizeof(int4) * (nb * (size_t)S + 1));
-  L.sidx = off; off = align256(off + sizeof(int32_t) * (nb + 1));
-  L.sval = off; off = align256(off + sizeof(double) * (nb + 1));
-  L.tail = off; off = align256(off + sizeof(double) * (nb + 1));
   if (bind) {
     L.brow = off; off = align256(off + sizeof(int32_t) * (nb + 1));
     L.dlist = off; off = align256(off + sizeof(int32_t) * (nb + 1));
-    L.stale = off; off = align256(off + sizeof(int32_t));
-    L.order = off; off = align256(off + sizeof(int32_t) * (nb + kXcds * kMaxB));
+    L.stale = off; off = align256(off + sizeof(int32_t) * 2);
+    L.slots = off; off = align256(off + sizeof(int4) * (nb + kXcds * kMaxB));
     L.ohist = off; off = align256(off + sizeof(uint32_t) * 2 * (kOrderBins + 1));
   }
   if (debug) {
@@ -1460,15 +1993,13 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
   p->n_tiles = L.n_tiles;
   p->n_bunches = L.n_bunches;
   p->aux = base_v;
-  p->dirty_mask = reinterpret_cast<uint32_t *>(base + L.dmask);
+  p->state = reinterpret_cast<BunchState *>(base + L.state);
   p->speculator = reinterpret_cast<int4 *>(base + L.spec);
-  p->sync_idx = reinterpret_cast<int32_t *>(base + L.sidx);
-  p->sync_val = reinterpret_cast<double *>(base + L.sval);
-  p->tail_val = reinterpret_cast<double *>(base + L.tail);
   p->bunch_row = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
   p->dirty_list = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.dlist) : nullptr;
   p->stale = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.stale) : nullptr;
-  p->order = nullptr;  // set by plan_order
+  p->carries = L.n_bunches > 1 ? 1 : 0;
+  p->slots = p->bind_rows ? reinterpret_cast<int4 *>(base + L.slots) : nullptr;
   p->order_hist = p->bind_rows ? reinterpret_cast<uint32_t *>(base + L.ohist) : nullptr;
   p->dbg_start = p->debug ? reinterpret_cast<int32_t *>(base + L.dstart) : nullptr;
   p->dbg_dirty = p->debug ? reinterpret_cast<int32_t *>(base + L.ddirty) : nullptr;
@@ -1512,27 +2043,41 @@ int check_call(sss_plan p, const int32_t *row_ptr, const int32_t *col, const voi
   return SSS_OK;
 }
 
+// The form for nnz nonzeros (of a whole batch) and an x of n entries (its
+// largest).
+// Streamed from 60 MB of columns and values on, three matrices in turn: 46 MB
+// (power law 200K rows) 30.2 us cached, 32.7 streamed; 42 MB (dense rows)
+// 41.4, 43.1; 63 MB (CG on the 1024^2 Laplacian) 39.3, 39.0 per step; 72 MB
+// (web-like 2M rows) 101.0, 99.4; 160 MB (5-point stencil) 35.2, 32.4; 320 MB
+// (FEM band FP32) 71, 65.
+constexpr int64_t kStreamBytes = int64_t(60) << 20;
+Form form_of(int64_t nnz, int64_t n, int dt) {
+  if (n * (int64_t)y_size(dt) > 0xfffffff0ll) return kWide;
+  const int64_t value = dt == SSS_F64 ? 8 : (dt == SSS_F32 ? 4 : 2);
+  return nnz * (4 + value) >= kStreamBytes ? kStreamed : kCached;
+}
+
 // The kernels' view of a single-matrix plan and the caller's arrays.
 MatCtx plan_ctx(sss_plan p, const int32_t *row_ptr, const int32_t *col, const void *val, const void *x, void *y) {
   MatCtx a{};
   a.row_ptr = row_ptr; a.col = col; a.val = val; a.x = x; a.y = y;
   a.m = (int32_t)p->m; a.nnz = (int32_t)p->nnz; a.S = p->S; a.W = p->W;
   a.n_bunches = p->n_bunches; a.n_tiles = p->n_tiles;
-  a.dirty_mask = p->dirty_mask; a.speculator = p->speculator;
-  a.sync_idx = p->sync_idx; a.sync_val = p->sync_val; a.tail_val = p->tail_val;
+  a.state = p->state; a.speculator = p->speculator;
   a.bunch_row = p->bunch_row;
   a.dirty_list = p->dirty_list;
   a.n_fix = p->dirty_list ? p->n_listed : p->n_bunches;
   a.stale = p->stale;
-  a.order = p->order;
+  a.carries = p->carries;
+  a.slots = p->slots;
   a.n_slots = p->n_slots;
   a.dbg_start = p->dbg_start; a.dbg_dirty = p->dbg_dirty; a.dbg_heads = p->dbg_heads;
   return a;
 }
 
-// Stage 1: speculative execution.  (nnz = 0: y is zeroed here.)
+// Stage 1 alone (`split`), or the fused kernel.  (nnz = 0: y is zeroed here.)
 int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const void *val, const void *x, void *y,
-                  hipStream_t stream) {
+                  bool split, hipStream_t stream) {
   if (p->m == 0) return SSS_OK;
   if (p->nnz == 0) {
     const int blocks = (int)std::min<int64_t>((p->m + 255) / 256, 4096);
@@ -1543,10 +2088,11 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
     SSS_HIP(hipGetLastError());
     return SSS_OK;
   }
-  Stage1Fn k1 = pick_stage1(p->dt, p->W, p->debug != 0);
+  Stage1Fn k1 = split ? SSS_PICK(pick_stage1, p->dt, p->W, p->debug != 0)
+                      : SSS_PICK(pick_fused, p->dt, p->W, form_of(p->nnz, p->n, p->dt));
   if (!k1) return SSS_ERR_UNSUPPORTED;
   const MatCtx a1 = plan_ctx(p, row_ptr, col, val, x, y);
-  const int64_t blocks1 = ((p->order ? p->n_slots : p->n_bunches) + p->B - 1) / p->B;
+  const int64_t blocks1 = ((p->slots ? p->n_slots : p->n_bunches) + p->B - 1) / p->B;
   const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
   hipLaunchKernelGGL(k1, dim3((unsigned)blocks1), dim3(p->B * kWave), lds1, stream, a1);
   SSS_HIP(hipGetLastError());
@@ -1577,30 +2123,37 @@ int launch(sss_plan p, const int32_t *row_ptr, const int32_t *col, const void *v
            hipStream_t stream) {
   int rc = check_call(p, row_ptr, col, val, x, y);
   if (rc != SSS_OK || p->m == 0) return rc;
-  rc = launch_stage1(p, row_ptr, col, val, x, y, stream);
-  if (rc != SSS_OK) return rc;
-  return launch_stage2(p, row_ptr, y, stream);
+  // a debug plan records the two stages as the paper has them
+  rc = launch_stage1(p, row_ptr, col, val, x, y, p->debug != 0, stream);
+  if (rc != SSS_OK || p->nnz == 0) return rc;
+  if (p->debug) return launch_stage2(p, row_ptr, y, stream);
+  if (!p->carries) return SSS_OK;
+  const MatCtx a = plan_ctx(p, row_ptr, nullptr, nullptr, nullptr, y);
+  const int64_t per_block = (int64_t)(kCarryThreads / kWave) * kWave;
+  const unsigned blocks = (unsigned)((p->n_bunches + per_block - 1) / per_block);
+  if (p->dt == SSS_F64)
+    hipLaunchKernelGGL(sss_carries<double>, dim3(blocks), dim3(kCarryThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(sss_carries<float>, dim3(blocks), dim3(kCarryThreads), 0, stream, a);
+  SSS_HIP(hipGetLastError());
+  return SSS_OK;
 }
 
-// Both stages of a batch plan: the stage-1 launch (one wavefront per
-// thread-bunch of every matrix, or the persistent form), then the persistent
-// stage-2 launch.
+// A batch plan: the fused launch (one wavefront per thread-bunch of every
+// matrix, or the persistent form), then the carries where the plan needs them.
 int launch_batch(sss_plan p, hipStream_t stream) {
-  if (p->bargs.total_waves == 0) return SSS_OK;
   if (p->bargs.total_bunches > 0) {
-    BatchFn k1 = pick_stage1_batch(p->dt, p->W, p->batch_persistent);
+    BatchFn k1 = SSS_PICK(pick_batch, p->dt, p->W, p->batch_form, p->batch_persistent);
     if (!k1) return SSS_ERR_UNSUPPORTED;
     const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->bargs.S_max) * sizeof(uint32_t);
     hipLaunchKernelGGL(k1, dim3((unsigned)p->blocks1), dim3(p->B * kWave), lds1, stream, p->bargs);
     SSS_HIP(hipGetLastError());
   }
-  const size_t lds2 = (size_t)p->wpb2 * p->W * kWave * y_size(p->dt);
+  if (p->bargs.total_waves == 0) return SSS_OK;
   if (p->dt == SSS_F64)
-    hipLaunchKernelGGL(sss_fixup_batch<double>, dim3((unsigned)p->blocks2), dim3(p->wpb2 * kWave), lds2, stream,
-                       p->bargs);
+    hipLaunchKernelGGL(sss_carries_batch<double>, dim3((unsigned)p->blocks2), dim3(kCarryThreads), 0, stream, p->bargs);
   else
-    hipLaunchKernelGGL(sss_fixup_batch<float>, dim3((unsigned)p->blocks2), dim3(p->wpb2 * kWave), lds2, stream,
-                       p->bargs);
+    hipLaunchKernelGGL(sss_carries_batch<float>, dim3((unsigned)p->blocks2), dim3(kCarryThreads), 0, stream, p->bargs);
   SSS_HIP(hipGetLastError());
   return SSS_OK;
 }
@@ -1677,17 +2230,16 @@ int launch_floor_w(sss_plan p, const MatCtx &a, void *out, int gather, hipStream
 // Stage 2 on a host core, as the paper runs it (Section 3.2, Section 3.4): the
 // same three parts as the device kernel, on host arrays, one thread.
 template <typename YT>
-void stage2_host(sss_plan p, const int32_t *rp, YT *y, const uint32_t *dm, const int4 *spec, const int32_t *si,
-                 const double *sv, const double *tv) {
+void stage2_host(sss_plan p, const int32_t *rp, YT *y, const BunchState *st, const int4 *spec) {
   const int64_t nb = p->n_bunches;
   const int64_t WT = (int64_t)p->W * kWave, SWT = (int64_t)p->S * WT;
   // leading empty rows
-  const int64_t r_first = nb > 0 ? si[0] : p->m;
+  const int64_t r_first = nb > 0 ? st[0].sync_idx : p->m;
   for (int64_t r = 0; r < r_first; ++r) y[r] = (YT)0;
   // dirty tiles: partial k >= 1 to the k-th non-empty row strictly inside
   std::vector<YT> slots((size_t)WT);
   for (int64_t tb = 0; tb < nb; ++tb) {
-    const int n_dirty = __builtin_popcount(dm[tb]);
+    const int n_dirty = __builtin_popcount(st[tb].dirty_mask);
     for (int e = 0; e < n_dirty; ++e) {
       const int4 s = spec[tb * p->S + e];
       const int start = s.x, stop = s.y;
@@ -1704,12 +2256,12 @@ void stage2_host(sss_plan p, const int32_t *rp, YT *y, const uint32_t *dm, const
   // order after the tail of the bunch before the run (unless the row begins
   // with the run)
   for (int64_t tb = 0; tb < nb;) {
-    const int idx = si[tb];
+    const int idx = st[tb].sync_idx;
     int64_t e = tb;
     double sum = 0.0;
-    while (e < nb && si[e] == idx) sum += sv[e++];
+    while (e < nb && st[e].sync_idx == idx) sum += st[e++].sync_val;
     const bool fresh = (int64_t)rp[idx] == tb * SWT;
-    y[idx] = (YT)(fresh ? sum : tv[tb - 1] + sum);
+    y[idx] = (YT)(fresh ? sum : st[tb - 1].tail_val + sum);
     tb = e;
   }
 }
@@ -1752,8 +2304,8 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
 
 namespace {
 
-// Bound plans: stage 1's column order (see sss_order_keys), where it can
-// gain: x must be larger than what stays in an XCD's 4 MB L2 beside the
+// Bound plans: stage 1's slots, in column order (see sss_order_keys) where it
+// can gain: x must be larger than what stays in an XCD's 4 MB L2 beside the
 // streamed matrix (power law, Zipf and dense rows: 2.16 MB of x 1% slower to
 // 1% faster, 2.8 MB 1 to 3%, 3.2 MB 2 to 4%, 4 MB 6 to 9%, 8 MB 9 to 22%
 // faster), and enough bunches must lie in long rows.  The order is made on
@@ -1763,37 +2315,45 @@ namespace {
 constexpr int64_t kOrderMinX = int64_t(5) << 19;
 constexpr int64_t kOrderMinBunches = 2048;
 
-int plan_order(sss_plan p, const int32_t *row_ptr, int32_t *order, int64_t SWT, hipStream_t s) {
+int plan_slots(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t s) {
   const int64_t nb = p->n_bunches, x_bytes = p->n * (int64_t)y_size(p->dt);
-  if (x_bytes < kOrderMinX || nb < kOrderMinBunches) return SSS_OK;
-  const int64_t group = (int64_t)kXcds * p->B, n_slots = (nb + group - 1) / group * group;
-  uint32_t *keys = reinterpret_cast<uint32_t *>(p->speculator), *hist = p->order_hist;
-  hipLaunchKernelGGL(sss_order_keys, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, row_ptr, (int32_t)p->m,
-                     (int32_t)p->nnz, SWT, nb, p->bunch_row, keys, hist);
+  const unsigned blocks = (unsigned)((nb + 255) / 256);
+  const int32_t m = (int32_t)p->m;
+  if (x_bytes >= kOrderMinX && nb >= kOrderMinBunches) {
+    const int64_t group = (int64_t)kXcds * p->B, n_slots = (nb + group - 1) / group * group;
+    uint32_t *keys = reinterpret_cast<uint32_t *>(p->speculator), *hist = p->order_hist;
+    hipLaunchKernelGGL(sss_order_keys, dim3(blocks), dim3(256), 0, s, row_ptr, m, (int32_t)p->nnz, SWT, nb,
+                       p->bunch_row, keys, hist);
+    SSS_HIP(hipGetLastError());
+    uint32_t n_short = 0;
+    SSS_HIP(hipMemcpyAsync(&n_short, hist + kOrderBins, sizeof(n_short), hipMemcpyDeviceToHost, s));
+    SSS_HIP(hipStreamSynchronize(s));
+    if ((nb - (int64_t)n_short) * 16 >= nb) {
+      hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, row_ptr, m, SWT,
+                         nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
+      SSS_HIP(hipGetLastError());
+      p->n_slots = n_slots;
+      return SSS_OK;
+    }
+  }
+  hipLaunchKernelGGL(sss_slots, dim3(blocks), dim3(256), 0, s, row_ptr, m, SWT, nb, p->bunch_row, p->slots);
   SSS_HIP(hipGetLastError());
-  hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, keys, nb, n_slots,
-                     p->B, hist, hist + kOrderBins + 1, order);
-  SSS_HIP(hipGetLastError());
-  uint32_t n_short = 0;
-  SSS_HIP(hipMemcpyAsync(&n_short, hist + kOrderBins, sizeof(n_short), hipMemcpyDeviceToHost, s));
-  SSS_HIP(hipStreamSynchronize(s));
-  if ((nb - (int64_t)n_short) * 16 < nb) return SSS_OK;
-  p->order = order;
-  p->n_slots = n_slots;
+  p->n_slots = nb;
   return SSS_OK;
 }
 
 // Bound plans: mark every bunch with a dirty tile on the device, then list
-// them on the host (bunch order) and copy the list to the plan; synchronises
-// `s`.
+// them on the host (bunch order) and copy the list to the plan; reads back
+// whether any row is a long crossing row; synchronises `s`.
 int plan_list_dirty(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t s) {
   const size_t nb = (size_t)p->n_bunches;
   const unsigned blocks = (unsigned)std::min<int64_t>((p->m + 255) / 256, 4096);
   hipLaunchKernelGGL(sss_mark_dirty_bunches, dim3(blocks), dim3(256), 0, s, row_ptr, (int32_t)p->m, SWT,
-                     reinterpret_cast<uint32_t *>(p->bunch_row), 1, 0x80000000u);
+                     reinterpret_cast<uint32_t *>(p->bunch_row), 0x80000000u);
   SSS_HIP(hipGetLastError());
   std::vector<int32_t> br(nb);
   SSS_HIP(hipMemcpyAsync(br.data(), p->bunch_row, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  SSS_HIP(hipMemcpyAsync(&p->carries, p->stale + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   SSS_HIP(hipStreamSynchronize(s));
   std::vector<int32_t> list;
   for (size_t tb = 0; tb < nb; ++tb)
@@ -1854,16 +2414,13 @@ int sss_csr_spmv_plan_create(int64_t m, int64_t n, int64_t nnz, const int32_t *r
     const int64_t SWT = (int64_t)p->S * p->W * kWave;
     const unsigned blocks = (unsigned)std::min<int64_t>((p->n_bunches + 255) / 256, 65535);
     hipLaunchKernelGGL(sss_bunch_rows, dim3(blocks), dim3(256), 0, s, row_ptr, (int32_t)m, SWT, p->n_bunches,
-                       p->bunch_row);
+                       p->bunch_row, p->stale + 1);
     e = hipGetLastError();
     if (e != hipSuccess) { g_last_hip = e; rc = SSS_ERR_HIP; }
     // the bunches with a dirty tile (marked in bunch_row's top bit), listed
     // in order so that stage 2 gives only them a wavefront
     if (rc == SSS_OK) rc = plan_list_dirty(p, row_ptr, SWT, s);
-    if (rc == SSS_OK) {
-      const AuxLayout L = aux_layout(nnz, p->W, p->S, true, p->debug != 0);
-      rc = plan_order(p, row_ptr, reinterpret_cast<int32_t *>(static_cast<char *>(p->aux) + L.order), SWT, s);
-    }
+    if (rc == SSS_OK) rc = plan_slots(p, row_ptr, SWT, s);
   }
   if (rc == SSS_OK) {
     e = hipStreamSynchronize(s);
@@ -1898,7 +2455,7 @@ int sss_csr_spmv_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, 
   if (!p || p->batch) return SSS_ERR_INVALID_VALUE;
   const int rc = check_call(p, row_ptr, col, val, x, y);
   if (rc != SSS_OK || p->m == 0) return rc;
-  return launch_stage1(p, row_ptr, col, val, x, y, static_cast<hipStream_t>(stream));
+  return launch_stage1(p, row_ptr, col, val, x, y, true, static_cast<hipStream_t>(stream));
 }
 
 int sss_floor_probe(sss_plan p, const int32_t *col, const void *val, const void *x, void *out, int gather,
@@ -2006,20 +2563,15 @@ int sss_csr_spmv_stage2_host(sss_plan p, const int32_t *row_ptr, void *y) {
   if (p->m == 0 || p->nnz == 0) return SSS_OK;
   if (!row_ptr || !y) return SSS_ERR_INVALID_VALUE;
   const size_t nb = (size_t)p->n_bunches;
-  std::vector<uint32_t> dm(nb);
+  std::vector<BunchState> st(nb);
   std::vector<int4> spec(nb * (size_t)p->S);
-  std::vector<int32_t> si(nb);
-  std::vector<double> sv(nb), tv(nb);
   SSS_HIP(hipDeviceSynchronize());
-  SSS_HIP(hipMemcpy(dm.data(), p->dirty_mask, nb * sizeof(uint32_t), hipMemcpyDeviceToHost));
+  SSS_HIP(hipMemcpy(st.data(), p->state, nb * sizeof(BunchState), hipMemcpyDeviceToHost));
   SSS_HIP(hipMemcpy(spec.data(), p->speculator, spec.size() * sizeof(int4), hipMemcpyDeviceToHost));
-  SSS_HIP(hipMemcpy(si.data(), p->sync_idx, nb * sizeof(int32_t), hipMemcpyDeviceToHost));
-  SSS_HIP(hipMemcpy(sv.data(), p->sync_val, nb * sizeof(double), hipMemcpyDeviceToHost));
-  SSS_HIP(hipMemcpy(tv.data(), p->tail_val, nb * sizeof(double), hipMemcpyDeviceToHost));
   if (p->dt == SSS_F64)
-    stage2_host(p, row_ptr, static_cast<double *>(y), dm.data(), spec.data(), si.data(), sv.data(), tv.data());
+    stage2_host(p, row_ptr, static_cast<double *>(y), st.data(), spec.data());
   else
-    stage2_host(p, row_ptr, static_cast<float *>(y), dm.data(), spec.data(), si.data(), sv.data(), tv.data());
+    stage2_host(p, row_ptr, static_cast<float *>(y), st.data(), spec.data());
   return SSS_OK;
 }
 
@@ -2102,8 +2654,10 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   }
   const int WT = W * kWave;
   std::vector<MatCtx> ctx((size_t)count);
-  std::vector<int64_t> bb((size_t)count + 1, 0), cb((size_t)count + 1, 0), sb((size_t)count + 1, 0);
+  std::vector<int64_t> bb((size_t)count + 1, 0), cb((size_t)count + 1, 0);
   int s_max = 1;
+  int64_t n_max = 0;
+  bool any_zero = false;  // a matrix with rows and no nonzero
   int64_t tot_m = 0, tot_n = 0, tot_nnz = 0, tot_tiles = 0;
   for (int i = 0; i < count; ++i) {
     const sss_csr_desc &d = mats[i];
@@ -2122,28 +2676,25 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
     c.dbg_start = nullptr; c.dbg_dirty = nullptr; c.dbg_heads = nullptr;
     bb[(size_t)i + 1] = bb[(size_t)i] + nb;
     cb[(size_t)i + 1] = cb[(size_t)i] + (nb + kWave - 1) / kWave;
-    sb[(size_t)i + 1] = sb[(size_t)i] + nb * Si;
+    n_max = std::max(n_max, d.n);
+    any_zero = any_zero || (d.m > 0 && nb == 0);
     tot_m += d.m; tot_n += d.n; tot_nnz += d.nnz; tot_tiles += c.n_tiles;
   }
-  const int64_t nb_all = bb[(size_t)count], spec_all = sb[(size_t)count];
-  // global bunch indices are listed as int32 (the dirty list): more bunches
-  // than that is beyond any batch that fits in memory
+  const int64_t nb_all = bb[(size_t)count];
+  // one wavefront per bunch in one grid: more bunches than this is beyond
+  // any batch that fits in memory
   if (nb_all > INT32_MAX) return SSS_ERR_INVALID_VALUE;
   size_t off = 0;
   const size_t o_mats = off; off = align256(off + sizeof(MatCtx) * (size_t)std::max(count, 1));
   const size_t o_bb = off; off = align256(off + sizeof(int64_t) * ((size_t)count + 1));
   const size_t o_cb = off; off = align256(off + sizeof(int64_t) * ((size_t)count + 1));
-  const size_t o_dm = off; off = align256(off + sizeof(uint32_t) * (size_t)(nb_all + 1));
-  const size_t o_sp = off; off = align256(off + sizeof(int4) * (size_t)(spec_all + 1));
-  const size_t o_si = off; off = align256(off + sizeof(int32_t) * (size_t)(nb_all + 1));
-  const size_t o_sv = off; off = align256(off + sizeof(double) * (size_t)(nb_all + 1));
-  const size_t o_tv = off; off = align256(off + sizeof(double) * (size_t)(nb_all + 1));
+  const size_t o_bs = off; off = align256(off + sizeof(BunchState) * (size_t)(nb_all + 1));
   const size_t o_bi = off; off = align256(off + sizeof(int4) * (size_t)(nb_all + 1));
-  const size_t o_dl = off; off = align256(off + sizeof(int32_t) * (size_t)(nb_all + 1));
-  const size_t o_st = off; off = align256(off + sizeof(int32_t));
+  const size_t o_al = off; off = align256(off + sizeof(int32_t));
 
   sss_plan p = new sss_plan_s();
   p->batch = true; p->dt = dt; p->W = W; p->S = S; p->B = B; p->batch_persistent = o.batch_persistent != 0;
+  p->batch_form = form_of(tot_nnz, n_max, dt);
   p->mat_S.resize((size_t)count);
   for (int i = 0; i < count; ++i) p->mat_S[(size_t)i] = ctx[(size_t)i].S;
   p->m = tot_m; p->n = tot_n; p->nnz = tot_nnz; p->n_tiles = tot_tiles; p->n_bunches = nb_all;
@@ -2164,12 +2715,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   char *base = static_cast<char *>(p->aux);
   for (int i = 0; i < count; ++i) {
     MatCtx &c = ctx[(size_t)i];
-    c.dirty_mask = reinterpret_cast<uint32_t *>(base + o_dm) + bb[(size_t)i];
-    c.speculator = reinterpret_cast<int4 *>(base + o_sp) + sb[(size_t)i];
-    c.sync_idx = reinterpret_cast<int32_t *>(base + o_si) + bb[(size_t)i];
-    c.sync_val = reinterpret_cast<double *>(base + o_sv) + bb[(size_t)i];
-    c.tail_val = reinterpret_cast<double *>(base + o_tv) + bb[(size_t)i];
-    c.stale = reinterpret_cast<int32_t *>(base + o_st);
+    c.state = reinterpret_cast<BunchState *>(base + o_bs) + bb[(size_t)i];
   }
   // host arrays stay alive until the stream synchronisation below
   if (count > 0)
@@ -2186,9 +2732,6 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   ba.count = count;
   ba.S_max = s_max;
   ba.total_bunches = nb_all;
-  ba.total_chunks = cb[(size_t)count];
-  ba.dirty_list = reinterpret_cast<const int32_t *>(base + o_dl);
-  ba.stale = reinterpret_cast<int32_t *>(base + o_st);
   // every global bunch's matrix, first row and index within the matrix, once
   // for all calls (the descriptors, and so the row pointers, are bound to the plan)
   int4 *binfo = reinterpret_cast<int4 *>(base + o_bi);
@@ -2196,47 +2739,24 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   if (nb_all > 0) {
     const unsigned blocks = (unsigned)std::min<int64_t>((nb_all + 255) / 256, 65535);
     hipLaunchKernelGGL(sss_batch_bunch_info, dim3(blocks), dim3(256), 0, s, ba.mats, ba.bunch_base, count, nb_all,
-                       binfo);
+                       binfo, reinterpret_cast<int32_t *>(base + o_al));
     e = hipGetLastError();
     if (e != hipSuccess) return fail(e);
-    // the bunches with a dirty tile, marked in their bunch_info entries
-    for (int i = 0; i < count && e == hipSuccess; ++i) {
-      const MatCtx &c = ctx[(size_t)i];
-      if (c.n_bunches == 0) continue;
-      const unsigned mb = (unsigned)std::min<int64_t>(((int64_t)c.m + 255) / 256, 4096);
-      hipLaunchKernelGGL(sss_mark_dirty_bunches, dim3(mb), dim3(256), 0, s, c.row_ptr, c.m, (int64_t)c.S * WT,
-                         reinterpret_cast<uint32_t *>(binfo + bb[(size_t)i]) + 3, 4, 1u);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) return fail(e);
   }
+  e = hipMemcpyAsync(&ba.carries, base + o_al, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (e != hipSuccess) return fail(e);
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail(e);
-  // list them in order, so that stage 2 gives only them a work item
-  std::vector<int32_t> dlist;
-  if (nb_all > 0) {
-    std::vector<int4> bi_host((size_t)nb_all);
-    e = hipMemcpy(bi_host.data(), binfo, sizeof(int4) * (size_t)nb_all, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(e);
-    for (int64_t g = 0; g < nb_all; ++g)
-      if (bi_host[(size_t)g].w) dlist.push_back((int32_t)g);
-    if (!dlist.empty()) {
-      e = hipMemcpy(base + o_dl, dlist.data(), sizeof(int32_t) * dlist.size(), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return fail(e);
-    }
-  }
-  ba.n_fix = (int64_t)dlist.size();
-  ba.total_waves = ba.total_chunks + ba.n_fix + count;
-  // stage 2's persistent grid: as many workgroups as stay resident on the device
+  ba.total_chunks = ba.carries ? cb[(size_t)count] : 0;
+  ba.total_waves = ba.total_chunks + (any_zero ? count : 0);
+  // the carries' persistent grid: as many workgroups as stay resident on the device
   int cus = 0;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e != hipSuccess) return fail(e);
   int per_cu2 = 0;
-  p->wpb2 = fixup_waves_per_block(W, dt);
-  const size_t lds2 = (size_t)p->wpb2 * WT * y_size(dt);
-  const void *k2 = dt == SSS_F64 ? reinterpret_cast<const void *>(sss_fixup_batch<double>)
-                                 : reinterpret_cast<const void *>(sss_fixup_batch<float>);
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu2, k2, p->wpb2 * kWave, lds2);
+  const void *k2 = dt == SSS_F64 ? reinterpret_cast<const void *>(sss_carries_batch<double>)
+                                 : reinterpret_cast<const void *>(sss_carries_batch<float>);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu2, k2, kCarryThreads, 0);
   if (e != hipSuccess) return fail(e);
   // stage 1: B bunches per workgroup, the count rounded up to a multiple of
   // kXcds so that every XCD gets an equal contiguous run (the extra
@@ -2247,7 +2767,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
     int per_cu1 = 0;
     const size_t lds1 = (size_t)B * stage1_lds_words(W, s_max) * sizeof(uint32_t);
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu1, reinterpret_cast<const void *>(pick_stage1_batch(dt, W, true)), B * kWave, lds1);
+        &per_cu1, reinterpret_cast<const void *>(SSS_PICK(pick_batch, dt, W, p->batch_form, true)), B * kWave, lds1);
     if (e != hipSuccess) return fail(e);
     wgs1 = std::min<int64_t>(wgs1, (int64_t)cus * std::max(per_cu1, 1));
     if (wgs1 > kXcds) wgs1 -= wgs1 % kXcds;
@@ -2283,8 +2803,9 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
     return SSS_ERR_INVALID_VALUE;
   }
   p->blocks1 = (int)wgs1;
+  const int64_t wpb2 = kCarryThreads / kWave;
   p->blocks2 = (int)std::max<int64_t>(
-      1, std::min<int64_t>((ba.total_waves + p->wpb2 - 1) / p->wpb2, (int64_t)cus * std::max(per_cu2, 1)));
+      1, std::min<int64_t>((ba.total_waves + wpb2 - 1) / wpb2, (int64_t)cus * std::max(per_cu2, 1)));
   *out = p;
   return SSS_OK;
 }
@@ -2418,15 +2939,15 @@ int sss_plan_debug_dump(sss_plan p, void *host_buf, size_t bytes) {
   const int64_t nt = p->n_tiles, nb = p->n_bunches;
   const int64_t wpt = (int64_t)p->W * kWave / 32;
   // the per-bunch speculator segments, packed into one list in bunch order
-  std::vector<uint32_t> dmask((size_t)nb);
+  std::vector<BunchState> st((size_t)nb);
   std::vector<int4> spec((size_t)(nb * p->S));
   if (nb > 0) {
-    SSS_HIP(hipMemcpy(dmask.data(), p->dirty_mask, nb * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    SSS_HIP(hipMemcpy(st.data(), p->state, nb * sizeof(BunchState), hipMemcpyDeviceToHost));
     SSS_HIP(hipMemcpy(spec.data(), p->speculator, nb * p->S * sizeof(int4), hipMemcpyDeviceToHost));
   }
   std::vector<int4> packed;
   for (int64_t b = 0; b < nb; ++b)
-    for (int i = 0; i < __builtin_popcount(dmask[(size_t)b]); ++i) packed.push_back(spec[(size_t)(b * p->S + i)]);
+    for (int i = 0; i < __builtin_popcount(st[(size_t)b].dirty_mask); ++i) packed.push_back(spec[(size_t)(b * p->S + i)]);
   int64_t *hdr = static_cast<int64_t *>(host_buf);
   hdr[0] = nt; hdr[1] = nb; hdr[2] = (int64_t)packed.size(); hdr[3] = wpt;
   char *cur = reinterpret_cast<char *>(hdr + 4);
@@ -2439,11 +2960,11 @@ int sss_plan_debug_dump(sss_plan p, void *host_buf, size_t bytes) {
   cur += nt * (2 * sizeof(int32_t) + wpt * sizeof(uint32_t));
   if (!packed.empty()) std::memcpy(cur, packed.data(), packed.size() * sizeof(int4));
   cur += nt * 4 * sizeof(int32_t);
-  if (nb > 0) {
-    SSS_HIP(hipMemcpy(cur, p->sync_idx, nb * sizeof(int32_t), hipMemcpyDeviceToHost));
-    SSS_HIP(hipMemcpy(cur + nb * sizeof(int32_t), p->sync_val, nb * sizeof(double), hipMemcpyDeviceToHost));
-    SSS_HIP(hipMemcpy(cur + nb * (sizeof(int32_t) + sizeof(double)), p->tail_val, nb * sizeof(double),
-                      hipMemcpyDeviceToHost));
+  for (int64_t b = 0; b < nb; ++b) {
+    std::memcpy(cur + b * sizeof(int32_t), &st[(size_t)b].sync_idx, sizeof(int32_t));
+    std::memcpy(cur + nb * sizeof(int32_t) + b * sizeof(double), &st[(size_t)b].sync_val, sizeof(double));
+    std::memcpy(cur + nb * (sizeof(int32_t) + sizeof(double)) + b * sizeof(double), &st[(size_t)b].tail_val,
+                sizeof(double));
   }
   return SSS_OK;
 }

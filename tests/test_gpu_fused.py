@@ -1,0 +1,156 @@
+"""The one-launch execute (fused kernel) where it can go wrong: rows that
+cross a bunch boundary by 0 to 64 entries and by more, row spans around the
+64 and 128 row_ptr entries that a bunch loads ahead, more than 4,096 rows in
+a bunch, ragged ends, rows the plan did not know of, streamed and wide forms.
+
+Integer-valued inputs are exact against the oracle.  On other values the
+fused kernel must give the two stages' y (a debug plan runs them) bit for
+bit: it adds the same partial sums in the same order."""
+import numpy as np
+import pytest
+
+import csrgen
+import oracle
+from helpers import note, assert_exact, csr_from_lengths, to_dev_precision
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = ("f64", "f32", "bf16")
+
+
+def torch_types(kind):
+    import torch
+    return {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[kind], \
+        torch.float64 if kind == "f64" else torch.float32
+
+
+def patterns():
+    rng = csrgen.rng_for(7)
+    out = {f"rows_of_{L}": [L] * (6000 // L + 3) for L in (1, 2, 4, 63, 64, 65, 66, 130, 300)}
+    out["rows_of_5000"] = [5000, 3, 5000, 5000, 1]
+    out["around_64_rows"] = list(rng.integers(3, 6, 3000))
+    out["around_128_rows"] = list(rng.integers(1, 4, 4000))
+    out["empty_between"] = [x for v in rng.integers(0, 70, 300) for x in (int(v), 0)]
+    out["empty_runs"] = [9] * 40 + [0] * 70 + [3] * 100 + [0] * 5000 + [80] * 9 + [0] * 300
+    out["leading_empty"] = [0] * 3000 + [33] * 200
+    out["one_entry"] = [0, 0, 1, 0]
+    return {k: [int(v) for v in lens] for k, lens in out.items()}
+
+
+PATTERNS = patterns()
+
+
+def run(plan, rp, col, v, xx, m, ydt):
+    import torch
+    y = torch.full((m,), float("nan"), dtype=ydt, device="cuda")
+    return plan.execute(rp, col, v, xx, y).cpu()
+
+
+@pytest.mark.parametrize("kind", DTYPES)
+@pytest.mark.parametrize("name", sorted(PATTERNS))
+def test_fused_exact_and_same_bits(name, kind):
+    import torch
+    from paper_1504_06474_amd import sss
+    vt, yt = torch_types(kind)
+    note(f"[gpu-test] fused {name} {kind}")
+    A, x = csr_from_lengths(PATTERNS[name], 6000, seed=3)
+    U, ux = csr_from_lengths(PATTERNS[name], 6000, seed=3, int_valued=False)
+    want = oracle.spmv(A.row_ptr, A.col, A.val, x)
+    di, du = to_dev_precision(A, x, kind)[:4], to_dev_precision(U, ux, kind)[:4]
+    for W, S in ((4, 1), (4, 3), (8, 2), (16, 1)):
+        split = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=W, S=S, debug=True)
+        bits = run(split, *du, A.m, yt)
+        for bind in (True, False):
+            for d, check in ((di, False), (du, True)):
+                plan = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=W, S=S, row_ptr=d[0], bind_rows=bind)
+                y = run(plan, *d, A.m, yt)
+                if check:
+                    assert torch.equal(y, bits), (W, S, bind)
+                else:
+                    assert_exact(y.double().numpy(), want)
+    # the same matrix twice in a batch, beside one with no nonzero
+    ys = [torch.full((A.m,), float("nan"), dtype=yt, device="cuda") for _ in range(2)]
+    y0 = torch.full((70,), float("nan"), dtype=yt, device="cuda")
+    e = torch.empty(0, dtype=torch.int32, device="cuda")
+    mats = [(*di, ys[0], A.n), (torch.zeros(71, dtype=torch.int32, device="cuda"), e, e.to(vt), di[3], y0, A.n),
+            (*di, ys[1], A.n)]
+    for persistent in (False, True):
+        batch = sss.BatchPlan(mats, dtype=vt, persistent=persistent)
+        for y in ys + [y0]:
+            y.fill_(float("nan"))
+        batch.execute()
+        for y in ys:
+            assert_exact(y.double().cpu().numpy(), want)
+        assert y0.tolist() == [0.0] * 70
+
+
+@pytest.mark.parametrize("kind", DTYPES)
+def test_bound_plan_meets_long_rows_it_did_not_know(kind):
+    """Planned with rows of 8 (no carry launch), then row_ptr rewritten in
+    place with a row over many bunches, and with empty rows before it."""
+    import torch
+    from paper_1504_06474_amd import sss
+    vt, yt = torch_types(kind)
+    note(f"[gpu-test] fused rewritten {kind}")
+    A, x = csr_from_lengths([8] * 2000, 16000, seed=1)
+    rp, col, v, xx = to_dev_precision(A, x, kind)[:4]
+    plan = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=4, S=2, row_ptr=rp, bind_rows=True)
+    assert_exact(run(plan, rp, col, v, xx, A.m, yt).double().numpy(), oracle.spmv(A.row_ptr, A.col, A.val, x))
+    for lens in ([0] * 100 + [9000] + [0] * 100 + [100] * 60 + [1] * 739 + [261], [1] * 1000 + [0] * 900 + [150] * 100):
+        lens = np.array(lens + [0] * (A.m - len(lens)), dtype=np.int64)
+        assert lens.sum() == A.nnz and len(lens) == A.m
+        rp2 = np.zeros(A.m + 1, dtype=np.int32)
+        np.cumsum(lens, out=rp2[1:])
+        rp.copy_(torch.from_numpy(rp2).to("cuda"))
+        assert_exact(run(plan, rp, col, v, xx, A.m, yt).double().numpy(), oracle.spmv(rp2, A.col, A.val, x))
+
+
+def test_entries_past_the_end_add_nothing():
+    """The last tile's idle lanes read column 0: an infinite x[0] that no row
+    uses must not reach y."""
+    from paper_1504_06474_amd import sss
+    A, x = csr_from_lengths([3] * 101, 500, seed=2)
+    A.col[A.col == 0] = 1
+    x[0] = 0.0
+    want = oracle.spmv(A.row_ptr, A.col, A.val, x)
+    x[0] = np.inf
+    rp, col, v, xx = to_dev_precision(A, x, "f64")[:4]
+    import torch
+    for bind in (True, False):
+        plan = sss.Plan(A.m, A.n, A.nnz, row_ptr=rp, bind_rows=bind)
+        assert_exact(run(plan, rp, col, v, xx, A.m, torch.float64).numpy(), want)
+
+
+@pytest.mark.parametrize("kind", DTYPES)
+def test_streamed_form(kind):
+    """60 MB and more of columns and values: non-temporal loads."""
+    from paper_1504_06474_amd import sss
+    vt, yt = torch_types(kind)
+    rows = {"f64": 200_003, "f32": 300_007, "bf16": 400_003}[kind]
+    note(f"[gpu-test] fused streamed {kind}")
+    A, x = csr_from_lengths([27] * rows, 20_000, seed=4)
+    rp, col, v, xx = to_dev_precision(A, x, kind)[:4]
+    plan = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=8, S=2, row_ptr=rp, bind_rows=True)
+    assert_exact(run(plan, rp, col, v, xx, A.m, yt).double().numpy(), oracle.spmv(A.row_ptr, A.col, A.val, x))
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+def test_wide_x(kind):
+    """x of more than 4 GB: gathers past a 32-bit byte offset, single and batch."""
+    import torch
+    from paper_1504_06474_amd import sss
+    vt, yt = torch_types(kind)
+    n = {"f64": 540_000_011, "f32": 1_080_000_007}[kind]
+    note(f"[gpu-test] fused wide x {kind}")
+    A, x = csr_from_lengths([7] * 400 + [200] * 5, 5000, seed=6)
+    spread = (np.arange(5000, dtype=np.int64) * ((n - 1) // 4999)).astype(np.int32)
+    rp, col, v, xx = to_dev_precision(A, x, kind)[:4]
+    big = torch.zeros(n, dtype=yt, device="cuda")
+    big[torch.from_numpy(spread).to("cuda").long()] = xx
+    col = torch.from_numpy(spread).to("cuda")[col.long()].contiguous()
+    want = oracle.spmv(A.row_ptr, A.col, A.val, x)
+    plan = sss.Plan(A.m, n, A.nnz, dtype=vt, W=4, S=2, row_ptr=rp, bind_rows=True)
+    assert_exact(run(plan, rp, col, v, big, A.m, yt).double().numpy(), want)
+    y = torch.full((A.m,), float("nan"), dtype=yt, device="cuda")
+    sss.BatchPlan([(rp, col, v, big, y, n)], dtype=vt).execute()
+    assert_exact(y.double().cpu().numpy(), want)
