@@ -147,7 +147,10 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
 /* y = A x with a plan (both stages of Section 3.2, enqueued on `stream` as one
  * launch that does both stages' work per thread-bunch, and a second, short
  * one for rows that cross into a thread-bunch by more than 64 entries; a
- * bind_rows plan that has no such row leaves the second out.  Debug plans run
+ * bind_rows plan that has no such row leaves the second out; a plan without
+ * bind_rows for 32 million nonzeros or more and 2.5 MB or more of x launches
+ * three short kernels first, which sort the thread-bunches of long rows by
+ * column).  Debug plans run
  * the two stages as separate launches; y is the same bit for bit).
  * The sizes are the plan's; val/x/y types follow the plan's dtype.  m = 0 is a
  * no-op; nnz = 0 zeroes y.  SSS_ERR_INVALID_VALUE for a NULL plan, a NULL
@@ -240,14 +243,13 @@ typedef struct {
   int reserved;
 } sss_csr_desc;
 
-/* A batch plan: y_i = A_i x_i for `count` matrices in one launch per stage.
+/* A batch plan: y_i = A_i x_i for `count` matrices in one launch.
  * The thread-bunches of all matrices form one nnz-balanced index space
  * (Section 3.1's decomposition applied to the concatenation); the plan finds
  * each bunch's matrix with the same rightmost-match search the method uses
- * for rows (Section 3.2).  Stage 1 runs one wavefront per bunch, each XCD
+ * for rows (Section 3.2).  One wavefront runs each bunch, each XCD
  * taking a contiguous run of the bunch space (opts->batch_persistent: a
- * persistent grid instead); stage 2 is a persistent grid.  All matrices
- * share dtype and W; each may have its own S.
+ * persistent grid instead).  All matrices share dtype and W; each may have its own S.
  * FIXED mode (opts NULL or mode FIXED): W = opts->W (0: the type's default),
  * each matrix's S = its descriptor's S, else opts->S, else the default.
  * SELECTOR mode: the tile schedule comes from the loaded selector network

@@ -358,7 +358,7 @@ struct MatCtx {
   int32_t *stale;            // bound plans: set (and never cleared) when stage 1 finds a dirty tile in a
                              // bunch outside dirty_list (row_ptr rewritten in place since plan time)
   int32_t carries;       // fused kernel: a sss_carries launch follows and completes the long crossing rows
-  const int4 *slots;     // bound plans, per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
+  const int4 *slots;     // bound plans (and calls that made them), per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
                          // dirty_list), slot_need, 0>; NULL: slot = bunch
   int64_t n_slots;
   int32_t *dbg_start;    // debug plans only
@@ -826,12 +826,11 @@ enum Form { kCached, kStreamed, kWide };
 // rp[r0] the bunch needs, up to the first that is past its end (kSpanMax:
 // more than the two that each lane loads ahead).
 constexpr int kSpanMax = 2 * kWave;
+// r_next: the next bunch's first row, m after the last bunch.
 __device__ __forceinline__ int slot_need(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb, int32_t r,
                                          int32_t r_next) {
   const int back = r < m ? back_entries(rp[r], rp[r + 1], tb * SWT, SWT) : 0;
-  // r_next: the next bunch's first row, m after the last bunch
-  const int64_t span = imin64((int64_t)(r_next < m ? r_next + 1 : m) - r, kSpanMax);
-  return back | (int)span << 8;
+  return back | (int)imin64((int64_t)(r_next < m ? r_next + 1 : m) - r, kSpanMax) << 8;
 }
 
 // Buffer loads: the descriptor's range is in bytes, checked per 32-bit word.
@@ -1275,6 +1274,9 @@ __global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
 // workgroup b to XCD b mod 8, and every XCD has its own L2.
 constexpr int kXcds = 8;
 
+constexpr int kOrderBins = 256;  // column order: places in a row; bin kOrderBins holds the short rows
+constexpr int kOrderShare = 16;
+
 // Plan time: the first row of every thread-bunch, the rightmost match of its
 // first nonzero (Section 3.2's tile boundary search), one thread per bunch.
 __device__ __forceinline__ int32_t rightmost_row(const int32_t *__restrict__ rp, int32_t m, int64_t b) {
@@ -1310,6 +1312,57 @@ __global__ void sss_mark_dirty_bunches(const int32_t *__restrict__ rp, int32_t m
   }
 }
 
+// The place in its row, as a bin of the column order (below), of nonzero `at`
+// of row [p, q); kOrderBins where the row is short.
+__device__ __forceinline__ uint32_t order_bin(int64_t at, int64_t p, int64_t q, int64_t SWT) {
+  return q - p >= SWT && at >= p ? (uint32_t)imin64((at - p) * kOrderBins / (q - p), kOrderBins - 1)
+                                 : (uint32_t)kOrderBins;
+}
+
+// The same for one call of a plan that binds no rows, with the bunches' keys
+// for the column order: one thread per row writes the first row of the bunches
+// that begin in it and the keys of those whose middle lies in it (a wavefront
+// writes those of a row with many), one pass over row_ptr instead of a search
+// per bunch.  Clears the two lists of hist.
+constexpr int kFewBunches = 4;
+
+__global__ __launch_bounds__(256) void sss_call_rows(const int32_t *__restrict__ rp, int32_t m, int32_t nnz,
+                                                     int32_t SWT, uint32_t n_bunches, int32_t *__restrict__ rows,
+                                                     uint32_t *__restrict__ keys, uint32_t *__restrict__ hist) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t u = (uint32_t)SWT, half = u / 2;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < 2 * (kOrderBins + 1); i += blockDim.x) hist[i] = 0u;
+    // (a last bunch that ends before its middle)
+    if (threadIdx.x == 0 && (n_bunches - 1) * u + half >= (uint32_t)nnz) keys[n_bunches - 1] = kOrderBins;
+  }
+  for (int64_t r0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; r0 < m;
+       r0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t r = r0 + lane;
+    const uint32_t p = r < m ? (uint32_t)rp[r] : 0u, q = r < m ? (uint32_t)rp[r + 1] : 0u;
+    // bunches k0 .. k1-1 begin in [p, q); m0 .. m1-1 have their middle there
+    // (the minima hold in every valid matrix)
+    const uint32_t k0 = (p + u - 1u) / u, m0 = (max(p, half) - half + u - 1u) / u;
+    const uint32_t k1 = q > p ? min((q + u - 1u) / u, n_bunches) : k0;
+    const uint32_t m1 = q > p ? min((max(q, half) - half + u - 1u) / u, n_bunches) : m0;
+    const bool many = k1 > k0 + kFewBunches;
+    if (!many) {
+      for (uint32_t k = k0; k < k1; ++k) rows[k] = (int32_t)r;
+      for (uint32_t k = m0; k < m1; ++k) keys[k] = order_bin((int64_t)k * u + half, p, q, SWT);
+    }
+    uint64_t todo = __ballot(many);
+    while (todo) {
+      const int l = __ffsll((unsigned long long)todo) - 1;
+      todo &= todo - 1;
+      const uint32_t pl = (uint32_t)lane_value((int)p, l), ql = (uint32_t)lane_value((int)q, l);
+      const uint32_t end = (uint32_t)lane_value((int)k1, l), mend = (uint32_t)lane_value((int)m1, l);
+      for (uint32_t k = (uint32_t)lane_value((int)k0, l) + lane; k < end; k += kWave) rows[k] = (int32_t)(r0 + l);
+      for (uint32_t k = (uint32_t)lane_value((int)m0, l) + lane; k < mend; k += kWave)
+        keys[k] = order_bin((int64_t)k * u + half, pl, ql, SWT);
+    }
+  }
+}
+
 // Stage 1's column order.  A bunch inside a long row reads a narrow slice of
 // the columns (a row's columns ascend), so such bunches are sorted by their
 // place in their row and dealt to the XCDs in eight equal runs: each XCD's L2
@@ -1324,8 +1377,9 @@ __global__ void sss_mark_dirty_bunches(const int32_t *__restrict__ rp, int32_t m
 // at least SWT of them.  SWT / 2 and SWT / 4 measured 2% faster on the first
 // matrix (179 us) and 2 to 5% slower on the second (848 us), whose bunches
 // are twice as long; 2 SWT and 4 SWT 2 to 10% slower on both.
-constexpr int kOrderBins = 256;  // places in a row; bin kOrderBins: short rows
-
+//
+// FIND: find the keys, else they are there (the lists of one call).
+template <bool FIND>
 __global__ __launch_bounds__(256) void sss_order_keys(const int32_t *__restrict__ rp, int32_t m, int32_t nnz,
                                                       int64_t SWT, int64_t n_bunches,
                                                       const int32_t *__restrict__ bunch_row,
@@ -1335,21 +1389,22 @@ __global__ __launch_bounds__(256) void sss_order_keys(const int32_t *__restrict_
   __syncthreads();
   const int64_t tb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (tb < n_bunches) {
-    const int32_t mid = (int32_t)imin64(tb * SWT + SWT / 2, (int64_t)nnz - 1);
-    // the row of nonzero mid, between the first rows of this bunch and the next
-    int32_t lo = bunch_row[tb] & 0x7fffffff;
-    int32_t hi = tb + 1 < n_bunches ? bunch_row[tb + 1] & 0x7fffffff : m;
-    while (lo < hi) {
-      const int32_t c = lo + (hi - lo + 1) / 2;
-      if (rp[c] <= mid) lo = c;
-      else hi = c - 1;
+    uint32_t key;
+    if constexpr (FIND) {
+      const int32_t mid = (int32_t)imin64(tb * SWT + SWT / 2, (int64_t)nnz - 1);
+      // the row of nonzero mid, between the first rows of this bunch and the next
+      int32_t lo = bunch_row[tb] & 0x7fffffff;
+      int32_t hi = tb + 1 < n_bunches ? bunch_row[tb + 1] & 0x7fffffff : m;
+      while (lo < hi) {
+        const int32_t c = lo + (hi - lo + 1) / 2;
+        if (rp[c] <= mid) lo = c;
+        else hi = c - 1;
+      }
+      key = order_bin(mid, rp[lo], lo < m ? rp[lo + 1] : nnz, SWT);
+      keys[tb] = key;
+    } else {
+      key = min(keys[tb], (uint32_t)kOrderBins);
     }
-    const int32_t p = rp[lo];
-    const int64_t len = (lo < m ? (int64_t)rp[lo + 1] : (int64_t)nnz) - p;
-    const int64_t at = (int64_t)(mid - p);
-    const uint32_t key = len >= SWT && at >= 0 ? (uint32_t)imin64(at * kOrderBins / len, kOrderBins - 1)
-                                            : (uint32_t)kOrderBins;
-    keys[tb] = key;
     atomicAdd(&count[key], 1u);
   }
   __syncthreads();
@@ -1377,7 +1432,8 @@ __global__ __launch_bounds__(256) void sss_slots(const int32_t *__restrict__ rp,
   if (tb < n_bunches) slots[tb] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row);
 }
 
-// Slots in column order.  hist: the bunches per bin; cursor: zeros.  Within a bin the order is that
+// Slots in column order; in bunch order where fewer than one bunch in
+// kOrderShare is long.  hist: the bunches per bin; cursor: zeros.  Within a bin the order is that
 // of the atomics, which decides only when a bunch runs.
 __global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restrict__ rp, int32_t m, int64_t SWT,
                                                          int64_t n_bunches, const int32_t *__restrict__ bunch_row,
@@ -1399,9 +1455,14 @@ __global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restri
   }
   const int64_t n_long = first[kOrderBins - 1];
   const int64_t tb = (int64_t)blockIdx.x * blockDim.x + t;
+  if (n_long * kOrderShare < n_bunches) {
+    if (tb < n_slots)
+      slots[tb] = tb < n_bunches ? slot_entry(rp, m, SWT, tb, n_bunches, bunch_row) : make_int4(-1, 0, 0, 0);
+    return;
+  }
   uint32_t key = 0, mine = 0;
   if (tb < n_bunches) {
-    key = keys[tb];
+    key = min(keys[tb], (uint32_t)kOrderBins);
     mine = atomicAdd(&count[key], 1u);
   }
   __syncthreads();
@@ -1929,6 +1990,7 @@ struct sss_plan_s {
   int32_t carries = 1;           // 0: no long crossing row at plan time (see sss_fused), so no second launch
   int4 *slots = nullptr;         // bind_rows plans: see MatCtx::slots
   uint32_t *order_hist = nullptr;
+  bool call_order = false;       // plans without bind_rows: every call makes bunch_row and slots, see orders_calls
   int64_t n_slots = 0;
   int32_t *dbg_start = nullptr;
   int32_t *dbg_dirty = nullptr;
@@ -1959,7 +2021,7 @@ struct AuxLayout {
   size_t total = 0;
 };
 
-AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug) {
+AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug, bool call_order) {
   AuxLayout L;
   const int WT = W * kWave;
   L.n_tiles = nnz > 0 ? (nnz + WT - 1) / WT : 0;
@@ -1971,10 +2033,12 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug) {
   // sss_csr_spmv_noalloc is stated for)
   L.state = off; off += 2 * align256(sizeof(int32_t) * (nb + 1)) + 2 * align256(sizeof(double) * (nb + 1));
   L.spec = off; off = align256(off + sizeof(int4) * (nb * (size_t)S + 1));
-  if (bind) {
+  if (bind || call_order) {
     L.brow = off; off = align256(off + sizeof(int32_t) * (nb + 1));
     L.dlist = off; off = align256(off + sizeof(int32_t) * (nb + 1));
     L.stale = off; off = align256(off + sizeof(int32_t) * 2);
+  }
+  if (bind || call_order) {
     L.slots = off; off = align256(off + sizeof(int4) * (nb + kXcds * kMaxB));
     L.ohist = off; off = align256(off + sizeof(uint32_t) * 2 * (kOrderBins + 1));
   }
@@ -1995,12 +2059,13 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
   p->aux = base_v;
   p->state = reinterpret_cast<BunchState *>(base + L.state);
   p->speculator = reinterpret_cast<int4 *>(base + L.spec);
-  p->bunch_row = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
+  p->bunch_row = p->bind_rows || p->call_order ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
   p->dirty_list = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.dlist) : nullptr;
   p->stale = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.stale) : nullptr;
   p->carries = L.n_bunches > 1 ? 1 : 0;
-  p->slots = p->bind_rows ? reinterpret_cast<int4 *>(base + L.slots) : nullptr;
-  p->order_hist = p->bind_rows ? reinterpret_cast<uint32_t *>(base + L.ohist) : nullptr;
+  const bool slots = p->bind_rows || p->call_order;
+  p->slots = slots ? reinterpret_cast<int4 *>(base + L.slots) : nullptr;
+  p->order_hist = slots ? reinterpret_cast<uint32_t *>(base + L.ohist) : nullptr;
   p->dbg_start = p->debug ? reinterpret_cast<int32_t *>(base + L.dstart) : nullptr;
   p->dbg_dirty = p->debug ? reinterpret_cast<int32_t *>(base + L.ddirty) : nullptr;
   p->dbg_heads = p->debug ? reinterpret_cast<uint32_t *>(base + L.dheads) : nullptr;
@@ -2010,7 +2075,7 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
 // allocated), else one hipMalloc owned by the plan.  Cleared on `stream`
 // (stream-ordered; the caller of plan_create synchronises that stream).
 int plan_alloc(sss_plan p, void *workspace, size_t workspace_bytes, hipStream_t stream) {
-  const AuxLayout L = aux_layout(p->nnz, p->W, p->S, p->bind_rows != 0, p->debug != 0);
+  const AuxLayout L = aux_layout(p->nnz, p->W, p->S, p->bind_rows != 0, p->debug != 0, p->call_order);
   void *base = workspace;
   if (workspace) {
     if (workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return SSS_ERR_INVALID_VALUE;
@@ -2064,15 +2129,58 @@ MatCtx plan_ctx(sss_plan p, const int32_t *row_ptr, const int32_t *col, const vo
   a.m = (int32_t)p->m; a.nnz = (int32_t)p->nnz; a.S = p->S; a.W = p->W;
   a.n_bunches = p->n_bunches; a.n_tiles = p->n_tiles;
   a.state = p->state; a.speculator = p->speculator;
-  a.bunch_row = p->bunch_row;
+  a.bunch_row = p->bind_rows ? p->bunch_row : nullptr;
   a.dirty_list = p->dirty_list;
   a.n_fix = p->dirty_list ? p->n_listed : p->n_bunches;
   a.stale = p->stale;
   a.carries = p->carries;
-  a.slots = p->slots;
+  a.slots = p->bind_rows ? p->slots : nullptr;
   a.n_slots = p->n_slots;
   a.dbg_start = p->dbg_start; a.dbg_dirty = p->dbg_dirty; a.dbg_heads = p->dbg_heads;
   return a;
+}
+
+// Stage 1's column order (see sss_order_keys) can gain where x is larger than
+// what stays in an XCD's 4 MB L2 beside the streamed matrix (power law, Zipf
+// and dense rows: 2.16 MB of x 1% slower to 1% faster, 2.8 MB 1 to 3%, 3.2 MB
+// 2 to 4%, 4 MB 6 to 9%, 8 MB 9 to 22% faster).
+constexpr int64_t kOrderMinX = int64_t(5) << 19;
+constexpr int64_t kOrderMinBunches = 2048;
+
+// Whether the calls of a plan without bind_rows make the slots in column order
+// themselves, three short launches before the fused kernel.  us per product
+// without / with: 4M-row Zipf 1.8 FP32 (80M nonzeros) 1,095 / 818, 2M-row
+// power law FP64 (40M) 569 / 465, 1M rows of it (20M) 213 / 189; where no row
+// is long they only cost, 8 us beside a short kernel: 5-point stencils 42 /
+// 51 (10M) and 97 / 107 (24M), 27-point stencils 59 / 65 (19M) and 128 / 130
+// (46M), a FEM band 125 / 126 (50M).
+constexpr int64_t kCallOrderNnz = 32000000;
+bool orders_calls(int64_t nnz, int64_t n, int dt) {
+  return nnz >= kCallOrderNnz && n * (int64_t)y_size(dt) >= kOrderMinX;
+}
+
+int64_t slots_of(sss_plan p) {
+  const int64_t group = (int64_t)kXcds * p->B;
+  return (p->n_bunches + group - 1) / group * group;
+}
+
+int launch_call_order(sss_plan p, const int32_t *row_ptr, MatCtx &a, hipStream_t s) {
+  const int64_t nb = p->n_bunches, n_slots = slots_of(p);
+  const int32_t m = (int32_t)p->m, SWT = p->S * p->W * kWave;
+  const unsigned row_blocks = (unsigned)std::min<int64_t>((p->m + 255) / 256, 8192);
+  uint32_t *keys = reinterpret_cast<uint32_t *>(p->speculator), *hist = p->order_hist;
+  hipLaunchKernelGGL(sss_call_rows, dim3(row_blocks), dim3(256), 0, s, row_ptr, m,
+                     (int32_t)p->nnz, SWT, (uint32_t)nb, p->bunch_row, keys, hist);
+  SSS_HIP(hipGetLastError());
+  hipLaunchKernelGGL(sss_order_keys<false>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, row_ptr, m,
+                     (int32_t)p->nnz, (int64_t)SWT, nb, p->bunch_row, keys, hist);
+  SSS_HIP(hipGetLastError());
+  hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, row_ptr, m,
+                     (int64_t)SWT, nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
+  SSS_HIP(hipGetLastError());
+  a.slots = p->slots;
+  a.n_slots = n_slots;
+  return SSS_OK;
 }
 
 // Stage 1 alone (`split`), or the fused kernel.  (nnz = 0: y is zeroed here.)
@@ -2091,8 +2199,12 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
   Stage1Fn k1 = split ? SSS_PICK(pick_stage1, p->dt, p->W, p->debug != 0)
                       : SSS_PICK(pick_fused, p->dt, p->W, form_of(p->nnz, p->n, p->dt));
   if (!k1) return SSS_ERR_UNSUPPORTED;
-  const MatCtx a1 = plan_ctx(p, row_ptr, col, val, x, y);
-  const int64_t blocks1 = ((p->slots ? p->n_slots : p->n_bunches) + p->B - 1) / p->B;
+  MatCtx a1 = plan_ctx(p, row_ptr, col, val, x, y);
+  if (!split && p->call_order) {
+    const int rc = launch_call_order(p, row_ptr, a1, stream);
+    if (rc != SSS_OK) return rc;
+  }
+  const int64_t blocks1 = ((a1.slots ? a1.n_slots : p->n_bunches) + p->B - 1) / p->B;
   const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
   hipLaunchKernelGGL(k1, dim3((unsigned)blocks1), dim3(p->B * kWave), lds1, stream, a1);
   SSS_HIP(hipGetLastError());
@@ -2282,20 +2394,21 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
   if (opts) o = *opts;
   if (o.mode != SSS_MODE_FIXED && o.mode != SSS_MODE_SELECTOR) return SSS_ERR_UNSUPPORTED;
   const bool bind = o.bind_rows && m > 0 && nnz > 0, dbg = o.debug != 0;
+  const bool order = !bind && !dbg && orders_calls(nnz, n, dt);
   size_t need = 0;
   if (o.mode == SSS_MODE_FIXED) {
     const int W = o.W ? o.W : default_W(dt), S = o.S ? o.S : default_S(dt);
     if (!(W == 4 || W == 8 || W == 16)) return SSS_ERR_UNSUPPORTED;
     if (S < 1 || S > kMaxS) return SSS_ERR_INVALID_VALUE;
-    need = aux_layout(nnz, W, S, bind, dbg).total;
+    need = aux_layout(nnz, W, S, bind, dbg, order).total;
   } else {
     // the selector's choice is not known yet: the largest of the grid's
     // classes and the type's defaults
-    need = aux_layout(nnz, default_W(dt), default_S(dt), bind, dbg).total;
+    need = aux_layout(nnz, default_W(dt), default_S(dt), bind, dbg, order).total;
     for (int c = 0; c < SSS_N_CLASSES; ++c) {
       int W = 0, S = 0;
       (void)sss_class_params(c, &W, &S);
-      need = std::max(need, aux_layout(nnz, W, S, bind, dbg).total);
+      need = std::max(need, aux_layout(nnz, W, S, bind, dbg, order).total);
     }
   }
   *bytes = need;
@@ -2304,31 +2417,24 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
 
 namespace {
 
-// Bound plans: stage 1's slots, in column order (see sss_order_keys) where it
-// can gain: x must be larger than what stays in an XCD's 4 MB L2 beside the
-// streamed matrix (power law, Zipf and dense rows: 2.16 MB of x 1% slower to
-// 1% faster, 2.8 MB 1 to 3%, 3.2 MB 2 to 4%, 4 MB 6 to 9%, 8 MB 9 to 22%
-// faster), and enough bunches must lie in long rows.  The order is made on
-// the device; the host reads back only how many bunches are short.  The
-// speculator's space holds the keys (stage 1 writes every entry that stage 2
-// reads).
-constexpr int64_t kOrderMinX = int64_t(5) << 19;
-constexpr int64_t kOrderMinBunches = 2048;
-
+// Bound plans: stage 1's slots, in column order where that can gain and
+// enough bunches lie in long rows.  The order is made on the device; the host
+// reads back only how many bunches are short.  The speculator's space holds
+// the keys (stage 1 writes every entry that stage 2 reads).
 int plan_slots(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t s) {
   const int64_t nb = p->n_bunches, x_bytes = p->n * (int64_t)y_size(p->dt);
   const unsigned blocks = (unsigned)((nb + 255) / 256);
   const int32_t m = (int32_t)p->m;
   if (x_bytes >= kOrderMinX && nb >= kOrderMinBunches) {
-    const int64_t group = (int64_t)kXcds * p->B, n_slots = (nb + group - 1) / group * group;
+    const int64_t n_slots = slots_of(p);
     uint32_t *keys = reinterpret_cast<uint32_t *>(p->speculator), *hist = p->order_hist;
-    hipLaunchKernelGGL(sss_order_keys, dim3(blocks), dim3(256), 0, s, row_ptr, m, (int32_t)p->nnz, SWT, nb,
+    hipLaunchKernelGGL(sss_order_keys<true>, dim3(blocks), dim3(256), 0, s, row_ptr, m, (int32_t)p->nnz, SWT, nb,
                        p->bunch_row, keys, hist);
     SSS_HIP(hipGetLastError());
     uint32_t n_short = 0;
     SSS_HIP(hipMemcpyAsync(&n_short, hist + kOrderBins, sizeof(n_short), hipMemcpyDeviceToHost, s));
     SSS_HIP(hipStreamSynchronize(s));
-    if ((nb - (int64_t)n_short) * 16 >= nb) {
+    if ((nb - (int64_t)n_short) * kOrderShare >= nb) {
       hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, row_ptr, m, SWT,
                          nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
       SSS_HIP(hipGetLastError());
@@ -2404,6 +2510,7 @@ int sss_csr_spmv_plan_create(int64_t m, int64_t n, int64_t nnz, const int32_t *r
   p->m = m; p->n = n; p->nnz = nnz; p->dt = dt; p->W = W; p->S = S; p->B = B; p->debug = o.debug ? 1 : 0;
   p->bind_rows = (o.bind_rows && m > 0 && nnz > 0) ? 1 : 0;
   p->bound_row_ptr = p->bind_rows ? row_ptr : nullptr;
+  p->call_order = !p->bind_rows && !p->debug && orders_calls(nnz, n, dt);
   hipStream_t s = static_cast<hipStream_t>(stream);
   int rc = SSS_OK;
   hipError_t e = hipGetDevice(&p->device);
@@ -2518,7 +2625,14 @@ int sss_csr_spmv_noalloc(int64_t m, int64_t n, int64_t nnz, const int32_t *row_p
   if (m < 0 || n < 0 || nnz < 0 || m > SSS_MAX_INDEX || n > SSS_MAX_INDEX || nnz > SSS_MAX_INDEX)
     return SSS_ERR_INVALID_VALUE;
   if (m == 0) return SSS_OK;
-  const AuxLayout L = aux_layout(nnz, default_W(SSS_F64), default_S(SSS_F64), false, false);
+  const int W = default_W(SSS_F64), S = default_S(SSS_F64);
+  // column order where the scratch holds its lists too
+  bool order = orders_calls(nnz, n, SSS_F64);
+  AuxLayout L = aux_layout(nnz, W, S, false, false, order);
+  if (order && L.total > kScratchBytes) {
+    order = false;
+    L = aux_layout(nnz, W, S, false, false, order);
+  }
   if (L.total > kScratchBytes) return SSS_ERR_TOO_LARGE;
   int dev = -1;
   SSS_HIP(hipGetDevice(&dev));
@@ -2536,7 +2650,7 @@ int sss_csr_spmv_noalloc(int64_t m, int64_t n, int64_t nnz, const int32_t *row_p
   sss_plan_s p;
   p.device = dev;
   p.m = m; p.n = n; p.nnz = nnz; p.dt = SSS_F64;
-  p.W = default_W(SSS_F64); p.S = default_S(SSS_F64); p.B = kDefaultB;
+  p.W = W; p.S = S; p.B = kDefaultB; p.call_order = order;
   plan_bind_aux(&p, L, base);
   return launch(&p, row_ptr, col, val, x, y, static_cast<hipStream_t>(stream));
 }

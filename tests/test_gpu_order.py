@@ -39,3 +39,55 @@ def test_column_order_exact(name, B):
             y = torch.full((A.m,), float("nan"), dtype=torch.float64, device="cuda")
             plan.execute(rp, col, v, xx, y)
             assert_exact(y.cpu().numpy(), want)
+
+
+def _strided_csr(lengths, n, seed):
+    """Entry j of a row of length L in column j n / L: sorted and distinct."""
+    import csrgen
+    rng = csrgen.rng_for(seed)
+    rp = np.zeros(len(lengths) + 1, dtype=np.int64)
+    np.cumsum(lengths, out=rp[1:])
+    each = np.repeat(lengths, lengths)
+    j = np.arange(rp[-1]) - np.repeat(rp[:-1], lengths)
+    val = rng.integers(-3, 4, rp[-1]).astype(np.float64)
+    return csrgen.CSR(len(lengths), n, rp.astype(np.int32), (j * n // each).astype(np.int32), val), \
+        rng.integers(-3, 4, n).astype(np.float64)
+
+
+def test_column_order_per_call_exact():
+    """Plans without bind_rows from 32M nonzeros on: every call orders the
+    bunches of the row_ptr it is given (two structures on one plan, calls
+    replayed from a graph, the one-call forms)."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note("[gpu-test] column order per call")
+    rng = np.random.default_rng(5)
+    lens = np.concatenate([[N, N - 1, 150_000], np.full(900, 9000), np.zeros(5000, int), rng.integers(1, 60, 760_000)])
+    lens = np.append(lens.astype(np.int64), 0)
+    lens[-1] = 32_000_001 - lens.sum() if lens.sum() < 32_000_001 else 1
+    assert lens.max() <= N and lens.sum() >= 32_000_000
+    A, x = _strided_csr(rng.permutation(lens), N, 1)
+    A2, _ = _strided_csr(np.sort(lens), N, 2)
+    d, d2 = to_dev(A, x), to_dev(A2, x)
+    want, want2 = oracle.spmv(A.row_ptr, A.col, A.val, x), oracle.spmv(A2.row_ptr, A2.col, A2.val, x)
+    y = torch.full((A.m,), float("nan"), dtype=torch.float64, device="cuda")
+    for W, S, B in ((8, 5, 2), (4, 2, 3), (16, 1, 1)):
+        plan = sss.Plan(A.m, A.n, A.nnz, W=W, S=S, B=B)
+        for args, expect in ((d, want), (d2, want2), (d, want)):
+            y.fill_(float("nan"))
+            plan.execute(*args, y)
+            assert_exact(y.cpu().numpy(), expect)
+    plan = sss.Plan(A.m, A.n, A.nnz)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.execute(*d, y)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        g.replay()
+        assert_exact(y.cpu().numpy(), want)
+    for call in (sss.csr_spmv, sss.csr_spmv_noalloc):
+        for args, expect in ((d2, want2), (d, want)):
+            y.fill_(float("nan"))
+            call(*args, y)
+            assert_exact(y.cpu().numpy(), expect)
+    sss.csr_spmv_cache_clear()
