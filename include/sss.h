@@ -193,8 +193,9 @@ int sss_csr_spmv_stage2(sss_plan p, const int32_t *row_ptr, void *y, void *strea
  * device stage 2 is the product path. */
 int sss_csr_spmv_stage2_host(sss_plan p, const int32_t *row_ptr, void *y);
 
-/* The one-call form of the method in double precision: y = A x with the
- * default parameters.  Keeps an internal plan per (device, stream, m, n, nnz)
+/* The one-call form of the method in double precision: y = A x with a tile
+ * schedule picked from nnz (W = 4, S = 1 below 500,000 nonzeros, then W = 8
+ * with S = 1, 2 and, from 8 million on, the default 5).  Keeps an internal plan per (device, stream, m, n, nnz)
  * that it allocates on first use (so the first call for a new size on a
  * stream is not graph-capturable; later calls are) and keeps until the
  * process ends or sss_csr_spmv_cache_clear.  Calls on one stream run in
@@ -206,7 +207,7 @@ int sss_csr_spmv(int64_t m, int64_t n, int64_t nnz, const int32_t *row_ptr,
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * product as sss_csr_spmv (double precision, the default parameters, the same
+ * product as sss_csr_spmv (double precision, the same tile schedule, the same
  * kernels, so the same y bit for bit) with the plan's auxiliary arrays in a
  * static device array of 16 MiB that the library holds on each device until
  * the process ends, instead of a cached plan.  Allocates nothing and never

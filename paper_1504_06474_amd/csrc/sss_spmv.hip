@@ -2270,6 +2270,19 @@ int launch_batch(sss_plan p, hipStream_t stream) {
   return SSS_OK;
 }
 
+// The tile schedule of the one-call forms, which keep no plan of the
+// caller's.  The paper's S = 5 leaves a GPU of 256 CUs idle on all but large
+// matrices (a 317^2 5-point stencil ran on 196 wavefronts, 17.4 us against
+// 7.8 with W = 4, S = 1); each line is where the next schedule's geometric
+// mean over stencils, a FEM band, Poisson, web-like, power-law and dense-row
+// matrices takes over: 352K nonzeros W = 4 S = 1 7% ahead of W = 8 S = 1,
+// 0.9 to 1M 4% behind it; 3.5 to 6M W = 8 S = 2 6% ahead of that; 10 to 20M
+// W = 8 S = 5 13% ahead of S = 2.
+void one_call_params(int64_t nnz, int *W, int *S) {
+  *W = nnz < 500000 ? 4 : 8;
+  *S = nnz < 2000000 ? 1 : (nnz < 8000000 ? 2 : 5);
+}
+
 std::mutex g_cache_mu;
 std::map<std::tuple<int, void *, int64_t, int64_t, int64_t>, sss_plan> g_cache;
 
@@ -2281,8 +2294,8 @@ constexpr int kMaxDevices = 64;
 std::mutex g_validate_mu;
 int *g_validate_ptr[kMaxDevices] = {};
 
-// sss_csr_spmv_noalloc's plan arrays (dirty masks, speculator, synchronizer,
-// tails of a default double-precision plan): a static array in the code
+// sss_csr_spmv_noalloc's plan arrays (what a double-precision plan of its
+// schedule holds): a static array in the code
 // object, one per device, held until the process ends.  Host code never uses
 // its name as an address: the device address comes from hipGetSymbolAddress,
 // once per device.  Every call on a device shares it; stage 1 writes every
@@ -2612,7 +2625,10 @@ int sss_csr_spmv(int64_t m, int64_t n, int64_t nnz, const int32_t *row_ptr, cons
     if (it != g_cache.end()) {
       p = it->second;
     } else {
-      const int rc = sss_csr_spmv_plan_create(m, n, nnz, row_ptr, SSS_F64, nullptr, stream, &p);
+      sss_plan_opts o{};
+      o.mode = SSS_MODE_FIXED;
+      one_call_params(nnz, &o.W, &o.S);
+      const int rc = sss_csr_spmv_plan_create(m, n, nnz, row_ptr, SSS_F64, &o, stream, &p);
       if (rc != SSS_OK) return rc;
       g_cache[key] = p;
     }
@@ -2625,7 +2641,8 @@ int sss_csr_spmv_noalloc(int64_t m, int64_t n, int64_t nnz, const int32_t *row_p
   if (m < 0 || n < 0 || nnz < 0 || m > SSS_MAX_INDEX || n > SSS_MAX_INDEX || nnz > SSS_MAX_INDEX)
     return SSS_ERR_INVALID_VALUE;
   if (m == 0) return SSS_OK;
-  const int W = default_W(SSS_F64), S = default_S(SSS_F64);
+  int W = 0, S = 0;
+  one_call_params(nnz, &W, &S);
   // column order where the scratch holds its lists too
   bool order = orders_calls(nnz, n, SSS_F64);
   AuxLayout L = aux_layout(nnz, W, S, false, false, order);
