@@ -50,9 +50,8 @@
 //    launch; per-bunch slots need neither, and stage 2's wavefront for a bunch
 //    finds that bunch's dirty tiles directly.
 //
-// Precision: F64 sums in double.  F32/BF16 multiply in float and sum segments
-// with TwoSum-compensated float pairs; each partial is formed in double, the
-// transmitter, the synchronizer and the stage-2 carry sums are double.
+// Precision: F32/BF16 multiply in float; every sum is in double: the segments',
+// the partials, the transmitter, the synchronizer and the stage-2 carry sums are double.
 
 #include <hip/hip_runtime.h>
 
@@ -122,8 +121,14 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) {
   return __uint_as_float(bits16 << 16);
 }
 
-// Accumulators.  F64: one double.  F32/BF16: an unevaluated float pair
-// (hi, lo) kept by TwoSum (Knuth), i.e. compensated summation.
+// The segment sums of every type are doubles.  F32 and BF16 round each product
+// to float once and add the products in double: a float pair kept by TwoSum
+// has at most the same accuracy, takes seven float additions per entry where
+// this takes a conversion and one double addition (which issues at the same
+// rate), and eleven per scan step where this takes one.  It had made those
+// types issue 2.4 times FP64's vector instructions on the same tiles (FEM band
+// 778K x 50, W = 8, S = 2: 1,595 per wavefront against 661 on the 27-point
+// stencil).
 struct AccD {
   double s;
   __device__ __forceinline__ void zero() { s = 0.0; }
@@ -131,44 +136,7 @@ struct AccD {
   // this := earlier (+) this
   __device__ __forceinline__ void prepend(const AccD &earlier) { s = earlier.s + s; }
   __device__ __forceinline__ double value() const { return s; }
-  __device__ __forceinline__ AccD shfl_up(unsigned d) const { AccD r; r.s = __shfl_up(s, d, kWave); return r; }
 };
-
-__device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
-  s = a + b;
-  const float z = s - a;
-  e = (a - (s - z)) + (b - z);
-}
-
-struct AccC {
-  float hi, lo;
-  __device__ __forceinline__ void zero() { hi = 0.f; lo = 0.f; }
-  __device__ __forceinline__ void add(float v) {
-    float s, e;
-    two_sum(hi, v, s, e);
-    hi = s;
-    lo += e;
-  }
-  // this := earlier (+) this, as a float pair
-  __device__ __forceinline__ void prepend(const AccC &earlier) {
-    float s, e;
-    two_sum(earlier.hi, hi, s, e);
-    e += earlier.lo + lo;
-    hi = s + e;  // renormalise (fast two-sum; |s| >= |e| up to rounding)
-    lo = e - (hi - s);
-  }
-  __device__ __forceinline__ double value() const { return (double)hi + (double)lo; }
-  __device__ __forceinline__ AccC shfl_up(unsigned d) const {
-    AccC r;
-    r.hi = __shfl_up(hi, d, kWave);
-    r.lo = __shfl_up(lo, d, kWave);
-    return r;
-  }
-};
-
-template <int DT> struct AccSel { using type = AccC; };
-template <> struct AccSel<SSS_F64> { using type = AccD; };
-template <int DT> using Acc = typename AccSel<DT>::type;
 
 // ---------------------------------------------------------------- loads
 
@@ -252,10 +220,6 @@ __device__ __forceinline__ int dpp_i(int v) {
   return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, true);
 }
 template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(dpp_i<CTRL, ROWS>(__float_as_int(v)));
-}
-template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_d(double v) {
   const long long b = __double_as_longlong(v);
   const int lo = dpp_i<CTRL, ROWS>((int)(unsigned long long)b);
@@ -264,13 +228,6 @@ __device__ __forceinline__ double dpp_d(double v) {
 }
 template <int CTRL, int ROWS>
 __device__ __forceinline__ AccD dpp_acc(const AccD &v) { AccD r; r.s = dpp_d<CTRL, ROWS>(v.s); return r; }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ AccC dpp_acc(const AccC &v) {
-  AccC r;
-  r.hi = dpp_f<CTRL, ROWS>(v.hi);
-  r.lo = dpp_f<CTRL, ROWS>(v.lo);
-  return r;
-}
 
 // one step of the segmented scan: (v, f) := (v_src, f_src) (+) (v, f), where
 // (a, fa) (+) (b, fb) = (fb ? b : a + b, fa | fb)
@@ -667,7 +624,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     // too (q - 1 = rank0 - 1, or 0 for the tile's first entry); the segment's
     // full sum overwrites it after the wave scan.  The transmitter is added
     // to the tile's first partial where that partial is read.
-    Acc<DT> acc, pre;
+    AccD acc, pre;
     acc.zero();
     pre.zero();
     bool seen = false;
@@ -686,21 +643,21 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     if (!seen) pre = acc;
     // ---- wave segmented scan of the open segments (the lane's running
     // sum: its run after the last head, or all of it); carry into each lane
-    Acc<DT> inc = acc;
+    AccD inc = acc;
     int f = seen ? 1 : 0;
     wave_seg_scan(inc, f);
-    const Acc<DT> carry = dpp_acc<kWaveShr1, 0xf>(inc);
+    const AccD carry = dpp_acc<kWaveShr1, 0xf>(inc);
 
     // ---- the segment closed by this lane's first head: carry + pre; the
     // segment open at the tile's end (last lane): its run, or carry + pre
     // when the last lane holds no head
     if (seen && rank0 > 0) {
-      Acc<DT> c = pre;
+      AccD c = pre;
       c.prepend(carry);
       part[rank0 - 1] = c.value();
     }
     if (lane == kWave - 1) {
-      Acc<DT> c = pre;
+      AccD c = pre;
       c.prepend(carry);
       part[cnt - 1] = seen ? acc.value() : c.value();
     }
@@ -914,7 +871,7 @@ __device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, doubl
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
   constexpr int kFirst = kWave - kBack / W;  // the first lane whose entries are among the last kBack
-  Acc<DT> acc;
+  AccD acc;
   acc.zero();
   if (lane >= kFirst) {
 #pragma unroll
@@ -923,11 +880,11 @@ __device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, doubl
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const int head = kFirst + (rs - (b0 - kBack)) / W;
-  Acc<DT> inc = acc;
+  AccD inc = acc;
   int f = lane == head ? 1 : 0;
   wave_seg_scan(inc, f);
-  const Acc<DT> carry = dpp_acc<kWaveShr1, 0xf>(inc);
-  Acc<DT> c = acc;
+  const AccD carry = dpp_acc<kWaveShr1, 0xf>(inc);
+  AccD c = acc;
   if (head != kWave - 1) c.prepend(carry);
   return last_lane(c.value());
 }
@@ -971,7 +928,7 @@ struct Bunch {
     const int rank0 = incl - c_heads;
 
     products_in<DT, W>(reinterpret_cast<const prod_t *>(part), lane, pr);
-    Acc<DT> acc, pre;
+    AccD acc, pre;
     acc.zero();
     pre.zero();
     bool seen = false;
@@ -988,17 +945,17 @@ struct Bunch {
       acc.add(pr[i]);
     }
     if (!seen) pre = acc;
-    Acc<DT> inc = acc;
+    AccD inc = acc;
     int f = seen ? 1 : 0;
     wave_seg_scan(inc, f);
-    const Acc<DT> carry = dpp_acc<kWaveShr1, 0xf>(inc);
+    const AccD carry = dpp_acc<kWaveShr1, 0xf>(inc);
     if (seen && rank0 > 0) {
-      Acc<DT> c = pre;
+      AccD c = pre;
       c.prepend(carry);
       part[rank0 - 1] = c.value();
     }
     if (lane == kWave - 1) {
-      Acc<DT> c = pre;
+      AccD c = pre;
       c.prepend(carry);
       part[cnt - 1] = seen ? acc.value() : c.value();
     }
