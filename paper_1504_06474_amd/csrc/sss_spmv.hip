@@ -445,21 +445,24 @@ __device__ __forceinline__ void products_out(const P (&av)[W], const P (&xv)[W],
   }
 }
 
+template <int W, typename P>
+__device__ __forceinline__ void products_read(const P *buf, int lane, P (&pr)[W]) {
+  constexpr int CH = 16 / (int)sizeof(P);
+  // one wavefront owns buf and its LDS operations run in order; the
+  // fence keeps the compiler from moving a read above another lane's write
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < W / CH; ++k) {
+    const P *src = buf + tr_chunk<P, W>((lane * W) / CH + k) * CH;
+#pragma unroll
+    for (int e = 0; e < CH; ++e) pr[k * CH + e] = src[e];
+  }
+}
+
 template <int DT, int W, typename P>
 __device__ __forceinline__ void products_in(const P *buf, int lane, P (&pr)[W]) {
-  constexpr int CH = 16 / (int)sizeof(P);
-  if constexpr (group_w<DT, W>() != W) {
-    // one wavefront owns buf and its LDS operations run in order; the
-    // fence keeps the compiler from moving a read above another lane's write
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < W / CH; ++k) {
-      const P *src = buf + tr_chunk<P, W>((lane * W) / CH + k) * CH;
-#pragma unroll
-      for (int e = 0; e < CH; ++e) pr[k * CH + e] = src[e];
-    }
-  }
+  if constexpr (group_w<DT, W>() != W) products_read<W>(buf, lane, pr);
 }
 
 template <int DT, int W, bool DEBUG>
@@ -817,46 +820,78 @@ __device__ __forceinline__ T buffer_load(rsrc_t r, int voffset, int soffset) {
   return v;
 }
 
-// One tile's columns and stored values in the grouped order, as loaded: one
-// 16-byte load of values per row (8 bytes where G is 4 BF16 values).
+// The fused kernel's grouped order (see group_of): G entries of a lane are
+// consecutive.  Two for FP64 and four for FP32 are 16 bytes of values; BF16
+// takes four as well, 8 bytes: its gathers then fall on half as many
+// consecutive nonzeros as with eight, which on a 160^3 27-point stencil is
+// worth 20 of 186 us (1M-row power law 111.0 / 106.2, FEM band 57.0 / 53.3;
+// 5-point stencils 0.5% slower).  One or two for the others measured 4 to 12%
+// slower on stencils and batches (more registers for the same bytes).
+template <int DT> constexpr int fused_group() { return DT == SSS_F64 ? 2 : 4; }
+
+template <int N, bool NT>
+__device__ __forceinline__ void load_words(rsrc_t r, int voffset, int soffset, uint32_t *w) {
+  if constexpr (N == 1) {
+    w[0] = buffer_load<uint32_t, NT>(r, voffset, soffset);
+  } else if constexpr (N == 2) {
+    const v2u v = buffer_load<v2u, NT>(r, voffset, soffset);
+    w[0] = v.x; w[1] = v.y;
+  } else {
+    static_assert(N % 4 == 0, "1, 2 or quadruples of words");
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+      const v4u v = buffer_load<v4u, NT>(r, voffset + 4 * i, soffset);
+      w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
+    }
+  }
+}
+
+// One tile's columns and stored values, as loaded.
 template <int DT, int W>
 struct Tile {
-  static constexpr int G = group_w<DT, W>(), R = W / G;
+  static constexpr int G = fused_group<DT>(), R = W / G;
   static constexpr int VB = (int)sizeof(typename VT<DT>::val_t);
-  static constexpr int CI = G >= 4 ? G / 4 : 1;  // column loads per row
-  using col_t = std::conditional_t<G == 2, v2u, v4u>;
-  using raw_t = std::conditional_t<G * VB == 16, v4u, v2u>;
-  col_t c[R * CI];
-  raw_t v[R];
+  static constexpr int VW = G * VB / 4;  // words of values per row
+  uint32_t c[W], v[R * VW];
 
   template <bool NT>
   __device__ __forceinline__ void load(rsrc_t rc, rsrc_t rv, int t, int lane) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int i = 0; i < CI; ++i)
-        c[r * CI + i] = buffer_load<col_t, NT>(rc, lane * G * 4 + r * kWave * G * 4 + i * 16, t * W * kWave * 4);
-      v[r] = buffer_load<raw_t, NT>(rv, lane * G * VB + r * kWave * G * VB, t * W * kWave * VB);
+      load_words<G, NT>(rc, lane * G * 4 + r * kWave * G * 4, t * W * kWave * 4, &c[r * G]);
+      load_words<VW, NT>(rv, lane * G * VB + r * kWave * G * VB, t * W * kWave * VB, &v[r * VW]);
     }
   }
-  __device__ __forceinline__ uint32_t column(int i) const {
-    if constexpr (G == 2) return c[i / 2][i % 2];
-    else return c[i / 4][i % 4];
-  }
+  __device__ __forceinline__ uint32_t column(int i) const { return c[i]; }
   __device__ __forceinline__ typename VT<DT>::prod_t value(int i) const {
-    const int r = i / G, g = i % G;
-    if constexpr (DT == SSS_F64) {
-      const uint64_t b = (uint64_t)v[r][2 * g] | ((uint64_t)v[r][2 * g + 1] << 32);
-      return __longlong_as_double((long long)b);
-    } else if constexpr (DT == SSS_F32) {
-      return __uint_as_float(v[r][g]);
+    if constexpr (DT == SSS_F64)
+      return __longlong_as_double((long long)((uint64_t)v[2 * i] | ((uint64_t)v[2 * i + 1] << 32)));
+    else if constexpr (DT == SSS_F32)
+      return __uint_as_float(v[i]);
+    else
+      return __uint_as_float(i % 2 ? v[i / 2] & 0xffff0000u : v[i / 2] << 16);
+  }
+  // where in the tile a lane's entry i is
+  __device__ __forceinline__ static int offset(int i, int lane) { return (i / G) * kWave * G + lane * G + i % G; }
+
+  // the products into LDS, in the layout that products_read reads, or into
+  // pr where the loads' order is the lane order
+  template <typename P>
+  __device__ __forceinline__ static void store(const P (&av)[W], const P (&bv)[W], P *buf, int lane, P (&pr)[W]) {
+    if constexpr (G == W) {
+#pragma unroll
+      for (int i = 0; i < W; ++i) pr[i] = av[i] * bv[i];
     } else {
-      const uint32_t w = v[r][g / 2];
-      return __uint_as_float(g % 2 ? w & 0xffff0000u : w << 16);
+      constexpr int CH = 16 / (int)sizeof(P);
+      static_assert(CH == G, "a lane's consecutive entries are one chunk");
+#pragma unroll
+      for (int i = 0; i < W; i += G) {
+        P *dst = buf + tr_chunk<P, W>(offset(i, lane) / CH) * CH;
+#pragma unroll
+        for (int g = 0; g < G; ++g) dst[g] = av[i + g] * bv[i + g];
+      }
     }
   }
-  // the values of entries at or past `left` (in the tile) become 0
-  __device__ __forceinline__ static int offset(int i, int lane) { return (i / G) * kWave * G + lane * G + i % G; }
 };
 
 // The sum of row entries rs .. b0-1, the part of a row before the bunch that
@@ -906,8 +941,8 @@ struct Bunch {
   double transmitter, sync_v;
 
   // The segmented sum of tile t, entries b .. e-1 of the matrix, whose
-  // products lie in `part` in the layout of products_out; as in stage1_bunch.
-  // `pr` holds them already where that layout is the lane order.
+  // products lie in `part` (in `pr` where the loads' order is the lane order);
+  // as in stage1_bunch.
   __device__ __forceinline__ double sum_tile(int t, int e, prod_t (&pr)[W]) {
     constexpr int WT = W * kWave;
     constexpr int WPT = WT / 32;
@@ -927,7 +962,7 @@ struct Bunch {
     const int cnt = __builtin_amdgcn_readlane(incl, kWave - 1);
     const int rank0 = incl - c_heads;
 
-    products_in<DT, W>(reinterpret_cast<const prod_t *>(part), lane, pr);
+    if constexpr (fused_group<DT>() != W) products_read<W>(reinterpret_cast<const prod_t *>(part), lane, pr);
     AccD acc, pre;
     acc.zero();
     pre.zero();
@@ -1179,7 +1214,7 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
       for (int i = 0; i < W; ++i)
         if (Tile<DT, W>::offset(i, lane) >= left - t * WT) av[i] = bv[i] = (prod_t)0;
     }
-    products_out<DT, W>(av, bv, reinterpret_cast<prod_t *>(u.part), lane, pr);
+    Tile<DT, W>::store(av, bv, reinterpret_cast<prod_t *>(u.part), lane, pr);
   };
   double tail = 0.0;
   for (int t = 0; t + 1 < tiles; ++t) {
