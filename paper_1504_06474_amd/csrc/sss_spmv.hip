@@ -783,9 +783,9 @@ enum Form { kCached, kStreamed, kWide };
 
 // What a plan tells a bunch of its first row, rp[r0] <= b0 < rp[r0 + 1]: its
 // back_entries (7 bits), and above them how many entries of row_ptr after
-// rp[r0] the bunch needs, up to the first that is past its end (kSpanMax:
-// more than the two that each lane loads ahead).
-constexpr int kSpanMax = 2 * kWave;
+// rp[r0] the bunch needs, up to the first that is past its end (kSpanMax: that
+// many or more, which the bunch finds itself).
+constexpr int kSpanMax = 1 << 22;
 // r_next: the next bunch's first row, m after the last bunch.
 __device__ __forceinline__ int slot_need(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb, int32_t r,
                                          int32_t r_next) {
@@ -1085,9 +1085,10 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
   int r0 = known ? brow & 0x7fffffff : 0;
   const int span = need >> 8;
   const bool ahead = known && span < kSpanMax;
-  const rsrc_t rr = make_rsrc(a.row_ptr + r0, ahead ? (uint32_t)(span + 1) * 4u : 0u);
+  const rsrc_t rr = make_rsrc(a.row_ptr + r0, ahead ? (uint32_t)(min(span, 2 * kWave - 1) + 1) * 4u : 0u);
   const int rows0 = buffer_load<int>(rr, lane * 4, 0);
   const int rows1 = buffer_load<int>(rr, lane * 4 + kWave * 4, 0);
+  const int past_span = a.row_ptr[ahead ? imin64((int64_t)r0 + span, m) : 0];
   const int second_row = a.row_ptr[1];
   if (S > 1) next.template load<NT>(rc, rv, 1, lane);
 
@@ -1109,19 +1110,22 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
   uint64_t filled_rows = 0;
   // the plan's rows hold where rp[r0] <= b0 < rp[r0 + 1] and the entry after
   // the span is past bS (or the last): row_ptr ascends, so every row between
-  // is the bunch's.  Else (no plan, a long span, or row_ptr rewritten in place
-  // since) the pass loads its rows itself, from the row that it searches for.
-  bool loaded = false;
-  if (ahead) {
-    const int p0 = lane_value(rows0, 0), q0 = lane_value(rows0, 1);
-    const int end = span < kWave ? lane_value(rows0, span) : lane_value(rows1, span - kWave);
-    loaded = p0 <= b0 && b0 < q0 && (r0 + span >= m || end > bS);
-  }
+  // is the bunch's.  Else (no plan, a longer span, or row_ptr rewritten in
+  // place since) the bunch searches for its first row and reads on from there.
+  const bool loaded = ahead && lane_value(rows0, 0) <= b0 && b0 < lane_value(rows0, 1) &&
+                      ((int64_t)r0 + span >= m || past_span > bS);
   if (!loaded) {
     bool found = false;
     if (known) found = rp[r0] <= b0 && b0 < rp[r0 + 1];
     if (!found) r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(rp, m, b0, lane));
   }
+  const int last = loaded ? (int)imin64((int64_t)r0 + span, m) : m;  // the last entry to read
+  // entries rbase .. rbase + 63, INT_MAX past the last
+  auto entries = [&](int rbase) {
+    const int n = min(last - rbase + 1, kWave);
+    const int v = buffer_load<int>(make_rsrc(rp + rbase, n > 0 ? (uint32_t)n * 4u : 0u), lane * 4, 0);
+    return lane < n ? v : INT_MAX;
+  };
   // one chunk of 64 rows: p = rp[r], after = the entry past the chunk (a value
   // past bS beyond the last entry, or beyond the span); true when more follow
   auto row_chunk = [&](int rbase, int p, int after) {
@@ -1148,16 +1152,20 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
     }
     return lane_value(p, kWave - 1) <= bS && rbase + (kWave - 1) < m;
   };
-  if (loaded) {  // (apart from the loop below, whose loads would make this wait for tile 0's gathers)
+  if (loaded && span < 2 * kWave) {  // (apart from the loop below, whose loads would make this wait for tile 0's gathers)
     for (int chunk = 0; chunk < 2; ++chunk) {
       const int p = chunk * kWave + lane <= span ? (chunk == 0 ? rows0 : rows1) : INT_MAX;
       const int after = chunk == 0 && span >= kWave ? lane_value(rows1, 0) : INT_MAX;
       if (!row_chunk(r0 + chunk * kWave, p, after)) break;
     }
   } else {
+    // two chunks ahead: a chunk needs the first entry of the next
+    int p = loaded ? rows0 : entries(r0), next_p = loaded ? rows1 : entries(r0 + kWave);
     for (int rbase = r0;; rbase += kWave) {
-      const int p = rbase + lane <= m ? rp[rbase + lane] : INT_MAX;
-      if (!row_chunk(rbase, p, rbase + kWave <= m ? rp[rbase + kWave] : INT_MAX)) break;
+      const int p2 = entries(rbase + 2 * kWave);
+      if (!row_chunk(rbase, p, lane_value(next_p, 0))) break;
+      p = next_p;
+      next_p = p2;
     }
   }
   __builtin_amdgcn_wave_barrier();
