@@ -6,10 +6,11 @@
 // conversion to another format would cost about as much as the solve.  This
 // file is that use: Hestenes and Stiefel's iteration for a symmetric positive
 // definite A, with the vector steps and dot products in kernels of their own,
-// so that an iteration is the two stages of the product plus three short
-// launches and the host never waits inside the loop:
+// so that an iteration is the product plus two or three short launches and
+// the host never waits inside the loop:
 //
-//   cg_pq         partial sums of p.q, one per workgroup
+//   cg_pq         partial sums of p.q, one per workgroup; left out where the
+//                 product's kernel forms them (sss_execute_dot)
 //   cg_residual   alpha = (r.r) / (p.q); r -= alpha q; partial sums of the
 //                 new r.r
 //   cg_direction  beta = (r.r)_new / (r.r); x += alpha p; p = r + beta p;
@@ -29,7 +30,8 @@
 //   [2] b.b
 //   [3] alpha of the step under way (written by workgroup 0 of cg_residual,
 //       read by cg_direction)
-//   [kPartA ...) the per-workgroup partial sums of p.q (at the start: r.r)
+//   [kPartA ...) the per-workgroup partial sums of p.q (at the start: r.r),
+//       unless the product's kernel formed them
 //   [kPartB ...) the per-workgroup partial sums of the new r.r (start: b.b)
 // No kernel writes a word that another workgroup of the same launch reads.
 
@@ -38,7 +40,7 @@
 #include <algorithm>
 #include <cstdint>
 
-#include "sss.h"
+#include "sss_internal.h"
 
 namespace {
 
@@ -70,10 +72,18 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
   return s;
 }
 
-// the sum of the nblk partial sums, the same in every workgroup
+// the sum of the nblk partial sums, the same in every workgroup; where the
+// product's kernel left thousands, 8 loads in flight (on the 4 of a vector
+// kernel's 1,024 that costs 1% of a step)
 __device__ __forceinline__ double sum_partials(const double *part, int nblk, double *lds) {
   double v = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += kThreads) v += part[i];
+  if (nblk > kMaxBlocks) {
+#pragma unroll 8
+    for (int i = threadIdx.x; i < nblk; i += kThreads) v += part[i];
+  } else {
+#pragma unroll 1
+    for (int i = threadIdx.x; i < nblk; i += kThreads) v += part[i];
+  }
   return block_sum(v, lds);
 }
 
@@ -142,9 +152,10 @@ __global__ __launch_bounds__(kThreads) void cg_pq(const double *__restrict__ p, 
 
 // alpha = (r.r) / (p.q); r -= alpha q; partial sums of the new r.r
 __global__ __launch_bounds__(kThreads) void cg_residual(const double *__restrict__ q, double *__restrict__ r,
-                                                        double *__restrict__ work, int64_t m, int nblk) {
+                                                        double *__restrict__ work, int64_t m,
+                                                        const double *__restrict__ pq_part, int n_pq) {
   __shared__ double lds[kThreads / kWave];
-  const double pq = sum_partials(work + kPartA, nblk, lds);
+  const double pq = sum_partials(pq_part, n_pq, lds);
   const double rho = work[kRho];
   const double alpha = pq != 0.0 ? rho / pq : 0.0;
   double rr = 0.0;
@@ -275,10 +286,15 @@ int sss_cg_iterate(sss_plan p, const int32_t *row_ptr, const int32_t *col, const
   double *w = static_cast<double *>(work);
   const int nblk = vector_blocks(m);
   for (int it = 0; it < iterations; ++it) {
-    rc = sss_csr_spmv_execute(p, row_ptr, col, val, dir, q, stream);
+    const double *pq = w + kPartA;
+    int n_pq = 0;
+    rc = sss_execute_dot(p, row_ptr, col, val, dir, q, stream, &pq, &n_pq);
     if (rc != SSS_OK) return rc;
-    hipLaunchKernelGGL(cg_pq, dim3(nblk), dim3(kThreads), 0, s, dir, q, w, m);
-    hipLaunchKernelGGL(cg_residual, dim3(nblk), dim3(kThreads), 0, s, q, r, w, m, nblk);
+    if (n_pq == 0) {
+      hipLaunchKernelGGL(cg_pq, dim3(nblk), dim3(kThreads), 0, s, dir, q, w, m);
+      n_pq = nblk;
+    }
+    hipLaunchKernelGGL(cg_residual, dim3(nblk), dim3(kThreads), 0, s, q, r, w, m, pq, n_pq);
     hipLaunchKernelGGL(cg_direction, dim3(nblk), dim3(kThreads), 0, s, r, dir, x, w, m, nblk);
     if ((rc = launch_status()) != SSS_OK) return rc;
   }

@@ -1,0 +1,17 @@
+// Calls between the library's source files; not part of its C ABI.
+#ifndef SSS_INTERNAL_H
+#define SSS_INTERNAL_H
+
+#include <cstdint>
+
+#include "sss.h"
+
+// sss_csr_spmv_execute in double precision for a square matrix, with partial
+// sums of x . y beside it: *dots (device) holds *n_dots of them, in a fixed
+// order, until the plan's next call.  *n_dots = 0: this plan's product does
+// not form them (y is complete all the same).
+extern "C" __attribute__((visibility("hidden"))) int sss_execute_dot(sss_plan p, const int32_t *row_ptr, const int32_t *col,
+                                                          const double *val, const double *x, double *y,
+                                                          void *stream, const double **dots, int *n_dots);
+
+#endif  // SSS_INTERNAL_H

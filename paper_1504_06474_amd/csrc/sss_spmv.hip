@@ -66,11 +66,12 @@
 #include <type_traits>
 #include <vector>
 
-#include "sss.h"
+#include "sss_internal.h"
 
 namespace {
 
 constexpr int kWave = 64;
+constexpr int kMaxB = 4;  // wavefronts per workgroup
 constexpr int kShortRun = 16;  // stage-2 carry runs up to this many bunches: one thread
 
 thread_local hipError_t g_last_hip = hipSuccess;
@@ -924,8 +925,9 @@ __device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, doubl
   return last_lane(c.value());
 }
 
-// What the tiles of a bunch share.
-template <int DT, int W>
+// What the tiles of a bunch share.  DOT (square FP64 matrices): beside y, the
+// sum of x[r] y[r] over the rows that the bunch writes.
+template <int DT, int W, bool DOT>
 struct Bunch {
   using y_t = typename VT<DT>::y_t;
   using prod_t = typename VT<DT>::prod_t;
@@ -939,6 +941,15 @@ struct Bunch {
   int my_start, my_rp;   // lane t: tile t's start row and its row_ptr
   uint64_t filled_rows;  // lane c: which of the rows r0 + 64 c + 0 .. 63 hold entries
   double transmitter, sync_v;
+  const double *x;  // DOT only, as the next three
+  double x_row;     // x of row start + lane of the tile
+  double dot;
+
+  // x of the tile's rows, loaded ahead of the next tile's gathers so that the
+  // store loop need not wait for those
+  __device__ __forceinline__ void load_rows(int t) {
+    if constexpr (DOT) x_row = x[min(lane_value(my_start, t) + lane, m - 1)];
+  }
 
   // The segmented sum of tile t, entries b .. e-1 of the matrix, whose
   // products lie in `part` (in `pr` where the loads' order is the lane order);
@@ -1001,7 +1012,10 @@ struct Bunch {
       // (k >= 1), the empty ones 0.  Which are empty the row pass has kept for
       // its first 64 chunks (row_ptr read again here would make the tile wait
       // for every load in flight).
-      if (lane == 0 && start != r0 && !(cnt == 1 && ends_mid)) y_store((y_t)(part[0] + tx), &y[start]);
+      if (lane == 0 && start != r0 && !(cnt == 1 && ends_mid)) {
+        y_store((y_t)(part[0] + tx), &y[start]);
+        if constexpr (DOT) dot += x_row * (part[0] + tx);
+      }
       int k = 0;
       for (int c = (start + 1 - r0) / kWave; r0 + c * kWave < stop; ++c) {
         const int r = r0 + c * kWave + lane;
@@ -1016,6 +1030,8 @@ struct Bunch {
         }
         const int rank = k + 1 + __popcll(filled & ((1ull << lane) - 1ull));
         if (in) y_store((filled >> lane) & 1ull ? (y_t)part[min(rank, WT - 1)] : (y_t)0, &y[r]);
+        if constexpr (DOT)
+          if ((filled >> lane) & 1ull) dot += x[r] * part[min(rank, WT - 1)];
         k += __popcll(filled);
       }
       if (lane == 0 && speculator)
@@ -1028,6 +1044,7 @@ struct Bunch {
           double v = part[q];
           if (q == 0) v += tx;
           y_store((y_t)v, &y[idx]);
+          if constexpr (DOT) dot += (q < kWave ? x_row : x[idx]) * v;
         }
       }
     }
@@ -1043,9 +1060,10 @@ struct Bunch {
 };
 
 // tb, the bunch; brow, its first row at plan time or -1; need, its slot_need
-// (0 without a plan): the same in every lane.
-template <int DT, int W, Form FORM>
-__device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const int brow, const int need,
+// (0 without a plan): the same in every lane.  Returns the lane's part of the
+// bunch's dot product (DOT).
+template <int DT, int W, Form FORM, bool DOT = false>
+__device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, const int brow, const int need,
                                             uint32_t *lds_wave, const int lane) {
   using val_t = typename VT<DT>::val_t;
   using x_t = typename VT<DT>::x_t;
@@ -1170,7 +1188,7 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
   }
   __builtin_amdgcn_wave_barrier();
 
-  Bunch<DT, W> u;
+  Bunch<DT, W, DOT> u;
   u.rp = rp;
   u.y = static_cast<y_t *>(a.y);
   u.speculator = a.speculator ? a.speculator + (int64_t)tb * S : nullptr;
@@ -1186,6 +1204,8 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
   u.filled_rows = filled_rows;
   u.transmitter = 0.0;
   u.sync_v = 0.0;
+  if constexpr (DOT) u.x = static_cast<const double *>(a.x);
+  u.dot = 0.0;
 
   // ---- does this bunch write y[r0]: it does when the row ends here and is
   // no long crossing row; the row's entries before the bunch are summed here
@@ -1227,6 +1247,7 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
   double tail = 0.0;
   for (int t = 0; t + 1 < tiles; ++t) {
     products(t);
+    u.load_rows(t);
     cur = next;
 #pragma unroll
     for (int i = 0; i < W; ++i) xv[i] = gather(cur.column(i));
@@ -1234,9 +1255,13 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
     (void)u.sum_tile(t, b0 + (t + 1) * WT, pr);
   }
   products(tiles - 1);
+  u.load_rows(tiles - 1);
   tail = u.sum_tile(tiles - 1, bS, pr);
 
-  if (own_first && lane == 0) y_store((y_t)(before + u.sync_v), &u.y[r0]);
+  if (own_first && lane == 0) {
+    y_store((y_t)(before + u.sync_v), &u.y[r0]);
+    if constexpr (DOT) u.dot += u.x[r0] * (before + u.sync_v);
+  }
   // rows before the first non-empty one: those of this bunch's share of y
   if (second_row == 0) {
     const int64_t hi = (int64_t)m * (tb + 1) / a.n_bunches;
@@ -1251,6 +1276,7 @@ __device__ __forceinline__ void fused_bunch(const MatCtx &a, const int tb, const
     for (int i = 1; i < 6; ++i) w = lane == i ? words[i] : w;
     if (lane < 6) reinterpret_cast<uint32_t *>(a.state + tb)[lane] = w;
   }
+  return u.dot;
 }
 
 template <int DT, int W, Form FORM>
@@ -1268,6 +1294,33 @@ __global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
     return;
   }
   fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, lds_words + wid * stage1_lds_words(W, a.S), lane);
+}
+
+// The same with the partial sums of x . y, one per workgroup, for bound FP64
+// plans without long crossing rows (those are completed by another launch).
+// An iterative method that needs the product and its dot product with x (CG's
+// p . A p) saves a launch and a pass over both vectors.
+template <int W, Form FORM>
+__global__ __launch_bounds__(256) void sss_fused_dot(MatCtx a, double *__restrict__ dots) {
+  extern __shared__ uint32_t lds_words[];
+  __shared__ double sums[kMaxB];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = wave_in_block();
+  const int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
+  double dot = 0.0;
+  if (g < a.n_slots) {
+    const int4 slot = uniform_load(a.slots + g);
+    if (slot.x >= 0)
+      dot = fused_bunch<SSS_F64, W, FORM, true>(a, slot.x, slot.y, slot.z,
+                                                lds_words + wid * stage1_lds_words(W, a.S), lane);
+  }
+  dot = wave_sum_tree(dot);
+  if (lane == 0) sums[wid] = dot;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < (int)(blockDim.x / kWave); ++i) dot += sums[i];
+    dots[blockIdx.x] = dot;
+  }
 }
 
 // gfx950 (one partition) hands consecutive workgroups to its 8 XCDs in turn,
@@ -1926,7 +1979,6 @@ constexpr size_t kFixupLdsBytes = 64 * 1024;  // LDS of one fixup workgroup
 // also holds the carry pass's staged entries
 static_assert(4 * kWave * 4 >= (kWave + kShortRun) * (sizeof(double) + sizeof(int)), "carry staging fits");
 constexpr int kMaxS = 16;
-constexpr int kMaxB = 4;
 
 bool dtype_ok(int dt) { return dt == SSS_F64 || dt == SSS_F32 || dt == SSS_BF16; }
 size_t y_size(int dt) { return dt == SSS_F64 ? 8 : 4; }
@@ -1947,6 +1999,10 @@ Stage1Fn pick_fused(Form form) {
   return form == kCached ? sss_fused<DT, W, kCached>
                          : (form == kStreamed ? sss_fused<DT, W, kStreamed> : sss_fused<DT, W, kWide>);
 }
+
+using DotFn = void (*)(MatCtx, double *);
+template <int W>
+DotFn pick_dot(Form form) { return form == kCached ? sss_fused_dot<W, kCached> : sss_fused_dot<W, kStreamed>; }
 
 template <int DT, int W, Form FORM>
 BatchFn pick_batch_form(bool persistent) {
@@ -1990,6 +2046,7 @@ struct sss_plan_s {
   int32_t carries = 1;           // 0: no long crossing row at plan time (see sss_fused), so no second launch
   int4 *slots = nullptr;         // bind_rows plans: see MatCtx::slots
   uint32_t *order_hist = nullptr;
+  double *dots = nullptr;        // bind_rows FP64 plans: see sss_fused_dot
   bool call_order = false;       // plans without bind_rows: every call makes bunch_row and slots, see orders_calls
   int64_t n_slots = 0;
   int32_t *dbg_start = nullptr;
@@ -2016,7 +2073,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // entry per tile), every array 256-byte aligned.
 struct AuxLayout {
   int64_t n_tiles = 0, n_bunches = 0;
-  size_t state = 0, spec = 0, brow = 0, dlist = 0, stale = 0, slots = 0, ohist = 0,
+  size_t state = 0, spec = 0, brow = 0, dlist = 0, stale = 0, slots = 0, ohist = 0, dots = 0,
          dstart = 0, ddirty = 0, dheads = 0;
   size_t total = 0;
 };
@@ -2042,6 +2099,9 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug, bool call
     L.slots = off; off = align256(off + sizeof(int4) * (nb + kXcds * kMaxB));
     L.ohist = off; off = align256(off + sizeof(uint32_t) * 2 * (kOrderBins + 1));
   }
+  if (bind) {
+    L.dots = off; off = align256(off + sizeof(double) * (nb + kXcds * kMaxB));
+  }
   if (debug) {
     L.dstart = off; off = align256(off + sizeof(int32_t) * (nt + 1));
     L.ddirty = off; off = align256(off + sizeof(int32_t) * (nt + 1));
@@ -2059,6 +2119,7 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
   p->aux = base_v;
   p->state = reinterpret_cast<BunchState *>(base + L.state);
   p->speculator = reinterpret_cast<int4 *>(base + L.spec);
+  p->dots = p->bind_rows ? reinterpret_cast<double *>(base + L.dots) : nullptr;
   p->bunch_row = p->bind_rows || p->call_order ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
   p->dirty_list = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.dlist) : nullptr;
   p->stale = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.stale) : nullptr;
@@ -2250,6 +2311,13 @@ int launch(sss_plan p, const int32_t *row_ptr, const int32_t *col, const void *v
   SSS_HIP(hipGetLastError());
   return SSS_OK;
 }
+
+// Every workgroup of the reader adds up all the sums of sss_fused_dot, which
+// from some number on costs more than the launch saved.  50 CG steps on
+// Laplacians, us with a pass of its own / with the sums: 64^2 (80 sums) 775 /
+// 625, 256^2 786 / 664, 512^2 (2,560) 972 / 927, 700^2 1,383 / 1,319, 1024^2
+// (5,117) 1,955 / 1,996, 900^2 (3,950) 1,681 / 1,704, (7,900) 1,672 / 1,858.
+constexpr int64_t kMaxDots = 3072;
 
 // A batch plan: the fused launch (one wavefront per thread-bunch of every
 // matrix, or the persistent form), then the carries where the plan needs them.
@@ -2561,6 +2629,27 @@ int sss_plan_dirty_list(sss_plan p, int32_t *host_out, int64_t cap, int64_t *n) 
   *n = p->n_listed;
   const int64_t k = std::min(cap, p->n_listed);
   if (k > 0) SSS_HIP(hipMemcpy(host_out, p->dirty_list, (size_t)k * sizeof(int32_t), hipMemcpyDeviceToHost));
+  return SSS_OK;
+}
+
+int sss_execute_dot(sss_plan p, const int32_t *row_ptr, const int32_t *col, const double *val, const double *x,
+                    double *y, void *stream, const double **dots, int *n_dots) {
+  *n_dots = 0;
+  if (!p || p->batch) return SSS_ERR_INVALID_VALUE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const Form form = form_of(p->nnz, p->n, p->dt);
+  const int64_t blocks = (p->n_slots + p->B - 1) / p->B;
+  if (!p->bind_rows || p->dt != SSS_F64 || p->m != p->n || p->carries || p->debug || form == kWide || blocks > kMaxDots)
+    return launch(p, row_ptr, col, val, x, y, s);
+  const int rc = check_call(p, row_ptr, col, val, x, y);
+  if (rc != SSS_OK) return rc;
+  const DotFn k = p->W == 4 ? pick_dot<4>(form) : (p->W == 8 ? pick_dot<8>(form) : pick_dot<16>(form));
+  const size_t lds = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(p->B * kWave), lds, s, plan_ctx(p, row_ptr, col, val, x, y),
+                     p->dots);
+  SSS_HIP(hipGetLastError());
+  *dots = p->dots;
+  *n_dots = (int)blocks;
   return SSS_OK;
 }
 

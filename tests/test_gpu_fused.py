@@ -154,3 +154,40 @@ def test_wide_x(kind):
     y = torch.full((A.m,), float("nan"), dtype=yt, device="cuda")
     sss.BatchPlan([(rp, col, v, big, y, n)], dtype=vt).execute()
     assert_exact(y.double().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("W,S,B", [(4, 1, 2), (8, 2, 3), (16, 1, 1), (4, 3, 4)])
+@pytest.mark.parametrize("grid", [5, 60])
+def test_product_with_dot(grid, W, S, B):
+    """CG steps whose product forms p.q itself (bound plans without long
+    crossing rows), on a Laplacian with some unknowns taken out: their rows
+    are empty, so tiles are dirty.  Three steps against numpy's, normwise
+    1e-11 as the CG tests have it."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note(f"[gpu-test] product with dot {grid} W={W} S={S} B={B}")
+    L = csrgen.laplacian2d_csr(grid)
+    out = np.zeros(L.m, dtype=bool)
+    out[csrgen.rng_for(3).choice(L.m, L.m // 6, replace=False)] = True
+    out[:2] = True
+    rows = np.repeat(np.arange(L.m), np.diff(L.row_ptr))
+    keep = ~(out[rows] | out[L.col])
+    rp = np.zeros(L.m + 1, dtype=np.int32)
+    np.cumsum(np.bincount(rows[keep], minlength=L.m), out=rp[1:])
+    A = csrgen.CSR(L.m, L.m, rp, L.col[keep], L.val[keep])
+    b = np.where(out, 0.0, csrgen.rng_for(4).uniform(-1, 1, L.m))
+    drp, col, v, db = to_dev_precision(A, b, "f64")[:4]
+    plan = sss.Plan(A.m, A.m, A.nnz, W=W, S=S, B=B, row_ptr=drp, bind_rows=True)
+    vec = [torch.zeros(A.m, dtype=torch.float64, device="cuda") for _ in range(4)]
+    work = torch.zeros(sss.cg_workspace_size() // 8, dtype=torch.float64, device="cuda")
+    sss.cg_start(plan, drp, col, v, db, vec[0], vec[1], vec[2], vec[3], work)
+    sss.cg_iterate(plan, drp, col, v, *vec, work, 3)
+    x, r, p = np.zeros(A.m), b.copy(), b.copy()
+    for _ in range(3):
+        q = oracle.spmv(A.row_ptr, A.col, A.val, p)
+        alpha = r @ r / (p @ q)
+        x, r_new = x + alpha * p, r - alpha * q
+        p = r_new + (r_new @ r_new) / (r @ r) * p
+        r = r_new
+    for got, want in zip(vec, (x, r, p)):
+        assert np.linalg.norm(got.cpu().numpy() - want) <= 1e-11 * max(np.linalg.norm(want), np.linalg.norm(b))
