@@ -59,9 +59,9 @@ typedef enum {
 
 /* Value type.  SSS_F64: val, x, y are double.  SSS_F32: val, x, y are float.
  * SSS_BF16: val is bfloat16 (uint16 bit patterns), x and y are float.  The
- * reduced-precision types multiply in float, sum segments with compensated
- * (TwoSum) float arithmetic, and keep the carries between tiles and between
- * thread-bunches, and the fixup sums, in double. */
+ * reduced-precision types round each product to float and add everything else
+ * in double: segments, the carries between tiles and between thread-bunches,
+ * and the fixup sums.  y is rounded once. */
 typedef enum { SSS_F64 = 0, SSS_F32 = 1, SSS_BF16 = 2 } sss_dtype;
 
 /* How a plan chooses (W, S): FIXED takes opts.W/S/B; SELECTOR computes the

@@ -194,12 +194,6 @@ __device__ __forceinline__ int wave_prev(int v, int first) {
 __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
 // v of lane `l`, for a lane index the same in every lane
 __device__ __forceinline__ int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-// a 64-bit value the same in every lane, in scalar registers
-__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 // *p for an address the same in every lane, of data no kernel of the launch
 // writes (plan arrays written before it): read through the scalar unit into
@@ -757,11 +751,12 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 //
 // Per product, the two launches before / this kernel (and sss_carries where
 // needed): 160^3 27-point stencil FP64 276 / 262 us (1.39 GB: 5.0 / 5.3
-// TB/s), 1414^2 5-point stencil FP64 39.9 / 32.1 us (160 MB: 4.0 / 5.0 TB/s),
-// FEM band 778K x 50 FP32 74.2 / 64.2 us (320 MB: 4.3 / 5.0 TB/s), 1M-row
-// power law FP64 182.9 / 171.9 us and BF16 117.8 / 110.8 us (both in column
-// order), 30K-row web-like FP32 12.3 / 10.6 us (the host's share is most of
-// that).
+// TB/s), 1414^2 5-point stencil FP64 39.9 / 31.8 us (160 MB: 4.0 / 5.0 TB/s),
+// FEM band 778K x 50 FP32 74.2 / 61.7 us (320 MB: 4.3 / 5.2 TB/s), 1M-row
+// power law FP64 182.9 / 171 us and BF16 117.8 / 106.9 us (both in column
+// order), 30K-row web-like FP32 12.3 / 7.3 us (5.8 us of that is the host's
+// call; it was 9.3).  The double sums gave the band 2.5 of its 12 us, the
+// groups of four the BF16 matrix 4 of its 11.
 constexpr int kBack = kWave;
 
 // Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
