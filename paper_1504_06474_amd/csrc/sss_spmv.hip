@@ -1095,9 +1095,15 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   const val_t back_v = buffer_load<val_t>(
       make_rsrc(static_cast<const val_t *>(a.val) + (b0 - back_n), (uint32_t)back_n * sizeof(val_t)),
       back_off * (int)sizeof(val_t), 0);
-  int r0 = known ? brow & 0x7fffffff : 0;
-  const int span = need >> 8;
-  const bool ahead = known && span < kSpanMax;
+  // A bunch without a row from the plan searches for it here, ahead of the
+  // gathers: loads return in order, so behind them every round of the search
+  // would wait for tile 0's gathers first.  Unbound products, us behind /
+  // ahead, W = 4, S = 1: power law 70K rows FP64 18.2 / 17.0, FP32 17.3 / 15.7,
+  // Poisson 60K rows 11.5 / 10.9, 500^2 5-point stencil 13.5 / 12.9.
+  int r0 = brow & 0x7fffffff;
+  if (!known) r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(a.row_ptr, m, b0, lane));
+  const int span = known ? need >> 8 : m - r0;
+  const bool ahead = !known || span < kSpanMax;
   const rsrc_t rr = make_rsrc(a.row_ptr + r0, ahead ? (uint32_t)(min(span, 2 * kWave - 1) + 1) * 4u : 0u);
   const int rows0 = buffer_load<int>(rr, lane * 4, 0);
   const int rows1 = buffer_load<int>(rr, lane * 4 + kWave * 4, 0);
@@ -1123,14 +1129,14 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   uint64_t filled_rows = 0;
   // the plan's rows hold where rp[r0] <= b0 < rp[r0 + 1] and the entry after
   // the span is past bS (or the last): row_ptr ascends, so every row between
-  // is the bunch's.  Else (no plan, a longer span, or row_ptr rewritten in
-  // place since) the bunch searches for its first row and reads on from there.
+  // is the bunch's.  Else (a longer span, or row_ptr rewritten in place since)
+  // the bunch searches for its first row and reads on from there.  A row just
+  // searched for holds, with every row to the last as its span.
   const bool loaded = ahead && lane_value(rows0, 0) <= b0 && b0 < lane_value(rows0, 1) &&
                       ((int64_t)r0 + span >= m || past_span > bS);
   if (!loaded) {
-    bool found = false;
-    if (known) found = rp[r0] <= b0 && b0 < rp[r0 + 1];
-    if (!found) r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(rp, m, b0, lane));
+    if (!known || !(rp[r0] <= b0 && b0 < rp[r0 + 1]))
+      r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(rp, m, b0, lane));
   }
   const int last = loaded ? (int)imin64((int64_t)r0 + span, m) : m;  // the last entry to read
   // entries rbase .. rbase + 63, INT_MAX past the last
@@ -1165,7 +1171,9 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     }
     return lane_value(p, kWave - 1) <= bS && rbase + (kWave - 1) < m;
   };
-  if (loaded && span < 2 * kWave) {  // (apart from the loop below, whose loads would make this wait for tile 0's gathers)
+  // the two chunks that are there hold the bunch (apart from the loop below,
+  // whose loads would make this wait for tile 0's gathers)
+  if (loaded && (span < 2 * kWave || lane_value(rows1, kWave - 1) > bS)) {
     for (int chunk = 0; chunk < 2; ++chunk) {
       const int p = chunk * kWave + lane <= span ? (chunk == 0 ? rows0 : rows1) : INT_MAX;
       const int after = chunk == 0 && span >= kWave ? lane_value(rows1, 0) : INT_MAX;
