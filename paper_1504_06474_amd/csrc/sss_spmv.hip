@@ -751,12 +751,13 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 //
 // Per product, the two launches before / this kernel (and sss_carries where
 // needed): 160^3 27-point stencil FP64 276 / 262 us (1.39 GB: 5.0 / 5.3
-// TB/s), 1414^2 5-point stencil FP64 39.9 / 31.8 us (160 MB: 4.0 / 5.0 TB/s),
+// TB/s), 1414^2 5-point stencil FP64 39.9 / 34.3 us (160 MB: 4.0 / 4.7 TB/s),
 // FEM band 778K x 50 FP32 74.2 / 61.7 us (320 MB: 4.3 / 5.2 TB/s), 1M-row
-// power law FP64 182.9 / 171 us and BF16 117.8 / 106.9 us (both in column
-// order), 30K-row web-like FP32 12.3 / 7.3 us (5.8 us of that is the host's
-// call; it was 9.3).  The double sums gave the band 2.5 of its 12 us, the
-// groups of four the BF16 matrix 4 of its 11.
+// power law FP64 182.9 / 181 us and BF16 117.8 / 111 us (both in column
+// order), 30K-row web-like FP32 12.3 / 6.2 us (5.8 us of that is the host's
+// call; it was 9.3).  Three matrices in turn; one again and again, the power
+// law takes 171 us and the 5-point stencil 31.6 (see form_of).  The double
+// sums gave the band 2.5 of its 12 us.
 constexpr int kBack = kWave;
 
 // Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
@@ -773,7 +774,7 @@ __device__ __forceinline__ int back_entries(int64_t rs, int64_t re, int64_t b0, 
 //  kCached: plain loads.
 //  kStreamed: the columns and values as non-temporal loads, which leave L2 to
 //    x.  Faster where the matrix comes from memory anyway, slower where much
-//    of it was still cached (see form_of).
+//    of it would still be cached at the next product (see form_of).
 //  kWide: streamed, and x is 4 GB or more, past a buffer load's 32-bit offset.
 enum Form { kCached, kStreamed, kWide };
 
@@ -2172,18 +2173,21 @@ int check_call(sss_plan p, const int32_t *row_ptr, const int32_t *col, const voi
   return SSS_OK;
 }
 
-// The form for nnz nonzeros (of a whole batch) and an x of n entries (its
-// largest).
-// Streamed from 60 MB of columns and values on, three matrices in turn: 46 MB
-// (power law 200K rows) 30.2 us cached, 32.7 streamed; 42 MB (dense rows)
-// 41.4, 43.1; 63 MB (CG on the 1024^2 Laplacian) 39.3, 39.0 per step; 72 MB
-// (web-like 2M rows) 101.0, 99.4; 160 MB (5-point stencil) 35.2, 32.4; 320 MB
-// (FEM band FP32) 71, 65.
-constexpr int64_t kStreamBytes = int64_t(60) << 20;
-Form form_of(int64_t nnz, int64_t n, int dt) {
-  if (n * (int64_t)y_size(dt) > 0xfffffff0ll) return kWide;
+// The form of a matrix (or a whole batch; n_max, its largest x).
+// Streamed from 300 MB of matrix and vectors on: less of it stays in the 256 MB
+// last-level cache from one product to the next, and non-temporal loads would
+// give that up.  us per product cached / streamed, one matrix again and again:
+// 120 MB power law 62.2 / 72.0, 163 MB 27-point stencil 33.3 / 36.8, 248 MB FEM
+// band 41.0 / 45.4, 285 MB FEM band 46.6 / 51.7, 322 MB FEM band 60.6 / 61.0,
+// FP32 320 MB 63.5 / 61.8, 455 MB 27-point stencil 89.1 / 85.3.  Three in turn
+// streaming is ahead from 87 MB on (160 MB 5-point stencil 34.5 / 31.9, 322 MB
+// FEM band 63.5 / 61.4), behind below (78 MB power law 38.4 / 42.1); a program
+// that iterates has one.
+constexpr int64_t kStreamBytes = 300000000;
+Form form_of(int64_t m, int64_t n, int64_t nnz, int dt, int64_t n_max) {
+  if (n_max * (int64_t)y_size(dt) > 0xfffffff0ll) return kWide;
   const int64_t value = dt == SSS_F64 ? 8 : (dt == SSS_F32 ? 4 : 2);
-  return nnz * (4 + value) >= kStreamBytes ? kStreamed : kCached;
+  return nnz * (4 + value) + 4 * m + (m + n) * (int64_t)y_size(dt) >= kStreamBytes ? kStreamed : kCached;
 }
 
 // The kernels' view of a single-matrix plan and the caller's arrays.
@@ -2261,7 +2265,7 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
     return SSS_OK;
   }
   Stage1Fn k1 = split ? SSS_PICK(pick_stage1, p->dt, p->W, p->debug != 0)
-                      : SSS_PICK(pick_fused, p->dt, p->W, form_of(p->nnz, p->n, p->dt));
+                      : SSS_PICK(pick_fused, p->dt, p->W, form_of(p->m, p->n, p->nnz, p->dt, p->n));
   if (!k1) return SSS_ERR_UNSUPPORTED;
   MatCtx a1 = plan_ctx(p, row_ptr, col, val, x, y);
   if (!split && p->call_order) {
@@ -2640,7 +2644,7 @@ int sss_execute_dot(sss_plan p, const int32_t *row_ptr, const int32_t *col, cons
   *n_dots = 0;
   if (!p || p->batch) return SSS_ERR_INVALID_VALUE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const Form form = form_of(p->nnz, p->n, p->dt);
+  const Form form = form_of(p->m, p->n, p->nnz, p->dt, p->n);
   const int64_t blocks = (p->n_slots + p->B - 1) / p->B;
   if (!p->bind_rows || p->dt != SSS_F64 || p->m != p->n || p->carries || p->debug || form == kWide || blocks > kMaxDots)
     return launch(p, row_ptr, col, val, x, y, s);
@@ -2917,7 +2921,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
 
   sss_plan p = new sss_plan_s();
   p->batch = true; p->dt = dt; p->W = W; p->S = S; p->B = B; p->batch_persistent = o.batch_persistent != 0;
-  p->batch_form = form_of(tot_nnz, n_max, dt);
+  p->batch_form = form_of(tot_m, tot_n, tot_nnz, dt, n_max);
   p->mat_S.resize((size_t)count);
   for (int i = 0; i < count; ++i) p->mat_S[(size_t)i] = ctx[(size_t)i].S;
   p->m = tot_m; p->n = tot_n; p->nnz = tot_nnz; p->n_tiles = tot_tiles; p->n_bunches = nb_all;

@@ -123,15 +123,20 @@ def test_entries_past_the_end_add_nothing():
 
 @pytest.mark.parametrize("kind", DTYPES)
 def test_streamed_form(kind):
-    """60 MB and more of columns and values: non-temporal loads."""
+    """A matrix past the last-level cache: non-temporal loads.  Six copies of a
+    smaller one below each other."""
+    import torch
     from paper_1504_06474_amd import sss
     vt, yt = torch_types(kind)
     rows = {"f64": 200_003, "f32": 300_007, "bf16": 400_003}[kind]
     note(f"[gpu-test] fused streamed {kind}")
     A, x = csr_from_lengths([27] * rows, 20_000, seed=4)
     rp, col, v, xx = to_dev_precision(A, x, kind)[:4]
-    plan = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=8, S=2, row_ptr=rp, bind_rows=True)
-    assert_exact(run(plan, rp, col, v, xx, A.m, yt).double().numpy(), oracle.spmv(A.row_ptr, A.col, A.val, x))
+    m, nnz = 6 * A.m, 6 * A.nnz
+    rp = torch.cat([rp[:-1] + k * A.nnz for k in range(6)] + [torch.tensor([nnz], dtype=torch.int32, device="cuda")])
+    plan = sss.Plan(m, A.n, nnz, dtype=vt, W=8, S=2, row_ptr=rp, bind_rows=True)
+    y = run(plan, rp, col.repeat(6), v.repeat(6), xx, m, yt).double().numpy()
+    assert_exact(y, np.tile(oracle.spmv(A.row_ptr, A.col, A.val, x), 6))
 
 
 @pytest.mark.parametrize("kind", ["f64", "f32"])
