@@ -751,13 +751,11 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 //
 // Per product, the two launches before / this kernel (and sss_carries where
 // needed): 160^3 27-point stencil FP64 276 / 262 us (1.39 GB: 5.0 / 5.3
-// TB/s), 1414^2 5-point stencil FP64 39.9 / 34.3 us (160 MB: 4.0 / 4.7 TB/s),
+// TB/s), 1414^2 5-point stencil FP64 39.9 / 31.9 us (160 MB: 4.0 / 5.0 TB/s),
 // FEM band 778K x 50 FP32 74.2 / 61.7 us (320 MB: 4.3 / 5.2 TB/s), 1M-row
-// power law FP64 182.9 / 181 us and BF16 117.8 / 111 us (both in column
+// power law FP64 182.9 / 171 us and BF16 117.8 / 111 us (both in column
 // order), 30K-row web-like FP32 12.3 / 6.2 us (5.8 us of that is the host's
-// call; it was 9.3).  Three matrices in turn; one again and again, the power
-// law takes 171 us and the 5-point stencil 31.6 (see form_of).  The double
-// sums gave the band 2.5 of its 12 us.
+// call; it was 9.3).  The double sums gave the band 2.5 of its 12 us.
 constexpr int kBack = kWave;
 
 // Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
@@ -2182,12 +2180,18 @@ int check_call(sss_plan p, const int32_t *row_ptr, const int32_t *col, const voi
 // FP32 320 MB 63.5 / 61.8, 455 MB 27-point stencil 89.1 / 85.3.  Three in turn
 // streaming is ahead from 87 MB on (160 MB 5-point stencil 34.5 / 31.9, 322 MB
 // FEM band 63.5 / 61.4), behind below (78 MB power law 38.4 / 42.1); a program
-// that iterates has one.
-constexpr int64_t kStreamBytes = 300000000;
+// that iterates has one.  Where x is 8 MB or more, twice an XCD's L2, the
+// misses of the gathers hide where the matrix comes from, and streaming is
+// ahead from 87 MB on either way (one again and again / three in turn, cached
+// against streamed: power law 1M rows 167 / 181, 171 / 171; Poisson 1M rows 108
+// / 110, 103 / 104; dense rows 1M 71.0 / 72.9, 67.7 / 69.3; 5-point stencil
+// 31.6 / 34.4, 31.8 / 31.9).
+constexpr int64_t kStreamBytes = 300000000, kStreamX = 8000000, kStreamBytesX = 87000000;
 Form form_of(int64_t m, int64_t n, int64_t nnz, int dt, int64_t n_max) {
   if (n_max * (int64_t)y_size(dt) > 0xfffffff0ll) return kWide;
   const int64_t value = dt == SSS_F64 ? 8 : (dt == SSS_F32 ? 4 : 2);
-  return nnz * (4 + value) + 4 * m + (m + n) * (int64_t)y_size(dt) >= kStreamBytes ? kStreamed : kCached;
+  const int64_t from = n_max * (int64_t)y_size(dt) >= kStreamX ? kStreamBytesX : kStreamBytes;
+  return nnz * (4 + value) + 4 * m + (m + n) * (int64_t)y_size(dt) >= from ? kStreamed : kCached;
 }
 
 // The kernels' view of a single-matrix plan and the caller's arrays.
