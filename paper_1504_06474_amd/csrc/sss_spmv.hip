@@ -788,28 +788,30 @@ __device__ __forceinline__ int slot_need(const int32_t *__restrict__ rp, int32_t
   return back | (int)imin64((int64_t)(r_next < m ? r_next + 1 : m) - r, kSpanMax) << 8;
 }
 
-// Buffer loads: the descriptor's range is in bytes, checked per 32-bit word.
+// Buffer loads: the descriptor's range is in bytes, checked per 32-bit word
+// against the vector offset.  The instruction's scalar offset is not part of
+// that check, so it stays 0: what moves along an array moves the descriptor.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format
 __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRsrcWord3);
 }
 template <typename T, bool NT = false>
-__device__ __forceinline__ T buffer_load(rsrc_t r, int voffset, int soffset) {
+__device__ __forceinline__ T buffer_load(rsrc_t r, int voffset) {
   constexpr int kAux = NT ? 2 : 0;
   static_assert(sizeof(T) == 2 || sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one load");
   T v;
   if constexpr (sizeof(T) == 2) {
-    const auto w = __builtin_amdgcn_raw_buffer_load_b16(r, voffset, soffset, kAux);
+    const auto w = __builtin_amdgcn_raw_buffer_load_b16(r, voffset, 0, kAux);
     __builtin_memcpy(&v, &w, 2);
   } else if constexpr (sizeof(T) == 4) {
-    const auto w = __builtin_amdgcn_raw_buffer_load_b32(r, voffset, soffset, kAux);
+    const auto w = __builtin_amdgcn_raw_buffer_load_b32(r, voffset, 0, kAux);
     __builtin_memcpy(&v, &w, 4);
   } else if constexpr (sizeof(T) == 8) {
-    const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, voffset, soffset, kAux);
+    const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, voffset, 0, kAux);
     __builtin_memcpy(&v, &w, 8);
   } else {
-    const auto w = __builtin_amdgcn_raw_buffer_load_b128(r, voffset, soffset, kAux);
+    const auto w = __builtin_amdgcn_raw_buffer_load_b128(r, voffset, 0, kAux);
     __builtin_memcpy(&v, &w, 16);
   }
   return v;
@@ -825,17 +827,17 @@ __device__ __forceinline__ T buffer_load(rsrc_t r, int voffset, int soffset) {
 template <int DT> constexpr int fused_group() { return DT == SSS_F64 ? 2 : 4; }
 
 template <int N, bool NT>
-__device__ __forceinline__ void load_words(rsrc_t r, int voffset, int soffset, uint32_t *w) {
+__device__ __forceinline__ void load_words(rsrc_t r, int voffset, uint32_t *w) {
   if constexpr (N == 1) {
-    w[0] = buffer_load<uint32_t, NT>(r, voffset, soffset);
+    w[0] = buffer_load<uint32_t, NT>(r, voffset);
   } else if constexpr (N == 2) {
-    const v2u v = buffer_load<v2u, NT>(r, voffset, soffset);
+    const v2u v = buffer_load<v2u, NT>(r, voffset);
     w[0] = v.x; w[1] = v.y;
   } else {
     static_assert(N % 4 == 0, "1, 2 or quadruples of words");
 #pragma unroll
     for (int i = 0; i < N; i += 4) {
-      const v4u v = buffer_load<v4u, NT>(r, voffset + 4 * i, soffset);
+      const v4u v = buffer_load<v4u, NT>(r, voffset + 4 * i);
       w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
     }
   }
@@ -849,12 +851,13 @@ struct Tile {
   static constexpr int VW = G * VB / 4;  // words of values per row
   uint32_t c[W], v[R * VW];
 
+  // rc, rv: descriptors that begin with the tile
   template <bool NT>
-  __device__ __forceinline__ void load(rsrc_t rc, rsrc_t rv, int t, int lane) {
+  __device__ __forceinline__ void load(rsrc_t rc, rsrc_t rv, int lane) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      load_words<G, NT>(rc, lane * G * 4 + r * kWave * G * 4, t * W * kWave * 4, &c[r * G]);
-      load_words<VW, NT>(rv, lane * G * VB + r * kWave * G * VB, t * W * kWave * VB, &v[r * VW]);
+      load_words<G, NT>(rc, lane * G * 4 + r * kWave * G * 4, &c[r * G]);
+      load_words<VW, NT>(rv, lane * G * VB + r * kWave * G * VB, &v[r * VW]);
     }
   }
   __device__ __forceinline__ uint32_t column(int i) const { return c[i]; }
@@ -1077,23 +1080,29 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   uint32_t *dflag = mask + S * WPT;
 
   // ---- the loads that need nothing
-  const rsrc_t rc = make_rsrc(a.col + b0, (uint32_t)left * 4u);
-  // (whole words: an odd number of BF16 values ends inside one)
-  const rsrc_t rv = make_rsrc(static_cast<const val_t *>(a.val) + b0, ((uint32_t)left * sizeof(val_t) + 3u) & ~3u);
   const rsrc_t rx = make_rsrc(a.x, 0xffffffffu);
   auto gather = [&](uint32_t c) {
     if constexpr (FORM == kWide) return static_cast<const x_t *>(a.x)[c];
-    else return buffer_load<x_t>(rx, (int)(c * (uint32_t)sizeof(x_t)), 0);
+    else return buffer_load<x_t>(rx, (int)(c * (uint32_t)sizeof(x_t)));
   };
   constexpr bool NT = FORM != kCached;
   Tile<DT, W> cur, next;
-  cur.template load<NT>(rc, rv, 0, lane);
+  // tile t of the bunch; nothing of a tile past the bunch's end (rest = 0)
+  auto load_tile = [&](Tile<DT, W> &tile, int t) {
+    const uint32_t rest = (uint32_t)max(left - t * WT, 0);
+    // (whole words: an odd number of BF16 values ends inside one)
+    tile.template load<NT>(make_rsrc(a.col + (b0 + t * WT), rest * 4u),
+                           make_rsrc(static_cast<const val_t *>(a.val) + (b0 + t * WT),
+                                     (rest * (uint32_t)sizeof(val_t) + 3u) & ~3u),
+                           lane);
+  };
+  load_tile(cur, 0);
   const int back_off = lane - (kBack - back_n);  // lanes below 0: outside
   const uint32_t back_c =
-      buffer_load<uint32_t>(make_rsrc(a.col + (b0 - back_n), (uint32_t)back_n * 4u), back_off * 4, 0);
+      buffer_load<uint32_t>(make_rsrc(a.col + (b0 - back_n), (uint32_t)back_n * 4u), back_off * 4);
   const val_t back_v = buffer_load<val_t>(
       make_rsrc(static_cast<const val_t *>(a.val) + (b0 - back_n), (uint32_t)back_n * sizeof(val_t)),
-      back_off * (int)sizeof(val_t), 0);
+      back_off * (int)sizeof(val_t));
   // A bunch without a row from the plan searches for it here, ahead of the
   // gathers: loads return in order, so behind them every round of the search
   // would wait for tile 0's gathers first.  Unbound products, us behind /
@@ -1104,11 +1113,11 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   const int span = known ? need >> 8 : m - r0;
   const bool ahead = !known || span < kSpanMax;
   const rsrc_t rr = make_rsrc(a.row_ptr + r0, ahead ? (uint32_t)(min(span, 2 * kWave - 1) + 1) * 4u : 0u);
-  const int rows0 = buffer_load<int>(rr, lane * 4, 0);
-  const int rows1 = buffer_load<int>(rr, lane * 4 + kWave * 4, 0);
+  const int rows0 = buffer_load<int>(rr, lane * 4);
+  const int rows1 = buffer_load<int>(rr, lane * 4 + kWave * 4);
   const int past_span = a.row_ptr[ahead ? imin64((int64_t)r0 + span, m) : 0];
   const int second_row = a.row_ptr[1];
-  if (S > 1) next.template load<NT>(rc, rv, 1, lane);
+  if (S > 1) load_tile(next, 1);
 
   // ---- the gathers of tile 0
   x_t xv[W];
@@ -1141,7 +1150,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   // entries rbase .. rbase + 63, INT_MAX past the last
   auto entries = [&](int rbase) {
     const int n = min(last - rbase + 1, kWave);
-    const int v = buffer_load<int>(make_rsrc(rp + rbase, n > 0 ? (uint32_t)n * 4u : 0u), lane * 4, 0);
+    const int v = buffer_load<int>(make_rsrc(rp + rbase, n > 0 ? (uint32_t)n * 4u : 0u), lane * 4);
     return lane < n ? v : INT_MAX;
   };
   // one chunk of 64 rows: p = rp[r], after = the entry past the chunk (a value
@@ -1253,7 +1262,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     cur = next;
 #pragma unroll
     for (int i = 0; i < W; ++i) xv[i] = gather(cur.column(i));
-    if (t + 2 < tiles) next.template load<NT>(rc, rv, t + 2, lane);
+    if (t + 2 < tiles) load_tile(next, t + 2);
     (void)u.sum_tile(t, b0 + (t + 1) * WT, pr);
   }
   products(tiles - 1);
