@@ -6,6 +6,11 @@
 
 #include "sss.h"
 
+// The bytes that range-checked loads may read of `count` values of `size`
+// bytes each: whole 32-bit words that end with the last value or, where an odd
+// number of 16-bit values ends inside a word, one value before it.
+constexpr uint32_t value_range(uint32_t count, uint32_t size) { return count * size & ~3u; }
+
 // sss_csr_spmv_execute in double precision for a square matrix, with partial
 // sums of x . y beside it: *dots (device) holds *n_dots of them, in a fixed
 // order, until the plan's next call.  *n_dots = 0: this plan's product does

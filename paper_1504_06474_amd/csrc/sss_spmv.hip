@@ -1090,10 +1090,9 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   // tile t of the bunch; nothing of a tile past the bunch's end (rest = 0)
   auto load_tile = [&](Tile<DT, W> &tile, int t) {
     const uint32_t rest = (uint32_t)max(left - t * WT, 0);
-    // (whole words: an odd number of BF16 values ends inside one)
     tile.template load<NT>(make_rsrc(a.col + (b0 + t * WT), rest * 4u),
                            make_rsrc(static_cast<const val_t *>(a.val) + (b0 + t * WT),
-                                     (rest * (uint32_t)sizeof(val_t) + 3u) & ~3u),
+                                     value_range(rest, sizeof(val_t))),
                            lane);
   };
   load_tile(cur, 0);
@@ -1241,23 +1240,32 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
 
   // ---- the tiles
   prod_t pr[W];
-  auto products = [&](int t) {
+  auto products = [&](auto last_tile) {
     prod_t av[W], bv[W];
 #pragma unroll
     for (int i = 0; i < W; ++i) {
       av[i] = cur.value(i);
       bv[i] = (prod_t)xv[i];
     }
-    if (left - t * WT < WT) {  // the matrix's last tile: entries past its end add 0
+    const int rest = left - (tiles - 1) * WT;
+    if (decltype(last_tile)::value && rest < WT) {  // the matrix's last tile: entries past its end add 0
 #pragma unroll
       for (int i = 0; i < W; ++i)
-        if (Tile<DT, W>::offset(i, lane) >= left - t * WT) av[i] = bv[i] = (prod_t)0;
+        if (Tile<DT, W>::offset(i, lane) >= rest) av[i] = bv[i] = (prod_t)0;
+      if constexpr (DT == SSS_BF16) {
+        if (left & 1) {  // (the value that its load's range leaves out)
+          const prod_t odd = scalar_val(static_cast<const val_t *>(a.val), bS - 1);
+#pragma unroll
+          for (int i = 0; i < W; ++i)
+            if (Tile<DT, W>::offset(i, lane) == rest - 1) av[i] = odd;
+        }
+      }
     }
     Tile<DT, W>::store(av, bv, reinterpret_cast<prod_t *>(u.part), lane, pr);
   };
   double tail = 0.0;
   for (int t = 0; t + 1 < tiles; ++t) {
-    products(t);
+    products(std::false_type{});
     u.load_rows(t);
     cur = next;
 #pragma unroll
@@ -1265,7 +1273,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     if (t + 2 < tiles) load_tile(next, t + 2);
     (void)u.sum_tile(t, b0 + (t + 1) * WT, pr);
   }
-  products(tiles - 1);
+  products(std::true_type{});
   u.load_rows(tiles - 1);
   tail = u.sum_tile(tiles - 1, bS, pr);
 

@@ -31,3 +31,28 @@ def test_no_scalar_offset(tmp_path):
     # buffer_load_x  dst, vaddr, s[descriptor], soffset ...
     bad = [i for i in loads if re.search(r"s\[\d+:\d+\], (\S+)", i).group(1) != "0"]
     assert not bad, bad[:5]
+
+
+RANGES = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "sss_internal.h"
+int main() {
+  for (unsigned size : {2u, 4u, 8u})
+    for (unsigned count = 0; count <= 3000; ++count) {
+      const unsigned r = value_range(count, size), end = count * size;
+      if (r > end || r % 4 || r + (size == 2 && count % 2 ? 2 : 0) != end) return std::printf("%u x %u: %u\n", count, size, r), 1;
+    }
+}
+"""
+
+
+def test_ranges_end_with_the_values(tmp_path):
+    """Never a byte past the last value, and every value but an odd last one of
+    16 bits."""
+    src, exe = tmp_path / "r.cpp", tmp_path / "r"
+    src.write_text(RANGES)
+    csrc = os.path.join(build.HERE, "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, "-I", os.path.join(build.ROOT, "include"), str(src), "-o", str(exe)],
+                   check=True)
+    subprocess.run([str(exe)], check=True)

@@ -196,3 +196,23 @@ def test_product_with_dot(grid, W, S, B):
         r = r_new
     for got, want in zip(vec, (x, r, p)):
         assert np.linalg.norm(got.cpu().numpy() - want) <= 1e-11 * max(np.linalg.norm(want), np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("W", [4, 8, 16])
+def test_bf16_odd_last_value(W):
+    """An odd number of BF16 values ends inside a 32-bit word: every place of
+    the last value in a tile's lanes, one tile and more; val ends where its
+    array does."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note(f"[gpu-test] bf16 odd W={W}")
+    tile = 64 * W
+    for nnz in [1, 3, 5, 7, 9, 63, 65, tile - 1, tile + 1, 2 * tile - 1, 2 * tile + 3, 3 * tile + tile // 2 + 5]:
+        A, x = csr_from_lengths([2] * (nnz // 2) + [nnz % 2], 4000, seed=nnz)
+        A.val[-1], x[A.col[-1]] = 3.0, 2.0
+        rp, col, v, xx, ve, xe = to_dev_precision(A, x, "bf16")
+        want = oracle.spmv(A.row_ptr, A.col, ve, xe)
+        for S in (1, 3):
+            for bind in (True, False):
+                plan = sss.Plan(A.m, A.n, A.nnz, dtype=torch.bfloat16, W=W, S=S, row_ptr=rp, bind_rows=bind)
+                assert_exact(run(plan, rp, col, v, xx, A.m, torch.float32).double().numpy(), want)
