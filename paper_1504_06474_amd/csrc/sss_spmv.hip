@@ -272,6 +272,16 @@ __device__ __forceinline__ double wave_sum_tree(double v) {
   return v;
 }
 
+// Where lanes of a wavefront hand LDS words to each other, or a word changes its
+// type (products of prod_t, then partials in double, in the same words).  One
+// wavefront owns the words and its LDS operations run in order, so nothing
+// waits; the fence keeps the compiler from moving accesses of different lanes
+// or types, which it may take for independent, past each other.
+__device__ __forceinline__ void lds_handover() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- stage 1
 
 // What a bunch leaves for stage 2.  One record, stored by one instruction:
@@ -443,16 +453,14 @@ __device__ __forceinline__ void products_out(const P (&av)[W], const P (&xv)[W],
 template <int W, typename P>
 __device__ __forceinline__ void products_read(const P *buf, int lane, P (&pr)[W]) {
   constexpr int CH = 16 / (int)sizeof(P);
-  // one wavefront owns buf and its LDS operations run in order; the
-  // fence keeps the compiler from moving a read above another lane's write
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
 #pragma unroll
   for (int k = 0; k < W / CH; ++k) {
     const P *src = buf + tr_chunk<P, W>((lane * W) / CH + k) * CH;
 #pragma unroll
     for (int e = 0; e < CH; ++e) pr[k * CH + e] = src[e];
   }
+  lds_handover();  // the same words take the partials next
 }
 
 template <int DT, int W, typename P>
@@ -510,7 +518,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
   // ---- descriptor, tile start rows, dirty tiles: one pass over the rows
   for (int i = lane; i < S * WPT; i += kWave) mask[i] = 0u;
   if (lane == 0) *dflag = 0u;
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
 
   const int my_b = (int)imin64(tb * SWT + (int64_t)min(lane, S) * WT, nnz);
   int my_count = 0;  // lane t <= S: rows r >= r0 with rp[r] <= b_t
@@ -553,7 +561,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     const int p_last = lane_value(p, kWave - 1);
     if (!(p_last <= bS && rbase + (kWave - 1) < m)) break;
   }
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
   const uint32_t dirty_bits = *dflag;
   const int my_start = (lane <= S) ? r0 + my_count - 1 : 0;
 
@@ -659,7 +667,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
       c.prepend(carry);
       part[cnt - 1] = seen ? acc.value() : c.value();
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
 
     // ---- coalesced store of the compact partials to y[start + q] (the
     // first with the transmitter added).  Two partials stay in double
@@ -683,7 +691,7 @@ __device__ __forceinline__ void stage1_bunch(const MatCtx &a, const int64_t tb, 
     if (start == r0) sync_v = p0;
     transmitter = ends_mid ? plast : 0.0;
     if (!has_next && ends_mid && !(cnt == 1 && start == r0) && lane == 0) a.state[tb].tail_val = plast;
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
 
     // ---- dirty tile: label it for the re-arrangement, in this bunch's own
     // speculator slots (no global counter)
@@ -901,8 +909,7 @@ template <int DT, int W, typename prod_t>
 __device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, double *lds, int lane) {
   prod_t *buf = reinterpret_cast<prod_t *>(lds);
   buf[lane] = product;
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
   constexpr int kFirst = kWave - kBack / W;  // the first lane whose entries are among the last kBack
   AccD acc;
   acc.zero();
@@ -910,8 +917,7 @@ __device__ __forceinline__ double back_sum(prod_t product, int rs, int b0, doubl
 #pragma unroll
     for (int i = 0; i < W; ++i) acc.add(buf[(lane - kFirst) * W + i]);
   }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
   const int head = kFirst + (rs - (b0 - kBack)) / W;
   AccD inc = acc;
   int f = lane == head ? 1 : 0;
@@ -1002,7 +1008,7 @@ struct Bunch {
       c.prepend(carry);
       part[cnt - 1] = seen ? acc.value() : c.value();
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
 
     if (dirty) {
       // rows start + 1 .. stop - 1: the k-th non-empty one takes partial k
@@ -1049,7 +1055,7 @@ struct Bunch {
     const double plast = cnt == 1 ? p0 : part[cnt - 1];
     if (start == r0) sync_v = p0;
     transmitter = ends_mid ? plast : 0.0;
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
     // the tail, where this is the bunch's last tile: what its last row holds
     // of it, unless that row is the bunch's first (then the synchronizer's)
     return ends_mid && !(cnt == 1 && start == r0) ? plast : 0.0;
@@ -1127,7 +1133,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   // ---- descriptor, tile start rows, dirty tiles: one pass over the rows
   for (int i = lane; i < S * WPT; i += kWave) mask[i] = 0u;
   if (lane == 0) *dflag = 0u;
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
 
   const int32_t *__restrict__ rp = a.row_ptr;
   const int my_b = b0 + min(min(lane, S) * WT, left);
@@ -1196,7 +1202,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
       next_p = p2;
     }
   }
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
 
   Bunch<DT, W, DOT> u;
   u.rp = rp;
@@ -1777,8 +1783,7 @@ __device__ __forceinline__ void fixup_dirty(const MatCtx &a, const int64_t tb, Y
     // only the compiler must keep the order (no wait for memory); every load
     // of y above has returned before its value reached LDS, so the stores
     // below cannot overtake them, and other tiles touch other rows
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
     int base = 0;
     for (int rb = start + 1; rb < stop; rb += kWave) {
       if (rb != start + 1) {
@@ -1793,8 +1798,7 @@ __device__ __forceinline__ void fixup_dirty(const MatCtx &a, const int64_t tb, Y
       if (in) y[r] = ne ? slots[min(base + before, max(n_slots - 1, 0))] : (YT)0;
       base += __popcll(bal);
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    lds_handover();
   }
 }
 
@@ -1838,8 +1842,7 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
     s_val[kWave + lane] = tail_v;
   }
   // one wavefront owns `lds` and its LDS operations run in order
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
   const int prev = wave_prev(idx, before_chunk);
   const bool head = valid && (tb == 0 || prev != idx);
   const bool is_long = head && (tb + kShortRun < nb) && (s_idx[lane + kShortRun] == idx);
@@ -1878,8 +1881,7 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
     }
   }
   // the staged entries are read before the wavefront's next use of `lds`
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
 }
 
 // (2b) a bound plan whose row_ptr was rewritten in place: the dirty bunches
