@@ -1062,12 +1062,27 @@ struct Bunch {
   }
 };
 
+// The rows before the first non-empty one are empty and in no tile: zero those
+// of this wavefront's share of y, where rp[1] = 0.  (A row_ptr read per 64 rows
+// made the wavefront wait for each: 4M such rows before 1,000 rows of 5
+// entries, on two bunches, took 9.9 ms a product; the stores alone 0.96 ms, and
+// shared out over more wavefronts than bunches, see kLeadingRows, 20 us.)
+template <typename YT>
+__device__ __forceinline__ void zero_leading(const int32_t *__restrict__ rp, YT *__restrict__ y, int m, int64_t share,
+                                             int64_t shares, int lane) {
+  const int64_t lo = (int64_t)m * share / shares, hi = (int64_t)m * (share + 1) / shares;
+  if (lo >= hi || rp[lo + 1] != 0) return;
+  const int64_t end = rp[hi] == 0 ? hi : (int64_t)wave_rightmost(rp, m, 0, lane);
+  for (int64_t r = lo + lane; r < end; r += kWave) y[r] = (YT)0;
+}
+
 // tb, the bunch; brow, its first row at plan time or -1; need, its slot_need
-// (0 without a plan): the same in every lane.  Returns the lane's part of the
-// bunch's dot product (DOT).
+// (0 without a plan); share of shares, its part of the leading rows: the same
+// in every lane.  Returns the lane's part of the bunch's dot product (DOT).
 template <int DT, int W, Form FORM, bool DOT = false>
 __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, const int brow, const int need,
-                                            uint32_t *lds_wave, const int lane) {
+                                              const int64_t share, const int64_t shares, uint32_t *lds_wave,
+                                              const int lane) {
   using val_t = typename VT<DT>::val_t;
   using x_t = typename VT<DT>::x_t;
   using y_t = typename VT<DT>::y_t;
@@ -1287,11 +1302,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     y_store((y_t)(before + u.sync_v), &u.y[r0]);
     if constexpr (DOT) u.dot += u.x[r0] * (before + u.sync_v);
   }
-  // rows before the first non-empty one: those of this bunch's share of y
-  if (second_row == 0) {
-    const int64_t hi = (int64_t)m * (tb + 1) / a.n_bunches;
-    for (int64_t r = (int64_t)m * tb / a.n_bunches + lane; r < hi && rp[r + 1] == 0; r += kWave) u.y[r] = (y_t)0;
-  }
+  if (second_row == 0) zero_leading(rp, u.y, m, share, shares, lane);
   if (a.state) {  // (a batch that needs no carries keeps none)
     const uint64_t sv = (uint64_t)__double_as_longlong(u.sync_v), tv = (uint64_t)__double_as_longlong(tail);
     const uint32_t words[6] = {(uint32_t)sv, (uint32_t)(sv >> 32), (uint32_t)tv, (uint32_t)(tv >> 32), (uint32_t)r0,
@@ -1310,15 +1321,16 @@ __global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = wave_in_block();
   const int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
-  int4 slot = make_int4((int)g, -1, 0, 0);
-  if (a.slots) {
-    if (g >= a.n_slots) return;
-    slot = uniform_load(a.slots + g);
-    if (slot.x < 0) return;
-  } else if (g >= a.n_bunches) {
+  const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
+  int4 slot = make_int4(g < a.n_bunches ? (int)g : -1, -1, 0, 0);
+  if (a.slots) slot.x = -1;
+  if (a.slots && g < a.n_slots) slot = uniform_load(a.slots + g);
+  if (slot.x < 0) {  // no bunch
+    using y_t = typename VT<DT>::y_t;
+    if (a.row_ptr[1] == 0) zero_leading(a.row_ptr, static_cast<y_t *>(a.y), a.m, g, waves, lane);
     return;
   }
-  fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, lds_words + wid * stage1_lds_words(W, a.S), lane);
+  fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, g, waves, lds_words + wid * stage1_lds_words(W, a.S), lane);
 }
 
 // The same with the partial sums of x . y, one per workgroup, for bound FP64
@@ -1336,7 +1348,7 @@ __global__ __launch_bounds__(256) void sss_fused_dot(MatCtx a, double *__restric
   if (g < a.n_slots) {
     const int4 slot = uniform_load(a.slots + g);
     if (slot.x >= 0)
-      dot = fused_bunch<SSS_F64, W, FORM, true>(a, slot.x, slot.y, slot.z,
+      dot = fused_bunch<SSS_F64, W, FORM, true>(a, slot.x, slot.y, slot.z, slot.x, a.n_bunches,
                                                 lds_words + wid * stage1_lds_words(W, a.S), lane);
   }
   dot = wave_sum_tree(dot);
@@ -1700,7 +1712,7 @@ __global__ __launch_bounds__(256) void sss_fused_batch(BatchArgs b) {
   int4 bi;
   MatCtx a;
   batch_entry(b, g, bi, a);
-  fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, lds_wave, lane);
+  fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, bi.z, a.n_bunches, lds_wave, lane);
 }
 
 // The same work as a persistent grid (batch_persistent plans): as many
@@ -1722,7 +1734,7 @@ __global__ __launch_bounds__(256) void sss_fused_batch_persistent(BatchArgs b) {
     int4 bi;
     MatCtx a;
     batch_entry(b, g, bi, a);
-    fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, lds_wave, lane);
+    fused_bunch<DT, W, FORM>(a, bi.z, bi.y, bi.w, bi.z, a.n_bunches, lds_wave, lane);
   }
 }
 
@@ -2274,6 +2286,11 @@ int launch_call_order(sss_plan p, const int32_t *row_ptr, MatCtx &a, hipStream_t
   return SSS_OK;
 }
 
+// Rows per wavefront from which on the fused kernel gets wavefronts without a
+// bunch, which only take their share of the leading rows (see zero_leading).
+// Matrices with 0.6 entries per row and more (SWT = 2,560) have enough bunches.
+constexpr int64_t kLeadingRows = 4096;
+
 // Stage 1 alone (`split`), or the fused kernel.  (nnz = 0: y is zeroed here.)
 int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const void *val, const void *x, void *y,
                   bool split, hipStream_t stream) {
@@ -2295,7 +2312,9 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
     const int rc = launch_call_order(p, row_ptr, a1, stream);
     if (rc != SSS_OK) return rc;
   }
-  const int64_t blocks1 = ((a1.slots ? a1.n_slots : p->n_bunches) + p->B - 1) / p->B;
+  int64_t waves1 = a1.slots ? a1.n_slots : p->n_bunches;
+  if (!split) waves1 = std::max(waves1, p->m / kLeadingRows);
+  const int64_t blocks1 = (waves1 + p->B - 1) / p->B;
   const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
   hipLaunchKernelGGL(k1, dim3((unsigned)blocks1), dim3(p->B * kWave), lds1, stream, a1);
   SSS_HIP(hipGetLastError());
