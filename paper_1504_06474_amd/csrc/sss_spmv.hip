@@ -192,6 +192,10 @@ __device__ __forceinline__ int wave_prev(int v, int first) {
 // this wavefront's index in its workgroup, in a scalar register (what hangs
 // on it -- the bunch, its bounds and addresses -- then stays scalar too)
 __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
+// how many of the lanes before this one are in `mask` (the same in every lane)
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
 // v of lane `l`, for a lane index the same in every lane
 __device__ __forceinline__ int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 
@@ -1019,23 +1023,34 @@ struct Bunch {
         y_store((y_t)(part[0] + tx), &y[start]);
         if constexpr (DOT) dot += x_row * (part[0] + tx);
       }
-      int k = 0;
-      for (int c = (start + 1 - r0) / kWave; r0 + c * kWave < stop; ++c) {
+      int k = 1;
+      auto store_rows = [&](int r, bool in, uint64_t filled) {
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(filled);
+        const double v = part[min(k + lanes_below(filled), WT - 1)];
+        if (in) y_store(mine ? (y_t)v : (y_t)0, &y[r]);
+        if constexpr (DOT)
+          if (mine) dot += x[r] * v;
+        k += __popcll(filled);
+      };
+      int c = (start + 1 - r0) / kWave;
+      for (; c < kWave && r0 + c * kWave < stop; ++c) {
         const int r = r0 + c * kWave + lane;
         const bool in = r > start && r < stop;
-        uint64_t filled;
-        if (c < kWave) {
-          filled = ((uint64_t)(uint32_t)lane_value((int)(filled_rows >> 32), c) << 32) |
-                   (uint32_t)lane_value((int)(uint32_t)filled_rows, c);
-          filled &= __ballot(in);
-        } else {
-          filled = __ballot(in && rp[r] != rp[r + 1]);
+        const uint64_t filled = ((uint64_t)(uint32_t)lane_value((int)(filled_rows >> 32), c) << 32) |
+                                (uint32_t)lane_value((int)(uint32_t)filled_rows, c);
+        store_rows(r, in, filled & __ballot(in));
+      }
+      // (the next chunk's entries of row_ptr go out before this one's rows)
+      if (r0 + c * kWave < stop) {
+        int r = r0 + c * kWave + lane;
+        int p = rp[min(r, m)], q = rp[min(r + 1, m)];
+        for (; r - lane < stop; r += kWave) {
+          const int p_next = rp[min(r + kWave, m)], q_next = rp[min(r + kWave + 1, m)];
+          const bool in = r > start && r < stop;
+          store_rows(r, in, __ballot(in && p != q));
+          p = p_next;
+          q = q_next;
         }
-        const int rank = k + 1 + __popcll(filled & ((1ull << lane) - 1ull));
-        if (in) y_store((filled >> lane) & 1ull ? (y_t)part[min(rank, WT - 1)] : (y_t)0, &y[r]);
-        if constexpr (DOT)
-          if ((filled >> lane) & 1ull) dot += x[r] * part[min(rank, WT - 1)];
-        k += __popcll(filled);
       }
       if (lane == 0 && speculator)
         speculator[__popc(dirty_bits & ((1u << t) - 1u))] = make_int4(start, stop, first_tile + t, 0);
@@ -1186,7 +1201,9 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
       const int off = p - b0;
       atomicOr(&mask[off >> 5], 1u << (off & 31));
     }
-    if (r < m && q == p && p > b0 && p <= bS) atomicOr(dflag, 1u << ((p - b0 - 1) / WT));
+    // (of empty rows in a run, which all begin at p, the chunk's first marks the
+    // tile: the wavefront takes its lanes of one address one after another)
+    if (r < m && q == p && wave_prev(p, -1) != p && p > b0 && p <= bS) atomicOr(dflag, 1u << ((p - b0 - 1) / WT));
     const uint64_t filled = __ballot(q != p);
     if (lane == (rbase - r0) / kWave) filled_rows = filled;
     for (int t = 0; t <= S; ++t) {

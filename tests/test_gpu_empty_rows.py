@@ -60,3 +60,26 @@ def test_leading_rows_take_their_stores_time():
     note("[gpu-test] leading rows, time")
     for rows in (1, 1000):
         assert check([0] * 4_000_000 + [5] * rows, 1000) < 3.0
+
+
+def test_rows_between_and_behind_take_one_pass():
+    """A million empty rows inside a tile and behind the last entry: one
+    wavefront reads their row_ptr twice (to count, to store), 64 a round, each
+    round about a load's latency: 15 ms, where marking the tile 64 times a
+    round and waiting for the stores as well made it 44."""
+    note("[gpu-test] empty rows inside a tile, time")
+    few = [3] * 20 + [0, 0, 0, 1]
+    assert check(few * 20 + [0] * 1_000_000 + few * 20, 1000) < 25.0
+    assert check(few * 20 + [0] * 1_000_000, 1000) < 25.0
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32", "bf16"])
+def test_runs_of_empty_rows(kind):
+    """Runs of every length around a chunk of 64 rows, one after another and at
+    the ends of tiles, over more than the 64 chunks a bunch keeps."""
+    note(f"[gpu-test] runs of empty rows {kind}")
+    lens = []
+    for run in list(range(0, 5)) + list(range(60, 70)) + list(range(125, 131)) + [700, 64 * 70, 3, 64 * 3]:
+        lens += [0] * run + [1, 2] + [0] * run + [61]
+    for W, S in ((4, 1), (8, 2), (16, 3)):
+        check(lens, 500, kind, W=W, S=S)
