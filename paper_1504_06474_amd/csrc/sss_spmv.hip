@@ -2097,6 +2097,7 @@ struct sss_plan_s {
   int4 *slots = nullptr;         // bind_rows plans: see MatCtx::slots
   uint32_t *order_hist = nullptr;
   double *dots = nullptr;        // bind_rows FP64 plans: see sss_fused_dot
+  bool ordered = false;          // bind_rows plans: slots are in column order
   bool call_order = false;       // plans without bind_rows: every call makes bunch_row and slots, see orders_calls
   int64_t n_slots = 0;
   int32_t *dbg_start = nullptr;
@@ -2586,6 +2587,7 @@ int plan_slots(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t s) {
                          nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
       SSS_HIP(hipGetLastError());
       p->n_slots = n_slots;
+      p->ordered = true;
       return SSS_OK;
     }
   }
@@ -2705,7 +2707,11 @@ int sss_execute_dot(sss_plan p, const int32_t *row_ptr, const int32_t *col, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Form form = form_of(p->m, p->n, p->nnz, p->dt, p->n);
   const int64_t blocks = (p->n_slots + p->B - 1) / p->B;
-  if (!p->bind_rows || p->dt != SSS_F64 || p->m != p->n || p->carries || p->debug || form == kWide || blocks > kMaxDots)
+  // (in column order, the bunches of a workgroup, and so the bits of its sum,
+  // depend on the atomics that made the order: another plan of the same matrix
+  // would not repeat them)
+  if (!p->bind_rows || p->dt != SSS_F64 || p->m != p->n || p->carries || p->debug || p->ordered || form == kWide ||
+      blocks > kMaxDots)
     return launch(p, row_ptr, col, val, x, y, s);
   const int rc = check_call(p, row_ptr, col, val, x, y);
   if (rc != SSS_OK) return rc;

@@ -91,3 +91,27 @@ def test_column_order_per_call_exact():
             call(*args, y)
             assert_exact(y.cpu().numpy(), expect)
     sss.csr_spmv_cache_clear()
+
+
+def test_cg_repeats_over_plans_in_column_order():
+    """Within a bin the column order is that of atomics.  CG's dot products
+    must not follow it: plans of the same matrix give the same bits.  Rows of
+    one whole bunch each, which cross no boundary, among empty ones."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note("[gpu-test] column order, CG repeats")
+    rng = np.random.default_rng(9)
+    lens = np.zeros(N, dtype=np.int64)
+    lens[rng.choice(N, 2900, replace=False)] = 256
+    A, b = csr_from_lengths(lens, N, seed=1, int_valued=False)
+    rp, col, v, db = to_dev(A, b)
+    seen = None
+    for _ in range(6):
+        plan = sss.Plan(N, N, A.nnz, W=4, S=1, B=1, row_ptr=rp, bind_rows=True)
+        x, r, p, q = (torch.zeros(N, dtype=torch.float64, device="cuda") for _ in range(4))
+        work = torch.zeros(sss.cg_workspace_size() // 8, dtype=torch.float64, device="cuda")
+        sss.cg_start(plan, rp, col, v, db, x, r, p, q, work)
+        sss.cg_iterate(plan, rp, col, v, x, r, p, q, work, 2)
+        if seen is not None:
+            assert torch.equal(x, seen)
+        seen = x
