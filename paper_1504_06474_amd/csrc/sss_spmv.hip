@@ -324,6 +324,8 @@ struct MatCtx {
   int32_t *stale;            // bound plans: set (and never cleared) when stage 1 finds a dirty tile in a
                              // bunch outside dirty_list (row_ptr rewritten in place since plan time)
   int32_t carries;       // fused kernel: a sss_carries launch follows and completes the long crossing rows
+  int32_t keep_state;    // fused kernel: every bunch stores its state
+  int32_t *arrivals;     // bound plans, per bunch: see finish_row (zero between launches)
   const int4 *slots;     // bound plans (and calls that made them), per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
                          // dirty_list), slot_need, 0>; NULL: slot = bunch
   int64_t n_slots;
@@ -745,8 +747,8 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 //    that began further back (long crossing rows) are left to sss_carries,
 //    which adds the synchronizer entries in double as stage 2 does; where the
 //    plan saw no such row at plan time (MatCtx::carries = 0) that launch is
-//    left out, and a row_ptr rewritten in place since is served by the same
-//    loads, a wavefront's worth at a time.
+//    left out, and where row_ptr was rewritten in place since, the last of the
+//    row's bunches to finish adds them up (finish_row).
 //  * The leading empty rows are shared out over the bunches.
 //
 // What bounds it is the latency of the loads a wavefront waits for one after
@@ -1091,6 +1093,49 @@ __device__ __forceinline__ void zero_leading(const int32_t *__restrict__ rp, YT 
   for (int64_t r = lo + lane; r < end; r += kWave) y[r] = (YT)0;
 }
 
+// The sum of entries first .. end - 1, all of one row, by one wavefront.
+template <int DT>
+__device__ __forceinline__ double row_part(const MatCtx &a, int first, int end, int lane) {
+  constexpr int U = 4;
+  const auto *val = static_cast<const typename VT<DT>::val_t *>(a.val);
+  const auto *x = static_cast<const typename VT<DT>::x_t *>(a.x);
+  double sum = 0.0;
+  for (int k = first + lane; k - lane < end; k += U * kWave) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int at = min(k + u * kWave, end - 1);
+      v[u] = (double)scalar_val(val, at) * (double)x[a.col[at]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k + u * kWave < end) sum += v[u];
+  }
+  return last_lane(wave_sum_tree(sum));
+}
+
+// A long crossing row [rs, re) in a launch that no sss_carries follows.  Each
+// bunch that begins in it stores its part of the row (the first of them with
+// what lies before it, at most a bunch's worth) and counts itself in; the last
+// to do so adds the parts, in their order whoever is last, and writes y[row].
+// No bunch waits.  Called by a whole wavefront after its state is stored.
+template <typename YT>
+__device__ __forceinline__ void finish_row(const MatCtx &a, int row, int64_t rs, int64_t re, int64_t SWT, int lane) {
+  const int64_t head = (rs + SWT - 1) / SWT, end = (re + SWT - 1) / SWT;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  int before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(&a.arrivals[head], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(before) != (int)(end - head) - 1) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  double sum = 0.0;
+  for (int64_t k = head + lane; k < end; k += kWave) sum += a.state[k].sync_val;
+  sum = wave_sum_tree(sum);
+  if (lane == 0) {
+    static_cast<YT *>(a.y)[row] = (YT)sum;
+    a.arrivals[head] = 0;
+  }
+}
+
 // tb, the bunch; brow, its first row at plan time or -1; need, its slot_need
 // (0 without a plan); share of shares, its part of the leading rows: the same
 // in every lane.  Returns the lane's part of the bunch's dot product (DOT).
@@ -1257,23 +1302,18 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
 
   // ---- does this bunch write y[r0]: it does when the row ends here and is
   // no long crossing row; the row's entries before the bunch are summed here
-  const bool own_first = r0 < m && (int64_t)first_re <= (int64_t)b0 + SWT && (!a.carries || first_rs >= b0 - kBack);
+  const bool is_long = r0 < m && long_crossing(first_rs, first_re, b0, SWT);
+  const bool own_first = r0 < m && !is_long;
   double before = 0.0;
   if (own_first && first_rs < b0) {
     const val_t *__restrict__ val = static_cast<const val_t *>(a.val);
     const x_t *__restrict__ x = static_cast<const x_t *>(a.x);
-    if (first_rs < b0 - kBack) {  // a row further back than the plan knew of
-      double v = 0.0;
-      for (int k = first_rs + lane; k < b0; k += kWave) v += (double)scalar_val(val, k) * (double)x[a.col[k]];
-      before = last_lane(wave_sum_tree(v));
-    } else {
-      prod_t product = back_off >= 0 ? (prod_t)scalar_val(&back_v, 0) * (prod_t)back_x : (prod_t)0;
-      if (b0 - first_rs != back_n) {  // not found at plan time, or row_ptr rewritten since
-        const int k = b0 - kBack + lane;
-        product = k >= first_rs ? (prod_t)scalar_val(val, k) * (prod_t)x[a.col[k]] : (prod_t)0;
-      }
-      before = back_sum<DT, W>(product, first_rs, b0, u.part, lane);
+    prod_t product = back_off >= 0 ? (prod_t)scalar_val(&back_v, 0) * (prod_t)back_x : (prod_t)0;
+    if (b0 - first_rs != back_n) {  // not found at plan time, or row_ptr rewritten since
+      const int k = b0 - kBack + lane;
+      product = k >= first_rs ? (prod_t)scalar_val(val, k) * (prod_t)x[a.col[k]] : (prod_t)0;
     }
+    before = back_sum<DT, W>(product, first_rs, b0, u.part, lane);
   }
 
   // ---- the tiles
@@ -1320,7 +1360,13 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     if constexpr (DOT) u.dot += u.x[r0] * (before + u.sync_v);
   }
   if (second_row == 0) zero_leading(rp, u.y, m, share, shares, lane);
-  if (a.state) {  // (a batch that needs no carries keeps none)
+  const bool shared = is_long && !a.carries && a.arrivals;  // a row that the plan did not know
+  if (shared) {
+    if (first_rs < b0 && first_rs > b0 - SWT) u.sync_v += row_part<DT>(a, first_rs, b0, lane);
+    if constexpr (DOT)
+      if (lane == 0) u.dot += u.x[r0] * u.sync_v;
+  }
+  if (a.keep_state || shared) {  // (a batch that needs no carries keeps none)
     const uint64_t sv = (uint64_t)__double_as_longlong(u.sync_v), tv = (uint64_t)__double_as_longlong(tail);
     const uint32_t words[6] = {(uint32_t)sv, (uint32_t)(sv >> 32), (uint32_t)tv, (uint32_t)(tv >> 32), (uint32_t)r0,
                                u.dirty_bits};
@@ -1329,6 +1375,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     for (int i = 1; i < 6; ++i) w = lane == i ? words[i] : w;
     if (lane < 6) reinterpret_cast<uint32_t *>(a.state + tb)[lane] = w;
   }
+  if (shared) finish_row<y_t>(a, r0, first_rs, first_re, SWT, lane);
   return u.dot;
 }
 
@@ -1695,8 +1742,7 @@ struct BatchArgs {
 __device__ __forceinline__ void batch_entry(const BatchArgs &b, int64_t g, int4 &bi, MatCtx &a) {
   bi = uniform_load(b.bunch_info + g);
   a = uniform_load(b.mats + bi.x);
-  a.carries = b.carries;
-  if (!b.carries) a.state = nullptr;
+  a.carries = a.keep_state = b.carries;
 }
 
 
@@ -2093,6 +2139,7 @@ struct sss_plan_s {
   int32_t *dirty_list = nullptr; // bind_rows plans: the bunches with a dirty tile, found at plan time
   int64_t n_listed = 0;
   int32_t *stale = nullptr;      // bind_rows plans: see MatCtx::stale; the word after it: any long crossing row
+  int32_t *arrivals = nullptr;   // bind_rows plans: see MatCtx::arrivals
   int32_t carries = 1;           // 0: no long crossing row at plan time (see sss_fused), so no second launch
   int4 *slots = nullptr;         // bind_rows plans: see MatCtx::slots
   uint32_t *order_hist = nullptr;
@@ -2124,7 +2171,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // entry per tile), every array 256-byte aligned.
 struct AuxLayout {
   int64_t n_tiles = 0, n_bunches = 0;
-  size_t state = 0, spec = 0, brow = 0, dlist = 0, stale = 0, slots = 0, ohist = 0, dots = 0,
+  size_t state = 0, spec = 0, brow = 0, dlist = 0, stale = 0, slots = 0, ohist = 0, dots = 0, arrivals = 0,
          dstart = 0, ddirty = 0, dheads = 0;
   size_t total = 0;
 };
@@ -2152,6 +2199,7 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug, bool call
   }
   if (bind) {
     L.dots = off; off = align256(off + sizeof(double) * (nb + kXcds * kMaxB));
+    L.arrivals = off; off = align256(off + sizeof(int32_t) * (nb + 1));
   }
   if (debug) {
     L.dstart = off; off = align256(off + sizeof(int32_t) * (nt + 1));
@@ -2170,6 +2218,7 @@ void plan_bind_aux(sss_plan p, const AuxLayout &L, void *base_v) {
   p->aux = base_v;
   p->state = reinterpret_cast<BunchState *>(base + L.state);
   p->speculator = reinterpret_cast<int4 *>(base + L.spec);
+  p->arrivals = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.arrivals) : nullptr;
   p->dots = p->bind_rows ? reinterpret_cast<double *>(base + L.dots) : nullptr;
   p->bunch_row = p->bind_rows || p->call_order ? reinterpret_cast<int32_t *>(base + L.brow) : nullptr;
   p->dirty_list = p->bind_rows ? reinterpret_cast<int32_t *>(base + L.dlist) : nullptr;
@@ -2254,7 +2303,7 @@ MatCtx plan_ctx(sss_plan p, const int32_t *row_ptr, const int32_t *col, const vo
   a.dirty_list = p->dirty_list;
   a.n_fix = p->dirty_list ? p->n_listed : p->n_bunches;
   a.stale = p->stale;
-  a.carries = p->carries;
+  a.carries = p->carries; a.keep_state = 1; a.arrivals = p->arrivals;
   a.slots = p->bind_rows ? p->slots : nullptr;
   a.n_slots = p->n_slots;
   a.dbg_start = p->dbg_start; a.dbg_dirty = p->dbg_dirty; a.dbg_heads = p->dbg_heads;
@@ -2982,6 +3031,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   const size_t o_cb = off; off = align256(off + sizeof(int64_t) * ((size_t)count + 1));
   const size_t o_bs = off; off = align256(off + sizeof(BunchState) * (size_t)(nb_all + 1));
   const size_t o_bi = off; off = align256(off + sizeof(int4) * (size_t)(nb_all + 1));
+  const size_t o_ar = off; off = align256(off + sizeof(int32_t) * (size_t)(nb_all + 1));
   const size_t o_al = off; off = align256(off + sizeof(int32_t));
 
   sss_plan p = new sss_plan_s();
@@ -3008,6 +3058,7 @@ int sss_batch_plan_create(int count, const sss_csr_desc *mats, sss_dtype dt, con
   for (int i = 0; i < count; ++i) {
     MatCtx &c = ctx[(size_t)i];
     c.state = reinterpret_cast<BunchState *>(base + o_bs) + bb[(size_t)i];
+    c.arrivals = reinterpret_cast<int32_t *>(base + o_ar) + bb[(size_t)i];
   }
   // host arrays stay alive until the stream synchronisation below
   if (count > 0)
