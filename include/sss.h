@@ -194,9 +194,9 @@ int sss_csr_spmv_stage2(sss_plan p, const int32_t *row_ptr, void *y, void *strea
 int sss_csr_spmv_stage2_host(sss_plan p, const int32_t *row_ptr, void *y);
 
 /* The one-call form of the method in double precision: y = A x with a tile
- * schedule picked from nnz (W = 4, S = 1 below 500,000 nonzeros, then W = 8
- * with S = 1, 2 and, from 8 million on, the default 5).  Keeps an internal plan per (device, stream, m, n, nnz)
- * that it allocates on first use (so the first call for a new size on a
+ * schedule picked from nnz (W = 4, S = 1 below 650,000 nonzeros, then W = 8
+ * with S = 1, from 2.3 million on 2 and from 8 million on the default 5).
+ * Keeps an internal plan per (device, stream, m, n, nnz) that it allocates on first use (so the first call for a new size on a
  * stream is not graph-capturable; later calls are) and keeps until the
  * process ends or sss_csr_spmv_cache_clear.  Calls on one stream run in
  * order; calls of the same size on

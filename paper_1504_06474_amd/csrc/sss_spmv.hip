@@ -2275,16 +2275,24 @@ int check_call(sss_plan p, const int32_t *row_ptr, const int32_t *col, const voi
 // give that up.  us per product cached / streamed, one matrix again and again:
 // 120 MB power law 62.2 / 72.0, 163 MB 27-point stencil 33.3 / 36.8, 248 MB FEM
 // band 41.0 / 45.4, 285 MB FEM band 46.6 / 51.7, 322 MB FEM band 60.6 / 61.0,
-// FP32 320 MB 63.5 / 61.8, 455 MB 27-point stencil 89.1 / 85.3.  Three in turn
-// streaming is ahead from 87 MB on (160 MB 5-point stencil 34.5 / 31.9, 322 MB
-// FEM band 63.5 / 61.4), behind below (78 MB power law 38.4 / 42.1); a program
-// that iterates has one.  Where x is 8 MB or more, twice an XCD's L2, the
-// misses of the gathers hide where the matrix comes from, and streaming is
-// ahead from 87 MB on either way (one again and again / three in turn, cached
-// against streamed: power law 1M rows 167 / 181, 171 / 171; Poisson 1M rows 108
-// / 110, 103 / 104; dense rows 1M 71.0 / 72.9, 67.7 / 69.3; 5-point stencil
-// 31.6 / 34.4, 31.8 / 31.9).
-constexpr int64_t kStreamBytes = 300000000, kStreamX = 8000000, kStreamBytesX = 87000000;
+// FP32 320 MB 63.5 / 61.8, 455 MB 27-point stencil 89.1 / 85.3.
+// Where x has outgrown what an XCD's 4 MiB of L2 keep beside the streamed
+// matrix, keeping the matrix out of it is worth more, and the line is 100 MB.
+// The time streamed over cached, in the mean of random rows, power law, dense
+// rows and a band (W = 8, S = 2), one matrix again and again | three in turn:
+//   x, MB     80 MB           100 MB          140 MB          260 MB
+//   FP64 4.0  1.007 | 1.044   1.043 | 0.981   1.060 | 0.935   1.097 | 0.929
+//        5.0  0.996 | 1.025   1.013 | 0.993   1.032 | 0.941   1.052 | 0.941
+//        5.6  0.954 | 0.990   0.989 | 0.978   0.995 | 0.931   1.005 | 0.923
+//   FP32 4.4  1.022 | 1.050   1.031 | 0.990   1.052 | 0.943   1.084 | 0.943
+//        5.6  0.967 | 0.997   0.982 | 0.969   0.997 | 0.935   1.022 | 0.933
+// so the two uses cross between 5.0 and 5.6 MB of x.  At 80 MB a product alone
+// would gain already, but a CG step, whose vectors pass the cache between
+// products, loses 1.2% (1024^2 Laplacian, 84 MB) and nothing at 97 MB.  The
+// mean hides a spread: from 140 to 300 MB, multiplied again and again, rows that
+// read all over x gain 3 to 9% and a band, whose gathers hit, loses up to 16%;
+// in turn all gain 4 to 9%.
+constexpr int64_t kStreamBytes = 300000000, kStreamX = 5500000, kStreamBytesX = 100000000;
 Form form_of(int64_t m, int64_t n, int64_t nnz, int dt, int64_t n_max) {
   if (n_max * (int64_t)y_size(dt) > 0xfffffff0ll) return kWide;
   const int64_t value = dt == SSS_F64 ? 8 : (dt == SSS_F32 ? 4 : 2);
@@ -2456,15 +2464,16 @@ int launch_batch(sss_plan p, hipStream_t stream) {
 
 // The tile schedule of the one-call forms, which keep no plan of the
 // caller's.  The paper's S = 5 leaves a GPU of 256 CUs idle on all but large
-// matrices (a 317^2 5-point stencil ran on 196 wavefronts, 17.4 us against
-// 7.8 with W = 4, S = 1); each line is where the next schedule's geometric
-// mean over stencils, a FEM band, Poisson, web-like, power-law and dense-row
-// matrices takes over: 352K nonzeros W = 4 S = 1 7% ahead of W = 8 S = 1,
-// 0.9 to 1M 4% behind it; 3.5 to 6M W = 8 S = 2 6% ahead of that; 10 to 20M
-// W = 8 S = 5 13% ahead of S = 2.
+// matrices; each line is where the next schedule's geometric mean over 5- and
+// 27-point stencils, a FEM band, Poisson, web-like, power-law, Zipf and
+// dense-row matrices takes over (three matrices in turn, time of the schedule
+// below the line over the one above it): W = 4, S = 1 over W = 8, S = 1 0.975 at
+// 500K nonzeros, 0.978 at 600K, 1.011 at 700K, 1.017 at 1M; over S = 2 0.975 at
+// 1.4M, 0.988 at 2M, 1.020 at 2.8M, 1.057 at 4M; S = 2 over S = 5 0.991 at 5.6M,
+// 1.005 at 8M, 0.980 at 11M, 1.027 at 16M.
 void one_call_params(int64_t nnz, int *W, int *S) {
-  *W = nnz < 500000 ? 4 : 8;
-  *S = nnz < 2000000 ? 1 : (nnz < 8000000 ? 2 : 5);
+  *W = nnz < 650000 ? 4 : 8;
+  *S = nnz < 2300000 ? 1 : (nnz < 8000000 ? 2 : 5);
 }
 
 std::mutex g_cache_mu;

@@ -216,3 +216,30 @@ def test_bf16_odd_last_value(W):
             for bind in (True, False):
                 plan = sss.Plan(A.m, A.n, A.nnz, dtype=torch.bfloat16, W=W, S=S, row_ptr=rp, bind_rows=bind)
                 assert_exact(run(plan, rp, col, v, xx, A.m, torch.float32).double().numpy(), want)
+
+
+@pytest.mark.parametrize("nnz,W,S", [(649_999, 4, 1), (650_000, 8, 1), (2_299_999, 8, 1), (2_300_000, 8, 2),
+                                     (7_999_999, 8, 2), (8_000_000, 8, 5)])
+def test_one_call_schedule(nnz, W, S):
+    """The one-call forms run the schedule that their lines give: the bits of a
+    plan of that W and S, on both sides of each line."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note(f"[gpu-test] one-call schedule {nnz}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nnz)
+    m = 3001
+    lens = torch.full((m,), nnz // m, dtype=torch.int64, device="cuda")
+    lens[: nnz % m] += 1
+    rp = torch.zeros(m + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=rp[1:])
+    rp = rp.to(torch.int32)
+    col = torch.randint(0, 5000, (nnz,), generator=g, device="cuda", dtype=torch.int32)
+    v = torch.rand(nnz, generator=g, device="cuda", dtype=torch.float64) - 0.5
+    x = torch.rand(5000, generator=g, device="cuda", dtype=torch.float64) - 0.5
+    want = sss.Plan(m, 5000, nnz, W=W, S=S).execute(rp, col, v, x)
+    other = sss.Plan(m, 5000, nnz, W=16, S=3).execute(rp, col, v, x)
+    assert not torch.equal(other, want)  # (the bits do tell schedules apart)
+    for call in (sss.csr_spmv, sss.csr_spmv_noalloc):
+        assert torch.equal(call(rp, col, v, x, torch.empty_like(want)), want)
+    sss.csr_spmv_cache_clear()
