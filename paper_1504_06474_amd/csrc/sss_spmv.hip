@@ -329,6 +329,7 @@ struct MatCtx {
   const int4 *slots;     // bound plans (and calls that made them), per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
                          // dirty_list), slot_need, 0>; NULL: slot = bunch
   int64_t n_slots;
+  int64_t n_shares;      // fused kernel, single matrices: its wavefronts, which share the leading rows
   int32_t *dbg_start;    // debug plans only
   int32_t *dbg_dirty;
   uint32_t *dbg_heads;
@@ -1025,34 +1026,27 @@ struct Bunch {
         y_store((y_t)(part[0] + tx), &y[start]);
         if constexpr (DOT) dot += x_row * (part[0] + tx);
       }
+      // (a loop of its own past those, with the next chunk's entries read ahead,
+      // is 12% faster there and costs every kernel 0.3 us: 60K Poisson rows 7.3
+      // for 6.9 us)
       int k = 1;
-      auto store_rows = [&](int r, bool in, uint64_t filled) {
+      for (int c = (start + 1 - r0) / kWave; r0 + c * kWave < stop; ++c) {
+        const int r = r0 + c * kWave + lane;
+        const bool in = r > start && r < stop;
+        uint64_t filled;
+        if (c < kWave) {
+          filled = ((uint64_t)(uint32_t)lane_value((int)(filled_rows >> 32), c) << 32) |
+                   (uint32_t)lane_value((int)(uint32_t)filled_rows, c);
+          filled &= __ballot(in);
+        } else {
+          filled = __ballot(in && rp[r] != rp[r + 1]);
+        }
         const bool mine = __builtin_amdgcn_inverse_ballot_w64(filled);
         const double v = part[min(k + lanes_below(filled), WT - 1)];
         if (in) y_store(mine ? (y_t)v : (y_t)0, &y[r]);
         if constexpr (DOT)
           if (mine) dot += x[r] * v;
         k += __popcll(filled);
-      };
-      int c = (start + 1 - r0) / kWave;
-      for (; c < kWave && r0 + c * kWave < stop; ++c) {
-        const int r = r0 + c * kWave + lane;
-        const bool in = r > start && r < stop;
-        const uint64_t filled = ((uint64_t)(uint32_t)lane_value((int)(filled_rows >> 32), c) << 32) |
-                                (uint32_t)lane_value((int)(uint32_t)filled_rows, c);
-        store_rows(r, in, filled & __ballot(in));
-      }
-      // (the next chunk's entries of row_ptr go out before this one's rows)
-      if (r0 + c * kWave < stop) {
-        int r = r0 + c * kWave + lane;
-        int p = rp[min(r, m)], q = rp[min(r + 1, m)];
-        for (; r - lane < stop; r += kWave) {
-          const int p_next = rp[min(r + kWave, m)], q_next = rp[min(r + kWave + 1, m)];
-          const bool in = r > start && r < stop;
-          store_rows(r, in, __ballot(in && p != q));
-          p = p_next;
-          q = q_next;
-        }
       }
       if (lane == 0 && speculator)
         speculator[__popc(dirty_bits & ((1u << t) - 1u))] = make_int4(start, stop, first_tile + t, 0);
@@ -1385,16 +1379,15 @@ __global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = wave_in_block();
   const int64_t g = (int64_t)blockIdx.x * (blockDim.x / kWave) + wid;
-  const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  int4 slot = make_int4(g < a.n_bunches ? (int)g : -1, -1, 0, 0);
-  if (a.slots) slot.x = -1;
-  if (a.slots && g < a.n_slots) slot = uniform_load(a.slots + g);
+  int4 slot = make_int4((int)g, -1, 0, 0);
+  if (g >= (a.slots ? a.n_slots : a.n_bunches)) slot.x = -1;
+  else if (a.slots) slot = uniform_load(a.slots + g);
   if (slot.x < 0) {  // no bunch
     using y_t = typename VT<DT>::y_t;
-    if (a.row_ptr[1] == 0) zero_leading(a.row_ptr, static_cast<y_t *>(a.y), a.m, g, waves, lane);
+    if (a.row_ptr[1] == 0) zero_leading(a.row_ptr, static_cast<y_t *>(a.y), a.m, g, a.n_shares, lane);
     return;
   }
-  fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, g, waves, lds_words + wid * stage1_lds_words(W, a.S), lane);
+  fused_bunch<DT, W, FORM>(a, slot.x, slot.y, slot.z, g, a.n_shares, lds_words + wid * stage1_lds_words(W, a.S), lane);
 }
 
 // The same with the partial sums of x . y, one per workgroup, for bound FP64
@@ -2390,6 +2383,7 @@ int launch_stage1(sss_plan p, const int32_t *row_ptr, const int32_t *col, const 
   int64_t waves1 = a1.slots ? a1.n_slots : p->n_bunches;
   if (!split) waves1 = std::max(waves1, p->m / kLeadingRows);
   const int64_t blocks1 = (waves1 + p->B - 1) / p->B;
+  a1.n_shares = blocks1 * p->B;
   const size_t lds1 = (size_t)p->B * stage1_lds_words(p->W, p->S) * sizeof(uint32_t);
   hipLaunchKernelGGL(k1, dim3((unsigned)blocks1), dim3(p->B * kWave), lds1, stream, a1);
   SSS_HIP(hipGetLastError());
