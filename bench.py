@@ -42,22 +42,22 @@ def paper_bytes(m: int, nnz: int, val_size: int) -> int:
     return (m + 1 + nnz) * 4 + (2 * nnz + m) * val_size
 
 
-def measured_traffic(W: int, S: int, B: int, bind_rows: bool):
-    """HBM-side bytes per fused launch from the committed counter records
-    (one per launch shape), or None when the device code (the kernel source
-    file up to its host side) differs from the one the counters were taken
-    on, or no record has this launch shape."""
+def measured_traffic(W: int, S: int, B: int, bind_rows: bool, root: str = ""):
+    """HBM-side bytes per product (its fused launch and its sss_carries) from the
+    committed counter records, one per launch shape, or None when sss_spmv.hip
+    is no longer the file the counters were taken on, or no record has this
+    launch shape.  The whole file counts: its host side picks the kernel's form
+    and the order of the bunches."""
     import hashlib
-    here = os.path.dirname(os.path.abspath(__file__))
+    root = root or os.path.dirname(os.path.abspath(__file__))
     try:
-        doc = json.load(open(os.path.join(here, "profiles", "traffic.json")))
-        src = open(os.path.join(here, "paper_1504_06474_amd", "csrc", "sss_spmv.hip"), "rb").read()
+        doc = json.load(open(os.path.join(root, "profiles", "traffic.json")))
+        src = open(os.path.join(root, "paper_1504_06474_amd", "csrc", "sss_spmv.hip"), "rb").read()
     except (OSError, ValueError):
         return None
-    src = src[:src.index(b"struct sss_plan_s {")]  # the device code: every kernel precedes the host side
     if hashlib.sha256(src).hexdigest()[:16] != doc.get("source_sha256_16"):
         return None
-    for rec in doc.get("sss_fused", []):
+    for rec in doc.get("product", []):
         if (W, S, B) == (rec["W"], rec["S"], rec["B"]) and bool(rec["bind_rows"]) == bool(bind_rows):
             return int(rec["fetch_kib_raw"] * doc["fetch_factor"] * 1024 + rec["write_kib_raw"] * doc["write_factor"] * 1024)
     return None
@@ -94,6 +94,25 @@ def _finite(v):
         return [_finite(u) for u in v]
     if isinstance(v, float) and not np.isfinite(v):
         return None
+    return v
+
+
+# what the line leaves out of the blocks beside the headline: whole tables, and
+# the figures behind the ones it gives
+_DETAIL = ("probe", "with_rows", "rowwise_us", "gather_ceiling", "grid_", "vs_rowwise_by_class", "picks_over_10pct", "err_",
+           "S_counts", "floor", "stage1_", "stage2_us", "copies_rotated", "alg_bytes", "top1", "n_bunches", "separate_",
+           "speedup_vs_separate_graph", "batched_GFLOPs", "max_err_scaled", "persistent_", "stream_gather", "best_rowwise",
+           "val_streamed", "timing", "speedup_vs_best_rowwise")
+
+
+def _brief(v, depth: int = 0):
+    """The blocks beside the headline in five significant digits, without their
+    tables: with them the line is 22 KB, more than a log's tail keeps
+    (--record writes all of it)."""
+    if isinstance(v, dict):
+        return {k: _brief(u, depth + 1) for k, u in v.items() if depth == 0 or not k.startswith(_DETAIL)}
+    if isinstance(v, float) and np.isfinite(v):
+        return float(f"{v:.5g}")
     return v
 
 
@@ -954,6 +973,8 @@ def main():
                     help="search each thread-bunch's first row in every call instead of once at plan time")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--record", default="", metavar="FILE",
+                    help="write the whole record, with the tables that the printed line leaves out, to FILE")
     ap.add_argument("--mode", choices=["spmv", "copy"], default="spmv")
     ap.add_argument("--skip-precision", action="store_true", help="skip the FP32/BF16 comparison")
     ap.add_argument("--skip-batched", action="store_true", help="skip the 512-matrix batched comparison")
@@ -1250,7 +1271,12 @@ def main():
     if not args.no_cpu_baseline:
         log("[bench] timing the CPU oracle")
         out["cpu_baseline"] = cpu_baseline(A, x, args.cpu_seconds)
-    print(json.dumps(_finite(out), allow_nan=False), flush=True)
+    out = _finite(out)
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(out, f, allow_nan=False)
+    out["extras"] = _brief(out["extras"])
+    print(json.dumps(out, allow_nan=False), flush=True)
 
 
 if __name__ == "__main__":

@@ -74,3 +74,41 @@ def test_algorithmic_bytes_of_the_benchmark_matrix():
     assert bench.alg_bytes(1_000_000, 1_000_000, 19_189_716, 4, 4) == 19_189_716 * 8 + 4_000_004 + 8_000_000
     # rectangular: x has n entries, y has m
     assert bench.alg_bytes(3, 5, 7, 8, 8) == 7 * 12 + 4 * 4 + 5 * 8 + 3 * 8
+
+
+def test_line_leaves_the_tables_out():
+    """What is printed of the blocks beside the headline: their figures, not
+    their tables; the headline's own block whole."""
+    table = {f"W{w}S{s}": 100.0 + w + s for w in (4, 8, 16) for s in (1, 2, 4, 8)}
+    block = {"us": 1234.56789, "GFLOPs": 148.28, "gather_ceiling": {"probe_us": table, "with_rows": table},
+             "vs_rowwise": {"rowwise_us": table, "speedup_vs_csr_vector": 10.0}, "grid_us_by_class": table,
+             "err_vs_f64": table, "floors": {"stream_us": 1.0}, "bad": None}
+    got = bench._brief({"stage1_us": 160.0, "precision": block})
+    assert got == {"stage1_us": 160.0, "precision": {"us": 1234.6, "GFLOPs": 148.28, "vs_rowwise": {"speedup_vs_csr_vector": 10.0},
+                                                     "bad": None}}
+
+
+def test_traffic_records_hold_for_the_whole_source(tmp_path):
+    """The counter records are those of one sss_spmv.hip: a changed rule on its
+    host side (which form, which order) makes them stale as a changed kernel
+    does."""
+    import hashlib
+    import json
+    import os
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join("paper_1504_06474_amd", "csrc")
+    with open(os.path.join(root, csrc, "sss_spmv.hip")) as f:
+        src = f.read()
+    (tmp_path / csrc).mkdir(parents=True)
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / csrc / "sss_spmv.hip").write_text(src)
+    rec = {"W": 8, "S": 1, "B": 2, "bind_rows": True, "fetch_kib_raw": 100.0, "write_kib_raw": 10.0}
+    doc = {"source_sha256_16": hashlib.sha256(src.encode()).hexdigest()[:16], "fetch_factor": 2.0, "write_factor": 1.0,
+           "product": [rec]}
+    (tmp_path / "profiles" / "traffic.json").write_text(json.dumps(doc))
+    assert bench.measured_traffic(8, 1, 2, True, str(tmp_path)) == 210 * 1024
+    assert bench.measured_traffic(8, 2, 2, True, str(tmp_path)) is None
+    changed = src.replace("kOrderMinX = ", "kOrderMinX = 1 + ")
+    assert changed != src
+    (tmp_path / csrc / "sss_spmv.hip").write_text(changed)
+    assert bench.measured_traffic(8, 1, 2, True, str(tmp_path)) is None
