@@ -115,3 +115,60 @@ def test_cg_repeats_over_plans_in_column_order():
         if seen is not None:
             assert torch.equal(x, seen)
         seen = x
+
+
+@pytest.mark.parametrize("sort", [True, False], ids=["sorted", "unsorted"])
+@pytest.mark.parametrize("kind", ["f64", "f32", "bf16"])
+def test_column_order_changes_no_bit(kind, sort):
+    """The order decides when a bunch runs, not what it adds: the bits of the
+    two-stage form, for columns sorted within their rows or not."""
+    import torch
+    from helpers import to_dev_precision
+    from paper_1504_06474_amd import sss
+    note(f"[gpu-test] column order, bits {kind} {sort}")
+    n = N if kind == "f64" else 2 * N
+    A, x = csr_from_lengths(LENGTHS["mixed"], n, seed=4, int_valued=False)
+    if not sort:
+        rng = np.random.default_rng(8)
+        for r in np.flatnonzero(np.diff(A.row_ptr) > 1):
+            a, b = A.row_ptr[r], A.row_ptr[r + 1]
+            A.col[a:b] = rng.permutation(A.col[a:b])
+    rp, col, v, xx = to_dev_precision(A, x, kind)[:4]
+    for W, S in ((4, 1), (8, 1)):
+        args = dict(dtype=v.dtype, W=W, S=S, row_ptr=rp)
+        want = sss.Plan(A.m, A.n, A.nnz, debug=True, **args).execute(rp, col, v, xx).clone()
+        assert torch.equal(sss.Plan(A.m, A.n, A.nnz, bind_rows=True, **args).execute(rp, col, v, xx), want)
+
+
+@pytest.mark.parametrize("B", [1, 3])
+def test_column_order_row_ptr_rewritten(B):
+    """Slots in column order carry the rows and spans of the row_ptr they were
+    made from.  Rewritten in place (same rows, same entries): short rows
+    only, the long rows elsewhere, empty rows in front, behind and between."""
+    import torch
+    from paper_1504_06474_amd import sss
+    note(f"[gpu-test] column order, rewritten B={B}")
+    lens = np.array(LENGTHS["mixed"], dtype=np.int64)
+    A, x = csr_from_lengths(lens, N, seed=2)
+    rp, col, v, xx = to_dev(A, x)
+    plan = sss.Plan(A.m, A.n, A.nnz, W=4, S=1, B=B, row_ptr=rp, bind_rows=True)
+    rng = np.random.default_rng(B)
+    even = np.full(A.m, A.nnz // A.m, dtype=np.int64)
+    even[: A.nnz % A.m] += 1
+    few = np.zeros(A.m, dtype=np.int64)
+    few[rng.choice(A.m, 5000, replace=False)] = 1
+    few *= A.nnz // 5000
+    few[np.flatnonzero(few)[-1]] += A.nnz - few.sum()
+    front = np.concatenate([np.zeros(A.m - 2000, np.int64), np.full(2000, A.nnz // 2000, np.int64)])
+    front[-1] += A.nnz - front.sum()
+    y = torch.empty(A.m, dtype=torch.float64, device="cuda")
+    for new in (lens[::-1].copy(), rng.permutation(lens), even, few, front, front[::-1].copy(), lens):
+        rp2 = np.zeros(A.m + 1, dtype=np.int32)
+        np.cumsum(new, out=rp2[1:])
+        assert rp2[-1] == A.nnz
+        rp.copy_(torch.from_numpy(rp2).to("cuda"))
+        want = oracle.spmv(rp2, A.col, A.val, x)
+        for _ in range(2):
+            y.fill_(float("nan"))
+            plan.execute(rp, col, v, xx, y)
+            assert_exact(y.cpu().numpy(), want)
