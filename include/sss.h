@@ -160,7 +160,9 @@ int sss_csr_spmv_plan_workspace_size(int64_t m, int64_t n, int64_t nnz, sss_dtyp
  * checks each thread-bunch's stored first row against row_ptr's contents
  * (rp[r] <= b < rp[r + 1]) and searches again where it no longer holds, so
  * rewriting that array in place (same m and nnz) gives a correct y, at the
- * search's cost; a dirty tile in a bunch the plan did not list then marks
+ * search's cost (a row that crosses into bunches by more than 64 entries where
+ * the plan saw none, and so makes no second launch, is added up by the last of
+ * its bunches to finish); a dirty tile in a bunch the plan did not list then marks
  * the plan stale, and from that call on stage 2 (debug plans and
  * sss_csr_spmv_stage2) also re-arranges the unlisted dirty bunches (one after
  * another per 64 bunches: correct, slower; make a new plan for the new

@@ -769,8 +769,8 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 // TB/s), 1414^2 5-point stencil FP64 39.9 / 31.9 us (160 MB: 4.0 / 5.0 TB/s),
 // FEM band 778K x 50 FP32 74.2 / 61.7 us (320 MB: 4.3 / 5.2 TB/s), 1M-row
 // power law FP64 182.9 / 171 us and BF16 117.8 / 111 us (both in column
-// order), 30K-row web-like FP32 12.3 / 6.2 us (5.8 us of that is the host's
-// call; it was 9.3).  The double sums gave the band 2.5 of its 12 us.
+// order), 30K-row web-like FP32 12.3 / 5.8 to 7.3 us over boxes (5.8 us of that is
+// the host's call; it was 9.3).  The double sums gave the band 2.5 of its 12 us.
 constexpr int kBack = kWave;
 
 // Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
