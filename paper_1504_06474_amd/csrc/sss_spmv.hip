@@ -2193,9 +2193,9 @@ AuxLayout aux_layout(int64_t nnz, int W, int S, bool bind, bool debug, bool call
   L.state = off; off += 2 * align256(sizeof(int32_t) * (nb + 1)) + 2 * align256(sizeof(double) * (nb + 1));
   L.spec = off; off = align256(off + sizeof(int4) * (nb * (size_t)S + 1));
   if (bind || call_order) {
-    L.brow = off; off = align256(off + sizeof(int32_t) * (nb + 1));
+    L.brow = off; off += sizeof(int32_t) * nb;
+    L.stale = off; off = align256(off + sizeof(int32_t) * 2);  // (behind the rows: the plan copies both at once)
     L.dlist = off; off = align256(off + sizeof(int32_t) * (nb + 1));
-    L.stale = off; off = align256(off + sizeof(int32_t) * 2);
   }
   if (bind || call_order) {
     L.slots = off; off = align256(off + sizeof(int4) * (nb + kXcds * kMaxB));
@@ -2669,10 +2669,10 @@ int plan_list_dirty(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t
   hipLaunchKernelGGL(sss_mark_dirty_bunches, dim3(blocks), dim3(256), 0, s, row_ptr, (int32_t)p->m, SWT,
                      reinterpret_cast<uint32_t *>(p->bunch_row), 0x80000000u);
   SSS_HIP(hipGetLastError());
-  std::vector<int32_t> br(nb);
-  SSS_HIP(hipMemcpyAsync(br.data(), p->bunch_row, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  SSS_HIP(hipMemcpyAsync(&p->carries, p->stale + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  std::vector<int32_t> br(nb + 2);  // the first rows and, behind them, the stale words
+  SSS_HIP(hipMemcpyAsync(br.data(), p->bunch_row, br.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   SSS_HIP(hipStreamSynchronize(s));
+  p->carries = br[nb + 1];
   std::vector<int32_t> list;
   for (size_t tb = 0; tb < nb; ++tb)
     if (br[tb] < 0) list.push_back((int32_t)tb);
