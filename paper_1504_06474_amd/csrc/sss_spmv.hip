@@ -1245,15 +1245,25 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     if (r < m && q == p && wave_prev(p, -1) != p && p > b0 && p <= bS) atomicOr(dflag, 1u << ((p - b0 - 1) / WT));
     const uint64_t filled = __ballot(q != p);
     if (lane == (rbase - r0) / kWave) filled_rows = filled;
-    for (int t = 0; t <= S; ++t) {
-      const int c = __popcll(__ballot(p <= lane_value(my_b, t)));
-      const int p_last_in = lane_value(p, c > 0 ? c - 1 : 0);
-      if (lane == t) {
-        my_count += c;
-        if (c > 0) my_rp = p_last_in;
+    const int p_first = lane_value(p, 0), p_last = lane_value(p, kWave - 1);
+    // empty rows only: every tile boundary counts all of them or none (100K Poisson
+    // rows and 100K empty ones behind them: 1,456 -> 929 us; two stages 1,431)
+    if (p_first == p_last) {
+      if (p_first <= my_b) {
+        my_count += kWave;
+        my_rp = p_first;
+      }
+    } else {
+      for (int t = 0; t <= S; ++t) {
+        const int c = __popcll(__ballot(p <= lane_value(my_b, t)));
+        const int p_last_in = lane_value(p, c > 0 ? c - 1 : 0);
+        if (lane == t) {
+          my_count += c;
+          if (c > 0) my_rp = p_last_in;
+        }
       }
     }
-    return lane_value(p, kWave - 1) <= bS && rbase + (kWave - 1) < m;
+    return p_last <= bS && rbase + (kWave - 1) < m;
   };
   // the two chunks that are there hold the bunch (apart from the loop below,
   // whose loads would make this wait for tile 0's gathers)
