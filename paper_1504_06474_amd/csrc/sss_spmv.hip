@@ -742,14 +742,14 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 //  * A dirty tile stores its partials straight to its non-empty rows and
 //    zeroes the empty ones, from row_ptr and the partials in LDS, instead of
 //    storing them side by side for a re-arrangement to read back.
-//  * The bunch in which a row ends completes a row that began at most kBack
-//    nonzeros before the bunch: it loads and sums those itself (back_sum),
-//    and the bunch before drops its tail.  No bunch waits for another.  Rows
-//    that began further back (long crossing rows) are left to sss_carries,
-//    which adds the synchronizer entries in double as stage 2 does; where the
-//    plan saw no such row at plan time (MatCtx::carries = 0) that launch is
-//    left out, and where row_ptr was rewritten in place since, the last of the
-//    row's bunches to finish adds them up (finish_row).
+//  * Where no row that crosses into a bunch began more than kBack nonzeros
+//    before it (no long crossing row, a plan finds: MatCtx::carries = 0), the
+//    bunch in which a row ends loads and sums those itself (back_sum), and the
+//    bunch before drops its tail: no second launch, and no bunch waits for
+//    another.  Else sss_carries completes the rows that cross, adding the
+//    synchronizer entries in double as stage 2 does (see back_limit).  A long
+//    crossing row of a row_ptr rewritten in place since the plan saw none is
+//    added up by the last of its bunches to finish (finish_row).
 //  * The leading empty rows are shared out over the bunches.
 //
 // What bounds it is the latency of the loads a wavefront waits for one after
@@ -774,14 +774,17 @@ __global__ __launch_bounds__(256) void sss_stage1(MatCtx a) {
 constexpr int kBack = kWave;
 
 // Row [rs, re) against the bunch [b0, b0 + SWT) that holds some of it: is it
-// a long crossing row (left to sss_carries)?
-__device__ __forceinline__ bool long_crossing(int64_t rs, int64_t re, int64_t b0, int64_t SWT) {
-  return re > b0 + SWT ? true : rs < b0 - kBack;
+// a long crossing row (left to sss_carries)?  back: how many entries before the
+// bunch it may begin.
+__device__ __forceinline__ bool long_crossing(int64_t rs, int64_t re, int64_t b0, int64_t SWT, int back) {
+  return re > b0 + SWT ? true : rs < b0 - back;
 }
-// the entries of that row before the bunch that the bunch sums itself
-__device__ __forceinline__ int back_entries(int64_t rs, int64_t re, int64_t b0, int64_t SWT) {
-  return long_crossing(rs, re, b0, SWT) ? 0 : (int)(b0 - rs);
-}
+// Where the plan (or an unbound call) makes the carry launch anyway, it takes
+// every row that crosses: reading the entries before each bunch again would
+// only cost.  With / without that, us per product at W = 4, S = 1: 100K rows of 70
+// bound 41.7 / 38.4, searched 52.1 / 47.2 (two stages 39.4, 48.2); 50K Poisson
+// rows of 60 FP32, the selector's plan, 18.1 / 16.9; 256 uneven matrices 707 / 702.
+__device__ __forceinline__ int back_limit(bool carries) { return carries ? 0 : kBack; }
 
 // How the loads go out.
 //  kCached: plain loads.
@@ -792,14 +795,16 @@ __device__ __forceinline__ int back_entries(int64_t rs, int64_t re, int64_t b0, 
 enum Form { kCached, kStreamed, kWide };
 
 // What a plan tells a bunch of its first row, rp[r0] <= b0 < rp[r0 + 1]: its
-// back_entries (7 bits), and above them how many entries of row_ptr after
+// entries before the bunch that the bunch sums itself (7 bits), and above them how many entries of row_ptr after
 // rp[r0] the bunch needs, up to the first that is past its end (kSpanMax: that
 // many or more, which the bunch finds itself).
 constexpr int kSpanMax = 1 << 22;
 // r_next: the next bunch's first row, m after the last bunch.
 __device__ __forceinline__ int slot_need(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb, int32_t r,
-                                         int32_t r_next) {
-  const int back = r < m ? back_entries(rp[r], rp[r + 1], tb * SWT, SWT) : 0;
+                                         int32_t r_next, bool carries) {
+  const int64_t b0 = tb * SWT;
+  const int back =
+      r < m && !long_crossing(rp[r], rp[r + 1], b0, SWT, back_limit(carries)) ? (int)(b0 - rp[r]) : 0;
   return back | (int)imin64((int64_t)(r_next < m ? r_next + 1 : m) - r, kSpanMax) << 8;
 }
 
@@ -1306,7 +1311,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
 
   // ---- does this bunch write y[r0]: it does when the row ends here and is
   // no long crossing row; the row's entries before the bunch are summed here
-  const bool is_long = r0 < m && long_crossing(first_rs, first_re, b0, SWT);
+  const bool is_long = r0 < m && long_crossing(first_rs, first_re, b0, SWT, back_limit(a.carries));
   const bool own_first = r0 < m && !is_long;
   double before = 0.0;
   if (own_first && first_rs < b0) {
@@ -1453,7 +1458,7 @@ __global__ void sss_bunch_rows(const int32_t *__restrict__ rp, int32_t m, int64_
        tb += (int64_t)gridDim.x * blockDim.x) {
     const int32_t r = rightmost_row(rp, m, tb * SWT);
     out[tb] = r;
-    if (r < m && long_crossing(rp[r], rp[r + 1], tb * SWT, SWT)) *any_long = 1;
+    if (r < m && long_crossing(rp[r], rp[r + 1], tb * SWT, SWT, kBack)) *any_long = 1;
   }
 }
 
@@ -1575,18 +1580,18 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t k, int64_t t, int B) { retur
 
 // A slot's entry for bunch tb (bunch_row: first rows, with the top bit).
 __device__ __forceinline__ int4 slot_entry(const int32_t *__restrict__ rp, int32_t m, int64_t SWT, int64_t tb,
-                                           int64_t n_bunches, const int32_t *__restrict__ bunch_row) {
+                                           int64_t n_bunches, const int32_t *__restrict__ bunch_row, bool carries) {
   const int32_t row = bunch_row[tb];
   const int32_t next = tb + 1 < n_bunches ? bunch_row[tb + 1] & 0x7fffffff : m;
-  return make_int4((int)tb, row, slot_need(rp, m, SWT, tb, row & 0x7fffffff, next), 0);
+  return make_int4((int)tb, row, slot_need(rp, m, SWT, tb, row & 0x7fffffff, next, carries), 0);
 }
 
 // Slots in bunch order.
 __global__ __launch_bounds__(256) void sss_slots(const int32_t *__restrict__ rp, int32_t m, int64_t SWT,
                                                  int64_t n_bunches, const int32_t *__restrict__ bunch_row,
-                                                 int4 *__restrict__ slots) {
+                                                 bool carries, int4 *__restrict__ slots) {
   const int64_t tb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tb < n_bunches) slots[tb] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row);
+  if (tb < n_bunches) slots[tb] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row, carries);
 }
 
 // Slots in column order; in bunch order where fewer than one bunch in
@@ -1596,7 +1601,8 @@ __global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restri
                                                          int64_t n_bunches, const int32_t *__restrict__ bunch_row,
                                                          const uint32_t *__restrict__ keys, int64_t n_slots, int B,
                                                          const uint32_t *__restrict__ hist,
-                                                         uint32_t *__restrict__ cursor, int4 *__restrict__ slots) {
+                                                         uint32_t *__restrict__ cursor, bool carries,
+                                                         int4 *__restrict__ slots) {
   __shared__ uint32_t first[kOrderBins], count[kOrderBins + 1], base[kOrderBins + 1];
   const int t = threadIdx.x;
   static_assert(kOrderBins == 256, "one bin per thread");
@@ -1614,7 +1620,7 @@ __global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restri
   const int64_t tb = (int64_t)blockIdx.x * blockDim.x + t;
   if (n_long * kOrderShare < n_bunches) {
     if (tb < n_slots)
-      slots[tb] = tb < n_bunches ? slot_entry(rp, m, SWT, tb, n_bunches, bunch_row) : make_int4(-1, 0, 0, 0);
+      slots[tb] = tb < n_bunches ? slot_entry(rp, m, SWT, tb, n_bunches, bunch_row, carries) : make_int4(-1, 0, 0, 0);
     return;
   }
   uint32_t key = 0, mine = 0;
@@ -1638,7 +1644,7 @@ __global__ __launch_bounds__(256) void sss_order_scatter(const int32_t *__restri
       i += n_long;
       slot = xcd_slot(i % kXcds, i / kXcds, B);
     }
-    slots[slot] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row);
+    slots[slot] = slot_entry(rp, m, SWT, tb, n_bunches, bunch_row, carries);
   } else if (tb < n_slots) {
     slots[xcd_slot(tb % kXcds, tb / kXcds, B)] = make_int4(-1, 0, 0, 0);
   }
@@ -1660,9 +1666,9 @@ __global__ void sss_batch_bunch_info(const MatCtx *__restrict__ mats, const int6
     const MatCtx &a = mats[lo];
     const int64_t tb = g - bunch_base[lo], SWT = (int64_t)a.S * a.W * kWave;
     const int32_t r = rightmost_row(a.row_ptr, a.m, tb * SWT);
-    if (r < a.m && long_crossing(a.row_ptr[r], a.row_ptr[r + 1], tb * SWT, SWT)) *any_long = 1;
+    if (r < a.m && long_crossing(a.row_ptr[r], a.row_ptr[r + 1], tb * SWT, SWT, kBack)) *any_long = 1;
     const int32_t next = tb + 1 < a.n_bunches ? rightmost_row(a.row_ptr, a.m, (tb + 1) * SWT) : a.m;
-    out[g] = make_int4(lo, r, (int)tb, slot_need(a.row_ptr, a.m, SWT, tb, r, next));
+    out[g] = make_int4(lo, r, (int)tb, slot_need(a.row_ptr, a.m, SWT, tb, r, next, false));
   }
 }
 
@@ -1746,6 +1752,7 @@ __device__ __forceinline__ void batch_entry(const BatchArgs &b, int64_t g, int4 
   bi = uniform_load(b.bunch_info + g);
   a = uniform_load(b.mats + bi.x);
   a.carries = a.keep_state = b.carries;
+  if (b.carries) bi.w &= ~0xff;  // (found before the plan knew: no entries before the bunch)
 }
 
 
@@ -1903,8 +1910,9 @@ __device__ __forceinline__ void fixup_dirty(const MatCtx &a, const int64_t tb, Y
 // the kernel's occupancy); longer runs (rows longer than kShortRun bunches)
 // by the whole wavefront: coalesced loads, per-lane partial sums, then a
 // fixed-shape tree over the lanes, so the rounding does not depend on timing.
-// LONG_ONLY: only the long crossing rows, the others are complete.
-template <typename YT, bool LONG_ONLY>
+// CROSSING_ONLY: only rows that began before their bunch or end behind it, the
+// others are complete.
+template <typename YT, bool CROSSING_ONLY>
 __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chunk0, const int lane, void *lds) {
   const int32_t *__restrict__ rp = a.row_ptr;
   YT *y = static_cast<YT *>(a.y);
@@ -1937,8 +1945,8 @@ __device__ __forceinline__ void fixup_carries(const MatCtx &a, const int64_t chu
   const bool is_long = head && (tb + kShortRun < nb) && (s_idx[lane + kShortRun] == idx);
   if (head && !is_long) {
     const int rs = rp[idx];
-    // (a run of more than one bunch holds a long crossing row)
-    if (!LONG_ONLY || long_crossing(rs, rp[idx + 1], tb * SWT, SWT)) {
+    // (the row of a run of more than one bunch ends behind its first)
+    if (!CROSSING_ONLY || long_crossing(rs, rp[idx + 1], tb * SWT, SWT, back_limit(true))) {
       // sync_idx is non-decreasing (entries past the end read -1): the run is
       // the prefix of the next kShortRun entries equal to idx
       double sum = 0.0;
@@ -2022,8 +2030,8 @@ __global__ __launch_bounds__(1024) void sss_fixup(MatCtx a) {
   fixup_leading<YT>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
-// After the fused kernel: the carries of the long crossing rows, one
-// wavefront per 64 bunches.  What it costs is a launch that depends on the
+// After the fused kernel, where some row is a long crossing row: the carries of
+// the rows that cross, one wavefront per 64 bunches.  What it costs is a launch that depends on the
 // one before it (4 to 5 us behind a running kernel) and one chain of loads,
 // so a plan that knows it has no such row leaves it out.
 template <typename YT>
@@ -2368,7 +2376,7 @@ int launch_call_order(sss_plan p, const int32_t *row_ptr, MatCtx &a, hipStream_t
                      (int32_t)p->nnz, (int64_t)SWT, nb, p->bunch_row, keys, hist);
   SSS_HIP(hipGetLastError());
   hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, row_ptr, m,
-                     (int64_t)SWT, nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
+                     (int64_t)SWT, nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->carries != 0, p->slots);
   SSS_HIP(hipGetLastError());
   a.slots = p->slots;
   a.n_slots = n_slots;
@@ -2657,14 +2665,15 @@ int plan_slots(sss_plan p, const int32_t *row_ptr, int64_t SWT, hipStream_t s) {
     SSS_HIP(hipStreamSynchronize(s));
     if ((nb - (int64_t)n_short) * kOrderShare >= nb) {
       hipLaunchKernelGGL(sss_order_scatter, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0, s, row_ptr, m, SWT,
-                         nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->slots);
+                         nb, p->bunch_row, keys, n_slots, p->B, hist, hist + kOrderBins + 1, p->carries != 0, p->slots);
       SSS_HIP(hipGetLastError());
       p->n_slots = n_slots;
       p->ordered = true;
       return SSS_OK;
     }
   }
-  hipLaunchKernelGGL(sss_slots, dim3(blocks), dim3(256), 0, s, row_ptr, m, SWT, nb, p->bunch_row, p->slots);
+  hipLaunchKernelGGL(sss_slots, dim3(blocks), dim3(256), 0, s, row_ptr, m, SWT, nb, p->bunch_row, p->carries != 0,
+                     p->slots);
   SSS_HIP(hipGetLastError());
   p->n_slots = nb;
   return SSS_OK;

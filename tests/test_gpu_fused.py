@@ -243,3 +243,30 @@ def test_one_call_schedule(nnz, W, S):
     for call in (sss.csr_spmv, sss.csr_spmv_noalloc):
         assert torch.equal(call(rp, col, v, x, torch.empty_like(want)), want)
     sss.csr_spmv_cache_clear()
+
+
+@pytest.mark.parametrize("kind", DTYPES)
+@pytest.mark.parametrize("W,S", [(4, 1), (8, 2), (16, 1)])
+def test_short_crossing_rows_beside_long_ones(kind, W, S):
+    """One row that the carry launch is made for: it then also completes the
+    rows that cross by 1 to 64 entries, bound, searched and in batches, with the
+    two stages' bits."""
+    import torch
+    from paper_1504_06474_amd import sss
+    vt, yt = torch_types(kind)
+    note(f"[gpu-test] crossing rows {kind} W={W} S={S}")
+    SWT = 64 * W * S
+    lens = [SWT - 1, 2, SWT - 65, 64 + 64, SWT - 63 - 64, 63 + 1, 0, 0, SWT - 1] + [37] * 200 + [64, 65, 63, 1] * 30
+    for long_row in ([], [3 * SWT], [SWT + 65], [17 * SWT + 3]):
+        for order in (lens + long_row, long_row + lens):
+            A, x = csr_from_lengths(order, 30_000, seed=len(order), int_valued=False)
+            d = to_dev_precision(A, x, kind)[:4]
+            bits = run(sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=W, S=S, debug=True), *d, A.m, yt)
+            for bind in (True, False):
+                plan = sss.Plan(A.m, A.n, A.nnz, dtype=vt, W=W, S=S, row_ptr=d[0], bind_rows=bind)
+                assert torch.equal(run(plan, *d, A.m, yt), bits), bind
+            for persistent in (False, True):
+                ys = [torch.full((A.m,), float("nan"), dtype=yt, device="cuda") for _ in range(2)]
+                sss.BatchPlan([(*d, y, A.n) for y in ys], dtype=vt, W=W, S=S, persistent=persistent).execute()
+                for y in ys:
+                    assert torch.equal(y.cpu(), bits), persistent
