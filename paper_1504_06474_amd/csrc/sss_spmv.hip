@@ -1089,7 +1089,17 @@ __device__ __forceinline__ void zero_leading(const int32_t *__restrict__ rp, YT 
   const int64_t lo = (int64_t)m * share / shares, hi = (int64_t)m * (share + 1) / shares;
   if (lo >= hi || rp[lo + 1] != 0) return;
   const int64_t end = rp[hi] == 0 ? hi : (int64_t)wave_rightmost(rp, m, 0, lane);
-  for (int64_t r = lo + lane; r < end; r += kWave) y[r] = (YT)0;
+  // 16 bytes a lane: what bounds a wavefront here is how many stores it may have
+  // in flight
+  constexpr int N = 16 / (int)sizeof(YT);
+  typedef YT many __attribute__((ext_vector_type(N), aligned(sizeof(YT))));
+  for (int64_t r = lo + lane * N; r < end; r += kWave * N) {
+    if (r + N <= end) {
+      *reinterpret_cast<many *>(y + r) = (many)(YT)0;
+    } else {
+      for (int64_t i = r; i < end; ++i) y[i] = (YT)0;
+    }
+  }
 }
 
 // The sum of entries first .. end - 1, all of one row, by one wavefront.
