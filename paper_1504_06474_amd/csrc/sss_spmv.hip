@@ -1231,7 +1231,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
   // searched for holds, with every row to the last as its span.
   const bool loaded = ahead && lane_value(rows0, 0) <= b0 && b0 < lane_value(rows0, 1) &&
                       ((int64_t)r0 + span >= m || past_span > bS);
-  if (!loaded) {
+  if (__builtin_expect(!loaded, 0)) {
     if (!known || !(rp[r0] <= b0 && b0 < rp[r0 + 1]))
       r0 = __builtin_amdgcn_readfirstlane(wave_rightmost(rp, m, b0, lane));
   }
@@ -1263,7 +1263,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     const int p_first = lane_value(p, 0), p_last = lane_value(p, kWave - 1);
     // empty rows only: every tile boundary counts all of them or none (100K Poisson
     // rows and 100K empty ones behind them: 1,456 -> 929 us; two stages 1,431)
-    if (p_first == p_last) {
+    if (__builtin_expect(p_first == p_last, 0)) {
       if (p_first <= my_b) {
         my_count += kWave;
         my_rp = p_first;
@@ -1378,9 +1378,9 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     y_store((y_t)(before + u.sync_v), &u.y[r0]);
     if constexpr (DOT) u.dot += u.x[r0] * (before + u.sync_v);
   }
-  if (second_row == 0) zero_leading(rp, u.y, m, share, shares, lane);
+  if (__builtin_expect(second_row == 0, 0)) zero_leading(rp, u.y, m, share, shares, lane);
   const bool shared = is_long && !a.carries && a.arrivals;  // a row that the plan did not know
-  if (shared) {
+  if (__builtin_expect(shared, 0)) {
     if (first_rs < b0 && first_rs > b0 - SWT) u.sync_v += row_part<DT>(a, first_rs, b0, lane);
     if constexpr (DOT)
       if (lane == 0) u.dot += u.x[r0] * u.sync_v;
@@ -1394,7 +1394,7 @@ __device__ __forceinline__ double fused_bunch(const MatCtx &a, const int tb, con
     for (int i = 1; i < 6; ++i) w = lane == i ? words[i] : w;
     if (lane < 6) reinterpret_cast<uint32_t *>(a.state + tb)[lane] = w;
   }
-  if (shared) finish_row<y_t>(a, r0, first_rs, first_re, SWT, lane);
+  if (__builtin_expect(shared, 0)) finish_row<y_t>(a, r0, first_rs, first_re, SWT, lane);
   return u.dot;
 }
 
@@ -1407,7 +1407,9 @@ __global__ __launch_bounds__(256) void sss_fused(MatCtx a) {
   int4 slot = make_int4((int)g, -1, 0, 0);
   if (g >= (a.slots ? a.n_slots : a.n_bunches)) slot.x = -1;
   else if (a.slots) slot = uniform_load(a.slots + g);
-  if (slot.x < 0) {  // no bunch
+  // (the paths that few products take are marked: in line they cost the others'
+  // instruction fetch, a 4,096-row Poisson matrix 13.5 / 13.25 us)
+  if (__builtin_expect(slot.x < 0, 0)) {  // no bunch
     using y_t = typename VT<DT>::y_t;
     if (a.row_ptr[1] == 0) zero_leading(a.row_ptr, static_cast<y_t *>(a.y), a.m, g, a.n_shares, lane);
     return;
