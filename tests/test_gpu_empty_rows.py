@@ -65,7 +65,7 @@ def test_leading_rows_take_their_stores_time():
 def test_rows_between_and_behind_take_one_pass():
     """A million empty rows inside a tile and behind the last entry: one
     wavefront reads their row_ptr twice (to count, to store), 64 a round, each
-    round about a load's latency: 17 ms, where marking the tile 64 times a
+    round about a load's latency: 11 ms, where marking the tile 64 times a
     round and waiting for the stores as well made it 44."""
     note("[gpu-test] empty rows inside a tile, time")
     few = [3] * 20 + [0, 0, 0, 1]
