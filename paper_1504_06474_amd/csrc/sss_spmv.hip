@@ -323,7 +323,7 @@ struct MatCtx {
   int64_t n_fix;             // stage-2 re-arrangement wavefronts: entries of dirty_list, else n_bunches
   int32_t *stale;            // bound plans: set (and never cleared) when stage 1 finds a dirty tile in a
                              // bunch outside dirty_list (row_ptr rewritten in place since plan time)
-  int32_t carries;       // fused kernel: a sss_carries launch follows and completes the long crossing rows
+  int32_t carries;       // fused kernel: a sss_carries launch follows and completes the rows that cross
   int32_t keep_state;    // fused kernel: every bunch stores its state
   int32_t *arrivals;     // bound plans, per bunch: see finish_row (zero between launches)
   const int4 *slots;     // bound plans (and calls that made them), per wavefront slot: <bunch (-1: none), its first row (top bit: listed in
